@@ -314,7 +314,7 @@ def tile_dict(info) -> dict:
 
 
 KERNEL_NAMES = ["step_direct", "step_zmarch", "step_zring", "step_zfront", "step_rolled", "step_zlds", "step_zchain",
-                "step_zpipe", "step_fuse2"]
+                "step_zpipe", "step_fuse2", "smear_run"]
 
 
 def measure_workload(ctx, torch, tl, dev, index, prec, plain=False, passes=5):

@@ -93,15 +93,18 @@ enum { TL_ONELINK = 32 };  /* OR into a precision: a one-link field and the one-
 /* tl_smear / tl_plan_create flags */
 enum {
     TL_PLAIN = 1u,      /* one right-hand side per launch, RHS in succession, eager launches */
-    TL_GRAPH = 2u,      /* capture the n step launches in one HIP graph, replayed per run */
+    TL_GRAPH = 2u,      /* capture the n step launches in one HIP graph, replayed per run (a run that
+                           is one launch is launched as it is) */
     TL_AUTOTUNE = 4u,   /* time the candidate tilings once and keep the fastest (cached per context;
                            with TL_PLAIN timed on one RHS of each lattice shape, weighted by the
                            shape's RHS count); for batched plans of two or more steps the
                            candidates include launches
                            that run two steps each (the first step's result kept on chip, rounded
                            to the storage precision exactly as a store would round it, so the
-                           result is bit-identical to one step per launch) */
-    TL_ONE_STEP = 8u    /* tune over tilings of one step per launch only (no two-step launches) */
+                           result is bit-identical to one step per launch), and for plans of four
+                           or more steps launches that run all of them (the two-links kept in
+                           registers, the vectors exchanged between workgroups; the same bits) */
+    TL_ONE_STEP = 8u    /* tune over tilings of one step per launch only */
 };
 
 /* reduction kinds.  TL_NORM2 and TL_DOT are the spatial sums over the sites x of one
@@ -145,16 +148,17 @@ typedef struct {
     int32_t group_width;       /* largest group */
     int32_t n_tiles;           /* work-list entries per step */
     int32_t variant;           /* step kernel variant (0 direct, 1-3 z-marching, 4 rolled, 5-7 LDS row
-                                  tiles, 8 two steps per launch) */
+                                  tiles, 8 two steps per launch, 9 all steps of a run in one launch) */
     int32_t block;             /* threads per workgroup */
-    int32_t tz;                /* z planes per tile */
+    int32_t tz;                /* z planes per tile; variant 9: workgroups per team at most */
     int32_t grid;              /* workgroups per step launch */
     int32_t nt;                /* 1: nontemporal output stores */
     int32_t flip;              /* 1: odd steps run in reversed tile and march order */
     int32_t launches_per_step; /* 1 for batched plans, n_groups for TL_PLAIN (launches of one
                                   step each; see steps_per_launch) */
     int32_t steps_per_launch;  /* 2 when each launch runs two steps (variant 8; an odd step count
-                                  ends with one launch of a one-step tiling), else 1 */
+                                  ends with one launch of a one-step tiling), else 1 (also for
+                                  variant 9, whose one launch per run is timed per step) */
     int32_t tile_width;        /* RHS per step group in the launches: group_width, or 1 when the
                                   tuned tiling gives every RHS its own tiles */
     int64_t rhs_sites;         /* sum over RHS of Lx*Ly*Lz */
@@ -175,7 +179,10 @@ int tl_version(void);
  *                                    group (0 or absent: the plan's groups; 1: every RHS on its
  *                                    own tiles).  Variant 8 (two steps per launch) may name the
  *                                    one-step tiling an odd step count ends with after a ';'
- *                                    (default "0,256,4,0,0,0")
+ *                                    (default "0,256,4,0,0,0"); variant 9 (all steps in one
+ *                                    launch; fields: threads per workgroup at most, workgroups
+ *                                    per team at most, workgroups, 0, 0, RHS per thread) the
+ *                                    one that runs of fewer than four steps use
  *   TL_LOG=1                         print autotuning candidates to stderr
  *   TL_FAULT=alloc|launch            make internal allocations or launches fail
  *                                    (read at tl_create; exercises error paths)
@@ -205,7 +212,9 @@ int tl_destroy(tl_ctx *ctx);
  * new stream from then on.  TL_ERR_HIP if the runtime refuses the event.
  */
 int tl_set_stream(tl_ctx *ctx, void *stream);
-/* Block until the context's stream is idle; reports asynchronous device errors. */
+/* Block until the context's stream is idle; reports asynchronous device errors, among them
+ * (TL_ERR_HIP) a whole-run launch whose wait for another workgroup ran out after several
+ * seconds: that run's output is not valid. */
 int tl_sync(tl_ctx *ctx);
 /* Message of the last failing call on ctx (ctx = NULL: last failure of tl_create on this thread). */
 const char *tl_last_error(const tl_ctx *ctx);

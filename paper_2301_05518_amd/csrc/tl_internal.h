@@ -66,6 +66,8 @@ struct StepConfig {
                  //    the first step also on one chain row beyond each side, its result
                  //    kept in LDS for the second (an odd step count ends with one launch
                  //    of a one-step tiling)
+                 // 9: all steps of a run in one launch (tl_run.h); block: threads per workgroup at
+                 //    most, tz: workgroups per team at most
   int block;     // threads per workgroup (xy sites per tile; variants 5-7: an upper bound)
   int tz;        // z planes per tile
   int grid;      // workgroups; <= 0 means one workgroup per tile
@@ -132,6 +134,92 @@ TL_STEP_DECL(f32)
 TL_STEP_DECL(f16s)
 TL_STEP_DECL(bf16)
 #undef TL_STEP_DECL
+
+// ---- whole-run kernel (variant 9, tl_run.h): all n steps of a plan in one launch
+
+// One cell (the sites that hops connect: one parity of every even direction) of one RHS group,
+// and how it is cut into tiles.
+struct RunUnit {
+  const char* W;          // packed link slot of the slice
+  int64_t w_mu_stride;    // bytes between direction blocks
+  int64_t psi_off;        // byte offset of the group's first RHS in the resident buffers
+  int64_t rhs_stride;     // bytes between consecutive RHS of the group
+  int32_t Lx, Ly, Lz;
+  int32_t Vp;             // plane length (padded sites)
+  int32_t nr;             // RHS in the group
+  int32_t p[3];           // first site of the cell per direction
+  int32_t c[3];           // cell extents
+  int32_t b[3];           // tile extents
+  int32_t t[3];           // tiles per direction
+};
+
+// A team's meeting point, and the launch's control block (device memory, zeroed once; each
+// launch leaves it ready for the next and advances the epoch).
+struct alignas(128) RunTeam {
+  uint64_t mail;          // (sequence number << 32) | unit
+  uint32_t enrolled, size, arrived;
+};
+constexpr int kMaxRunTeams = 1024;
+struct RunCtl {
+  alignas(128) uint32_t epoch;
+  alignas(128) uint32_t next_unit;
+  alignas(128) uint32_t finished;
+  RunTeam team[kMaxRunTeams];
+};
+
+struct RunArgs {
+  const RunUnit* units;
+  RunCtl* ctl;
+  char* scratch;          // exchange words: [team][2][RHS word][team_size * np] of 16 bytes
+  uint32_t* fail;         // host-visible: set when a wait ran out
+  const char* in;
+  char* out;
+  int32_t n_units, n_steps, n_teams, team_size;
+  int32_t np;             // threads per RHS subset (a tile's sites, rounded up to waves)
+  int32_t subs;           // RHS subsets of a group on separate threads
+  int32_t hop;            // hop distance
+  bool w12;
+};
+
+struct RunConfig {
+  int grid;               // workgroups, a multiple of 8
+  int width;              // RHS per thread
+  int halo;               // halo entries fetched per thread and step: 0, 1 or 2
+  int64_t lds;            // dynamic LDS bytes
+};
+
+// 16-byte exchange words of a colour vector per precision.
+constexpr int kRunWords[4] = {4, 2, 2, 1};
+constexpr int kRunMsgBytes = 16;   // LDS in front of the vectors
+
+// LDS bytes of a site's `width` vectors, and the dynamic LDS bytes of a whole-run launch: per RHS
+// subset two generations of np vectors and the halo;
+// FP64 adds the backward two-links of np sites.
+constexpr int run_record(int prec, int width) { return prec == F64 ? 48 * width : width == 4 ? 104 : 24 * width; }
+inline int64_t run_lds(int prec, int width, int subs, int np, int halo) {
+  return kRunMsgBytes + (int64_t)subs * (2 + halo) * np * run_record(prec, width) +
+         (prec == F64 ? 27 * 16 * (int64_t)np : 0);
+}
+
+#define TL_RUN_DECL(name)                                                                                \
+  hipError_t launch_run_##name(const RunConfig& cfg, const RunArgs& args, double alpha, double beta,     \
+                               hipStream_t stream);                                                      \
+  hipError_t run_attributes_##name();
+TL_RUN_DECL(f64)
+TL_RUN_DECL(f32)
+TL_RUN_DECL(f16s)
+TL_RUN_DECL(bf16)
+#undef TL_RUN_DECL
+
+inline hipError_t launch_run(int prec, const RunConfig& cfg, const RunArgs& args, double alpha, double beta,
+                             hipStream_t stream) {
+  switch (prec) {
+    case F64: return launch_run_f64(cfg, args, alpha, beta, stream);
+    case F32: return launch_run_f32(cfg, args, alpha, beta, stream);
+    case F16S: return launch_run_f16s(cfg, args, alpha, beta, stream);
+    default: return launch_run_bf16(cfg, args, alpha, beta, stream);
+  }
+}
 
 // W slots slot_first .. slot_first+n-1 from slices t_first .. t_first+n-1, in format `code`:
 // two-links W_mu(x) = U_mu(x) U_mu(x+mu^), or the links U_mu(x) themselves when is_one(code).

@@ -324,7 +324,8 @@ __global__ void compare_kernel(const uint4* __restrict__ a, const uint4* __restr
 
 hipError_t init_kernel_attributes() {
   hipError_t e = hipSuccess;
-  for (hipError_t r : {step_attributes_f64(), step_attributes_f32(), step_attributes_f16s(), step_attributes_bf16()})
+  for (hipError_t r : {step_attributes_f64(), step_attributes_f32(), step_attributes_f16s(), step_attributes_bf16(),
+                       run_attributes_f64(), run_attributes_f32(), run_attributes_f16s(), run_attributes_bf16()})
     if (r != hipSuccess) e = r;
   return e;
 }

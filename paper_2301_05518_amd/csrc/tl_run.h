@@ -1,0 +1,717 @@
+// Whole-run kernel: all n smearing steps of a plan in one launch (step variant 9).
+//
+// What bounds the step kernels on lattices up to 64^3 is not the arithmetic: below 48^3 a
+// launch costs about 5 us whatever it does, and on 64^3 every step streams the two-links
+// again although they never change.  Here a workgroup keeps its share of the two-links in
+// registers (forward and backward ones of one site per thread: 108 VGPRs in FP32) for the
+// whole run, its colour vectors in LDS, and exchanges only the outer sites of its tile.
+//
+// Hops of two sites decouple a slice into cells: the sites of one parity in every direction
+// of even extent (a direction of odd extent is one chain 0, 2, 4, ... around the ring; a
+// one-link field is one cell).  Inside a cell the hops are nearest-neighbour and periodic.
+// A unit of work is one cell of one RHS group; it is cut into tiles, one per workgroup, and a
+// team of workgroups runs the unit's n steps together.
+//
+// Exchange.  A thread whose site has a neighbour in another tile publishes its vector in the
+// team's scratch memory as 16-byte words of 12 payload bytes and a 4-byte tag that names the
+// step; a reader loads a word until it holds the tag it waits for.  So there is no flag, no
+// fence and no barrier between workgroups: one store-to-load latency per step (about 1.3 us,
+// against 4 us with separate flags, and 40 us with the agent-scope fences that plain loads
+// would need).  The stores and loads are device-scope (they bypass the per-CU and are kept
+// coherent across the per-XCD caches), and a lane's aligned 16-byte word is one request, so
+// a tag never arrives without its payload.  Two scratch planes alternate; a tile overwrites
+// step s - 1 with step s + 1 only after it has read step s of all its neighbour tiles, each
+// of which published step s after it had read step s - 1 completely.  Tags never repeat
+// within a launch, and every launch begins at a new epoch (kept in device memory, advanced
+// by the launch's last workgroup), so a graph replay never takes an old word for a new one.
+//
+// Progress.  Nothing assumes that the whole grid is resident.  A team is made of workgroups
+// that run: each enrols when it starts, the first one closes the team when all expected
+// members have come or after about 200 us, later ones leave.  A team that is smaller than
+// the unit's tile count runs the same exchange with several tiles per workgroup and the
+// two-links read from memory each step (run_slow).  Teams take units from a common counter.
+// Every wait is bounded; one that runs out sets *fail and the kernel ends.
+#pragma once
+
+#include <type_traits>
+
+#include "tl_step.h"
+
+namespace tl {
+
+namespace {
+
+// Raw storage words of a colour vector and their exchange form.
+template <int P> struct Exch;
+template <> struct Exch<F64> {
+  static constexpr int ND = 12, NW = 4;   // dwords, tagged words
+  static __device__ __forceinline__ void load(const char* b, int64_t Vp, int64_t i, uint32_t (&d)[ND]) {
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+      const v4u w = ldg<v4u>(b + (c * Vp + i) * 16);
+      d[4 * c] = w.x; d[4 * c + 1] = w.y; d[4 * c + 2] = w.z; d[4 * c + 3] = w.w;
+    }
+  }
+  static __device__ __forceinline__ void decode(const uint32_t (&d)[ND], double (&v)[6]) {
+#pragma unroll
+    for (int c = 0; c < 6; c++) v[c] = __hiloint2double((int)d[2 * c + 1], (int)d[2 * c]);
+  }
+  static __device__ __forceinline__ void encode(const double (&v)[6], uint32_t (&d)[ND]) {
+#pragma unroll
+    for (int c = 0; c < 6; c++) {
+      d[2 * c] = (uint32_t)__double2loint(v[c]);
+      d[2 * c + 1] = (uint32_t)__double2hiint(v[c]);
+    }
+  }
+};
+template <> struct Exch<F32> {
+  static constexpr int ND = 6, NW = 2;
+  static __device__ __forceinline__ void load(const char* b, int64_t Vp, int64_t i, uint32_t (&d)[ND]) {
+    const v4u a = ldg<v4u>(b + i * 16);
+    const v2u c = ldg<v2u>(b + 16 * Vp + i * 8);
+    d[0] = a.x; d[1] = a.y; d[2] = a.z; d[3] = a.w; d[4] = c.x; d[5] = c.y;
+  }
+  static __device__ __forceinline__ void decode(const uint32_t (&d)[ND], float (&v)[6]) {
+#pragma unroll
+    for (int c = 0; c < 6; c++) v[c] = __uint_as_float(d[c]);
+  }
+  static __device__ __forceinline__ void encode(const float (&v)[6], uint32_t (&d)[ND]) {
+#pragma unroll
+    for (int c = 0; c < 6; c++) d[c] = __float_as_uint(v[c]);
+  }
+};
+template <> struct Exch<F16S> {
+  static constexpr int ND = 4, NW = 2;
+  static __device__ __forceinline__ void load(const char* b, int64_t, int64_t i, uint32_t (&d)[ND]) {
+    const v4u a = ldg<v4u>(b + i * 16);
+    d[0] = a.x; d[1] = a.y; d[2] = a.z; d[3] = a.w;
+  }
+  static __device__ __forceinline__ void decode(const uint32_t (&d)[ND], float (&v)[6]) {
+    f16s_decode(v4u{d[0], d[1], d[2], d[3]}, v);
+  }
+  static __device__ __forceinline__ void encode(const float (&v)[6], uint32_t (&d)[ND]) {
+    const v4u a = f16s_encode(v);
+    d[0] = a.x; d[1] = a.y; d[2] = a.z; d[3] = a.w;
+  }
+};
+template <> struct Exch<BF16> {
+  static constexpr int ND = 3, NW = 1;
+  static __device__ __forceinline__ void load(const char* b, int64_t Vp, int64_t i, uint32_t (&d)[ND]) {
+    const v2u a = ldg<v2u>(b + i * 8);
+    d[0] = a.x; d[1] = a.y; d[2] = ldg<uint32_t>(b + 8 * Vp + i * 4);
+  }
+  static __device__ __forceinline__ void decode(const uint32_t (&d)[ND], float (&v)[6]) {
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+      v[2 * c] = bf16_to_f32(d[c] & 0xffffu);
+      v[2 * c + 1] = bf16_to_f32(d[c] >> 16);
+    }
+  }
+  static __device__ __forceinline__ void encode(const float (&v)[6], uint32_t (&d)[ND]) {
+#pragma unroll
+    for (int c = 0; c < 3; c++) d[c] = pack_bf16(v[2 * c], v[2 * c + 1]);
+  }
+};
+
+// The exchange words of one plane pair entry: word q of a vector holds dwords 3q .. 3q + 2.
+template <int P>
+__device__ __forceinline__ v4u exch_word(const uint32_t (&d)[Exch<P>::ND], int q, uint32_t tag) {
+  constexpr int ND = Exch<P>::ND;
+  return v4u{d[3 * q], 3 * q + 1 < ND ? d[3 * q + 1] : 0u, 3 * q + 2 < ND ? d[3 * q + 2] : 0u, tag};
+}
+template <int P>
+__device__ __forceinline__ void exch_dwords(const v4u (&w)[Exch<P>::NW], uint32_t (&d)[Exch<P>::ND]) {
+#pragma unroll
+  for (int k = 0; k < Exch<P>::ND; k++) d[k] = w[k / 3][k % 3];
+}
+
+// A site's R vectors in LDS: one record, so that every access of a neighbour is one address
+// plus an immediate offset (run_record bytes; the odd multiple of 8 for four RHS keeps the
+// 16 lanes of an 8-byte access phase on different banks).
+template <int R>
+__device__ __forceinline__ void rec_put(unsigned char* p, int r, const float (&v)[6]) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) *reinterpret_cast<v2f*>(p + 24 * r + 8 * c) = v2f{v[2 * c], v[2 * c + 1]};
+}
+template <int R>
+__device__ __forceinline__ void rec_get(const unsigned char* p, int r, float (&v)[6]) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    const v2f w = *reinterpret_cast<const v2f*>(p + 24 * r + 8 * c);
+    v[2 * c] = w.x;
+    v[2 * c + 1] = w.y;
+  }
+}
+template <int R>
+__device__ __forceinline__ void rec_put(unsigned char* p, int r, const double (&v)[6]) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) *reinterpret_cast<v2d*>(p + 48 * r + 16 * c) = v2d{v[2 * c], v[2 * c + 1]};
+}
+template <int R>
+__device__ __forceinline__ void rec_get(const unsigned char* p, int r, double (&v)[6]) {
+#pragma unroll
+  for (int c = 0; c < 3; c++) {
+    const v2d w = *reinterpret_cast<const v2d*>(p + 48 * r + 16 * c);
+    v[2 * c] = w.x;
+    v[2 * c + 1] = w.y;
+  }
+}
+
+constexpr int kDeviceScope = 16;   // sc1 in a buffer instruction's cache policy
+
+// The word's offset goes into the instruction's vector offset alone.  With part of it in a
+// scalar register the compiler (which then sees no hazard) reuses the data registers in the
+// next instruction, and under load a store has been seen to write the next word's payload
+// under this word's tag, four lanes at a time.
+__device__ __forceinline__ void exch_store(v4u w, __amdgpu_buffer_rsrc_t rs, int off) {
+  __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, kDeviceScope);
+}
+
+__device__ __forceinline__ uint32_t ctl_load(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void ctl_store(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t ctl_add(uint32_t* p, uint32_t v) {
+  return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void run_failed(uint32_t* fail) {
+  __hip_atomic_store(fail, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// Barrier of a workgroup over LDS only: global loads and stores in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// A value every lane of a wave holds, as a scalar: the compiler cannot see that what comes from
+// LDS or from threadIdx / np is the same in all lanes.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+constexpr uint32_t kTeamClosed = 0x40000000u;
+constexpr int kEnrolSpins = 4000;        // about 200 us of the leader's wait for its team
+constexpr int kSpinLimit = 1 << 23;      // polls of any other wait (seconds)
+
+// Where a workgroup stands: its team and its place there; `expect` workgroups of the grid
+// belong to the team.  Workgroups are dispatched round-robin over the XCDs, so a team of up
+// to a grid's workgroups per XCD sits on one XCD (its exchange then stays in one L2), a
+// larger one on neighbouring XCDs; only speed depends on that.
+struct RunPlace {
+  int team, rank, expect;
+};
+__device__ __forceinline__ RunPlace run_place(int team_size) {
+  const int per = (int)gridDim.x / kXcds, k = (int)blockIdx.x % kXcds, j = (int)blockIdx.x / kXcds;
+  if (j >= per) return {0, 1 << 20, 0};
+  if (per >= team_size) {
+    const int tpx = per / team_size, q = j / team_size;
+    return {q < tpx ? q * kXcds + k : 0, q < tpx ? j - q * team_size : 1 << 20, team_size};
+  }
+  int xpt = 2;
+  while (xpt < kXcds && xpt * per < team_size) xpt *= 2;
+  const int r = (k % xpt) * per + j;
+  const int expect = min(team_size, xpt * per);
+  return {k / xpt, r < expect ? r : 1 << 20, expect};
+}
+
+// A tile of a unit: origin and extent in cell coordinates.
+struct RunTile {
+  int o[3], e[3];
+};
+__device__ __forceinline__ RunTile run_tile(const RunUnit& g, int tile) {
+  const int ix = tile % g.t[0], iyz = tile / g.t[0], iy = iyz % g.t[1], iz = iyz / g.t[1];
+  RunTile r;
+  r.o[0] = ix * g.b[0];
+  r.o[1] = iy * g.b[1];
+  r.o[2] = iz * g.b[2];
+#pragma unroll
+  for (int d = 0; d < 3; d++) r.e[d] = min(g.b[d], g.c[d] - r.o[d]);
+  return r;
+}
+
+// Lattice site index of a cell coordinate.
+__device__ __forceinline__ int run_site(const RunUnit& g, int hop, int cx, int cy, int cz) {
+  int x = g.p[0] + hop * cx, y = g.p[1] + hop * cy, z = g.p[2] + hop * cz;
+  x = x >= g.Lx ? x - g.Lx : x;
+  y = y >= g.Ly ? y - g.Ly : y;
+  z = z >= g.Lz ? z - g.Lz : z;
+  return (z * g.Ly + y) * g.Lx + x;
+}
+
+// Scratch slot of a cell coordinate: np slots per tile, the tile's sites in x, y, z order.
+__device__ __forceinline__ int run_slot(const RunUnit& g, int np, int cx, int cy, int cz) {
+  const int ix = cx / g.b[0], iy = cy / g.b[1], iz = cz / g.b[2];
+  const int lx = cx - ix * g.b[0], ly = cy - iy * g.b[1], lz = cz - iz * g.b[2];
+  return ((iz * g.t[1] + iy) * g.t[0] + ix) * np + (lz * g.b[1] + ly) * g.b[0] + lx;
+}
+
+__device__ __forceinline__ int ring(int c, int n) { return c < 0 ? c + n : c >= n ? c - n : c; }
+
+template <int P, typename T>
+__device__ __forceinline__ void run_load_w(bool w12, const char* b, int64_t Vp, int64_t i, T (&m)[18]) {
+  if (w12) Fmt<P | W12>::load_w(b, Vp, i, m);
+  else Fmt<P>::load_w(b, Vp, i, m);
+}
+
+// One unit by a team smaller than its tile count: member `me` of `size` takes the tiles me,
+// me + size, ... of every step in turn; vectors live in the scratch words, two-links are read
+// each step.  Every tile of a step is published before any of the next, so no wait is circular.
+template <int P, int R>
+__device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, uint32_t tag0, int par0, int team,
+                         typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
+  using real = typename Fmt<P>::real;
+  using X = Exch<P>;
+  const int sub = uniform((int)threadIdx.x / a.np), i = (int)threadIdx.x - sub * a.np;
+  const int n_tiles = g.t[0] * g.t[1] * g.t[2], bvol = g.b[0] * g.b[1] * g.b[2];
+  const int slots = a.team_size * a.np;
+  const int64_t plane = (int64_t)a.subs * R * X::NW * slots * 16;
+  char* const base = a.scratch + team * 2 * plane;
+  const __amdgpu_buffer_rsrc_t res[2] = {__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)plane, 0x00027000),
+                                         __builtin_amdgcn_make_buffer_rsrc(base + plane, 0, (int)plane, 0x00027000)};
+  bool dead = false;
+  for (int s = -1; s < a.n_steps; s++) {   // s = -1 publishes the input
+    for (int tile = me; tile < n_tiles; tile += size) {
+      const RunTile tl = run_tile(g, tile);
+      const int lx = i % g.b[0], lyz = i / g.b[0], ly = lyz % g.b[1], lz = lyz / g.b[1];
+      if (i >= bvol || lx >= tl.e[0] || ly >= tl.e[1] || lz >= tl.e[2]) continue;
+      const int cx = tl.o[0] + lx, cy = tl.o[1] + ly, cz = tl.o[2] + lz;
+      const int64_t site = run_site(g, a.hop, cx, cy, cz);
+      const int own = tile * a.np + i;
+      const uint32_t tag = tag0 + (uint32_t)s;
+      for (int r = 0; r < R; r++) {
+        const int rr = sub * R + r;
+        const int64_t off = g.psi_off + (int64_t)min(rr, g.nr - 1) * g.rhs_stride;
+        const int q0 = rr * X::NW;
+        uint32_t d[X::ND];
+        if (s < 0) {
+          X::load(a.in + off, g.Vp, site, d);
+        } else {
+          auto fetch = [&](int slot, real(&v)[6]) {
+            const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res[1] : res[0];
+            v4u w[X::NW];
+            int spin = 0;
+            while (true) {
+              bool ok = true;
+#pragma unroll
+              for (int q = 0; q < X::NW; q++)
+                w[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, slot * 16, (q0 + q) * slots * 16, kDeviceScope);
+              asm volatile("" ::: "memory");
+#pragma unroll
+              for (int q = 0; q < X::NW; q++) ok = ok && w[q].w == tag;
+              if (ok || dead) break;
+              if (++spin > kSpinLimit) {
+                run_failed(a.fail);
+                dead = true;
+              }
+            }
+            uint32_t e[X::ND];
+            exch_dwords<P>(w, e);
+            X::decode(e, v);
+          };
+          real acc[6], v[6], m[18];
+#pragma unroll
+          for (int c = 0; c < 6; c++) acc[c] = (real)0;
+          for (int mu = 0; mu < 3; mu++) {
+            const int dx = mu == 0, dy = mu == 1, dz = mu == 2;
+            const int fx = ring(cx + dx, g.c[0]), fy = ring(cy + dy, g.c[1]), fz = ring(cz + dz, g.c[2]);
+            const int bx = ring(cx - dx, g.c[0]), by = ring(cy - dy, g.c[1]), bz = ring(cz - dz, g.c[2]);
+            const char* W = g.W + mu * g.w_mu_stride;
+            run_load_w<P>(a.w12, W, g.Vp, site, m);
+            fetch(run_slot(g, a.np, fx, fy, fz), v);
+            mv_acc(m, v, acc);
+            run_load_w<P>(a.w12, W, g.Vp, run_site(g, a.hop, bx, by, bz), m);
+            fetch(run_slot(g, a.np, bx, by, bz), v);
+            mdv_acc(m, v, acc);
+          }
+          fetch(own, v);
+          real o[6];
+#pragma unroll
+          for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[c], alpha * v[c]);
+          if (s + 1 == a.n_steps) {
+            if (rr < g.nr) Fmt<P>::template store_v<real, false>(a.out + off, g.Vp, site, o);
+            continue;
+          }
+          X::encode(o, d);
+        }
+        const __amdgpu_buffer_rsrc_t ws = ((par0 + s + 1) & 1) ? res[1] : res[0];
+#pragma unroll
+        for (int q = 0; q < X::NW; q++)
+          exch_store(exch_word<P>(d, q, tag + 1), ws, (own + (q0 + q) * slots) * 16);
+      }
+    }
+  }
+}
+
+// One unit, one tile per workgroup: `tile` of this workgroup.  np threads per RHS subset,
+// one site each; K: halo entries each thread fetches per step (0: the unit is one tile).
+// FP32 arithmetic keeps both two-links of every direction in registers; FP64 keeps the
+// backward ones in LDS (27 planes of np 16-byte words, shared by the RHS subsets).
+template <int P, int R, int K>
+__device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
+                                               int team, unsigned char* lds, typename Fmt<P>::real alpha,
+                                               typename Fmt<P>::real beta) {
+  using real = typename Fmt<P>::real;
+  using X = Exch<P>;
+  constexpr bool kLdsW = P == F64;
+  constexpr int REC = run_record(P, R);
+  const int np = a.np;
+  const int sub = uniform((int)threadIdx.x / np), i = (int)threadIdx.x - sub * np;
+  const RunTile tl = run_tile(g, tile);
+  const int bx = g.b[0], by = g.b[1], bz = g.b[2];
+  const bool in = i < bx * by * bz;
+  const int i0 = in ? i : 0;
+  const int lx = i0 % bx, lyz = i0 / bx, ly = lyz % by, lz = lyz / by;
+  const bool active = in && lx < tl.e[0] && ly < tl.e[1] && lz < tl.e[2];
+  // threads without a site compute the tile's first one and publish and store nothing
+  const int ax = active ? lx : 0, ay = active ? ly : 0, az = active ? lz : 0;
+  const int cx = tl.o[0] + ax, cy = tl.o[1] + ay, cz = tl.o[2] + az;
+  const int site = run_site(g, a.hop, cx, cy, cz);
+  const int64_t Vp = g.Vp;
+  // LDS entries per RHS: own vectors of even and odd steps, then the halo
+  const int ne = (2 + K) * np;
+  unsigned char* const wl = lds + (int64_t)a.subs * ne * REC;
+  unsigned char* const vl = lds + (int64_t)sub * ne * REC;
+  // halo faces x-, x+, y-, y+, z-, z+ (those of directions cut into several tiles)
+  const int f[3] = {g.t[0] > 1 ? by * bz : 0, g.t[1] > 1 ? bx * bz : 0, g.t[2] > 1 ? bx * by : 0};
+  const int hb[3] = {2 * np, 2 * np + 2 * f[0], 2 * np + 2 * (f[0] + f[1])};
+  int nb[6];   // LDS offset of the neighbour x+, x-, y+, y-, z+, z- (own entries: those of even steps)
+  {
+    const int l[3] = {ax, ay, az}, st[3] = {1, bx, bx * by};
+    const int face[3] = {az * by + ay, az * bx + ax, ay * bx + ax};
+    const int me = (az * by + ay) * bx + ax;
+#pragma unroll
+    for (int d = 0; d < 3; d++) {
+      nb[2 * d] = l[d] + 1 < tl.e[d] ? me + st[d] : f[d] ? hb[d] + f[d] + face[d] : me - l[d] * st[d];
+      nb[2 * d + 1] = l[d] > 0 ? me - st[d] : f[d] ? hb[d] + face[d] : me + (tl.e[d] - 1) * st[d];
+    }
+  }
+  bool pub = false;
+#pragma unroll
+  for (int d = 0; d < 6; d++) {
+    pub = pub || nb[d] >= 2 * np;
+    nb[d] *= REC;
+  }
+  pub = pub && active;
+  int hsrc[K > 0 ? K : 1];
+#pragma unroll
+  for (int k = 0; k < K; k++) {
+    int h = k * np + i, d = -1, q = 0;
+    bool plus = false;
+#pragma unroll
+    for (int e = 0; e < 3; e++) {
+      const int u = h - (hb[e] - 2 * np);
+      if (f[e] > 0 && u >= 0 && u < 2 * f[e]) {
+        d = e;
+        plus = u >= f[e];
+        q = plus ? u - f[e] : u;
+      }
+    }
+    hsrc[k] = -1;
+    if (d >= 0) {
+      const int w = d == 0 ? by : bx;              // fast extent of the face
+      const int u = q % w, v = q / w;
+      int c[3] = {d == 0 ? 0 : u, d == 0 ? u : d == 1 ? 0 : v, d == 2 ? 0 : v};
+      const bool ok = (d == 0 || c[0] < tl.e[0]) && (d == 1 || c[1] < tl.e[1]) && (d == 2 || c[2] < tl.e[2]);
+#pragma unroll
+      for (int e = 0; e < 3; e++)
+        c[e] = e == d ? ring(plus ? tl.o[e] + tl.e[e] : tl.o[e] - 1, g.c[e]) : min(tl.o[e] + c[e], g.c[e] - 1);
+      if (ok) hsrc[k] = run_slot(g, np, c[0], c[1], c[2]) * 16;
+    }
+  }
+  real wf[3][18], wb[kLdsW ? 1 : 3][18];
+#pragma unroll
+  for (int mu = 0; mu < 3; mu++) {
+    const char* W = g.W + mu * g.w_mu_stride;
+    const int bs = run_site(g, a.hop, ring(cx - (mu == 0), g.c[0]), ring(cy - (mu == 1), g.c[1]), ring(cz - (mu == 2), g.c[2]));
+    run_load_w<P>(a.w12, W, Vp, site, wf[mu]);
+    if constexpr (kLdsW) {
+      if (sub == 0) {
+        real m[18];
+        run_load_w<P>(a.w12, W, Vp, bs, m);
+#pragma unroll
+        for (int c = 0; c < 9; c++) reinterpret_cast<v2d*>(wl)[(9 * mu + c) * np + i] = v2d{m[2 * c], m[2 * c + 1]};
+      }
+    } else {
+      run_load_w<P>(a.w12, W, Vp, bs, wb[mu]);
+    }
+  }
+  uint32_t dw[R][X::ND];
+#pragma unroll
+  for (int r = 0; r < R; r++)
+    X::load(a.in + g.psi_off + (int64_t)min(sub * R + r, g.nr - 1) * g.rhs_stride, Vp, site, dw[r]);
+  const int slots = a.team_size * np;
+  const int64_t plane = (int64_t)a.subs * R * X::NW * slots * 16;
+  char* const base = a.scratch + team * 2 * plane;
+  const __amdgpu_buffer_rsrc_t res0 = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)plane, 0x00027000);
+  const __amdgpu_buffer_rsrc_t res1 = __builtin_amdgcn_make_buffer_rsrc(base + plane, 0, (int)plane, 0x00027000);
+  const int q0 = sub * R * X::NW;
+  const int mine = (tile * np + i) * 16;
+  const bool x_in = f[0] == 0;   // x neighbours are inside the tile
+  bool dead = false;
+  // everything loaded so far has arrived: inside the loop only halo words are awaited, so that
+  // no wait there has to let the step's own stores finish first
+  __builtin_amdgcn_s_waitcnt(0);
+  lds_barrier();   // backward two-links, and the previous unit's last reads of LDS
+  for (int s = 0; s < a.n_steps; s++) {
+    const uint32_t tag = tag0 + (uint32_t)s;
+    const int own = (s & 1) ? np * REC : 0;
+    const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
+    if constexpr (K > 0) {
+      if (pub) {
+#pragma unroll
+        for (int r = 0; r < R; r++)
+#pragma unroll
+          for (int q = 0; q < X::NW; q++)
+            exch_store(exch_word<P>(dw[r], q, tag), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+      }
+    }
+    real v[R][6];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      X::decode(dw[r], v[r]);
+      rec_put<R>(vl + own + i * REC, r, v[r]);
+    }
+    v4u hw[K > 0 ? K : 1][R][X::NW];
+    auto halo_load = [&](int k) {
+#pragma unroll
+      for (int r = 0; r < R; r++)
+#pragma unroll
+        for (int q = 0; q < X::NW; q++)
+          hw[k][r][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, hsrc[k], (q0 + r * X::NW + q) * slots * 16, kDeviceScope);
+    };
+    if constexpr (K > 0) {
+#pragma unroll
+      for (int k = 0; k < K; k++)
+        if (hsrc[k] >= 0) halo_load(k);
+    }
+    lds_barrier();
+    real acc[R][6];
+#pragma unroll
+    for (int r = 0; r < R; r++)
+#pragma unroll
+      for (int c = 0; c < 6; c++) acc[r][c] = (real)0;
+    auto hops = [&](auto mu_c) {
+      constexpr int mu = decltype(mu_c)::value;
+      const unsigned char* const ef = vl + nb[2 * mu] + (nb[2 * mu] < np * REC ? own : 0);
+      const unsigned char* const eb = vl + nb[2 * mu + 1] + (nb[2 * mu + 1] < np * REC ? own : 0);
+#pragma unroll
+      for (int r = 0; r < R; r++) {
+        real u[6];
+        rec_get<R>(ef, r, u);
+        mv_acc(wf[mu], u, acc[r]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (kLdsW) {
+        real m[18];
+#pragma unroll
+        for (int c = 0; c < 9; c++) {
+          const v2d w = reinterpret_cast<const v2d*>(wl)[(9 * mu + c) * np + i];
+          m[2 * c] = w.x;
+          m[2 * c + 1] = w.y;
+        }
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+          real u[6];
+          rec_get<R>(eb, r, u);
+          mdv_acc(m, u, acc[r]);
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+          real u[6];
+          rec_get<R>(eb, r, u);
+          mdv_acc(wb[mu], u, acc[r]);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    if (K == 0 || x_in) hops(std::integral_constant<int, 0>{});
+    if constexpr (K > 0) {
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        if (hsrc[k] >= 0) {
+          int spin = 0;
+          while (true) {
+            bool ok = true;
+#pragma unroll
+            for (int r = 0; r < R; r++)
+#pragma unroll
+              for (int q = 0; q < X::NW; q++) ok = ok && hw[k][r][q].w == tag;
+            if (ok || dead) break;
+            if (++spin > kSpinLimit) {
+              run_failed(a.fail);
+              dead = true;
+            }
+            asm volatile("" ::: "memory");
+            halo_load(k);
+          }
+#pragma unroll
+          for (int r = 0; r < R; r++) {
+            uint32_t d[X::ND];
+            exch_dwords<P>(hw[k][r], d);
+            real u[6];
+            X::decode(d, u);
+            rec_put<R>(vl + (2 * np + k * np + i) * REC, r, u);
+          }
+        }
+      }
+      lds_barrier();
+      if (!x_in) hops(std::integral_constant<int, 0>{});
+    }
+    hops(std::integral_constant<int, 1>{});
+    hops(std::integral_constant<int, 2>{});
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      real o[6], w[6];
+      rec_get<R>(vl + own + i * REC, r, w);
+#pragma unroll
+      for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[r][c], alpha * w[c]);
+      if (s + 1 < a.n_steps) {
+        X::encode(o, dw[r]);
+      } else if (active && sub * R + r < g.nr) {
+        Fmt<P>::template store_v<real, false>(a.out + g.psi_off + (int64_t)(sub * R + r) * g.rhs_stride, Vp, site, o);
+      }
+    }
+  }
+}
+
+template <int P, int R, int K>
+__global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  uint32_t* const sh = reinterpret_cast<uint32_t*>(lds_raw);   // 16 bytes of messages, then the vectors
+  unsigned char* const lds = lds_raw + 16;
+  const RunPlace pl = run_place(a.team_size);
+  RunTeam* const tm = a.ctl->team + pl.team;
+  if (threadIdx.x == 0) {
+    uint32_t e = 1u << 20, size = 0;
+    if (pl.rank < pl.expect) {
+      e = ctl_add(&tm->enrolled, 1u);
+      if (e == 0) {
+        for (int k = 0; k < kEnrolSpins && ctl_load(&tm->enrolled) < (uint32_t)pl.expect; k++) __builtin_amdgcn_s_sleep(2);
+        size = __hip_atomic_fetch_or(&tm->enrolled, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ctl_store(&tm->size, size);
+      } else if (e < kTeamClosed) {
+        for (int k = 0; k < kSpinLimit && (size = ctl_load(&tm->size)) == 0; k++) __builtin_amdgcn_s_sleep(1);
+        if (size == 0) run_failed(a.fail);
+      }
+    }
+    sh[0] = size;
+    sh[1] = size == (uint32_t)pl.expect ? (uint32_t)pl.rank : e;   // a full team's members take their places' tiles
+    sh[2] = ctl_load(&a.ctl->epoch);
+    sh[3] = e;
+  }
+  __syncthreads();
+  const int size = uniform((int)sh[0]), me = uniform((int)sh[1]);
+  const uint32_t epoch = (uint32_t)uniform((int)sh[2]);
+  const bool leader = uniform((int)sh[3]) == 0;
+  __syncthreads();
+  if (me < size) {
+    for (uint32_t seq = 0;; seq++) {
+      if (threadIdx.x == 0) {
+        uint32_t u = (uint32_t)a.n_units;
+        if (leader) {
+          int k = 0;
+          while (ctl_load(&tm->arrived) < seq * (uint32_t)(size - 1) && ++k < kSpinLimit) {}
+          if (k >= kSpinLimit) run_failed(a.fail);
+          else u = min(ctl_add(&a.ctl->next_unit, 1u), (uint32_t)a.n_units);
+          __hip_atomic_store(&tm->mail, (uint64_t)(seq + 1) << 32 | u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+          if (seq > 0) ctl_add(&tm->arrived, 1u);
+          uint64_t m = 0;
+          int k = 0;
+          while (((m = __hip_atomic_load(&tm->mail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != seq + 1 &&
+                 ++k < kSpinLimit) {}
+          if (k >= kSpinLimit) run_failed(a.fail);
+          else u = (uint32_t)m;
+        }
+        sh[0] = u;
+      }
+      __syncthreads();
+      const int u = uniform((int)sh[0]);
+      __syncthreads();
+      if (u >= a.n_units) break;
+      const RunUnit& g = a.units[u];
+      const int n_tiles = g.t[0] * g.t[1] * g.t[2];
+      const uint32_t pubs = seq * (uint32_t)a.n_steps;
+      if (size >= n_tiles) {
+        if (me < n_tiles) run_tile_steps<P, R, K>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, lds, alpha, beta);
+      } else if constexpr (K > 0) {
+        run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
+      }
+      __syncthreads();   // every thread has read what it waited for before the team may move on
+    }
+  }
+  // the launch's last workgroup leaves the control block ready for the next launch
+  if (threadIdx.x == 0) {
+    __builtin_amdgcn_s_waitcnt(0);
+    sh[0] = ctl_add(&a.ctl->finished, 1u) == gridDim.x - 1;
+  }
+  __syncthreads();
+  if (!sh[0]) return;
+  for (int k = (int)threadIdx.x; k < a.n_teams; k += (int)blockDim.x) {
+    RunTeam* const t = a.ctl->team + k;
+    ctl_store(&t->enrolled, 0);
+    ctl_store(&t->size, 0);
+    ctl_store(&t->arrived, 0);
+    __hip_atomic_store(&t->mail, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (threadIdx.x == 0) {
+    ctl_store(&a.ctl->next_unit, 0);
+    ctl_store(&a.ctl->finished, 0);
+    ctl_store(&a.ctl->epoch, epoch + (uint32_t)a.n_units * (uint32_t)a.n_steps + 1u);
+  }
+}
+
+template <int P, int R>
+hipError_t launch_run_k(const RunConfig& c, const RunArgs& a, double alpha, double beta, hipStream_t s) {
+  using real = typename Fmt<P>::real;
+  const real al = (real)alpha, be = (real)beta;
+  const int threads = a.np * a.subs;
+  if (c.halo == 0) smear_run<P, R, 0><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
+  else if (c.halo == 1) smear_run<P, R, 1><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
+  else smear_run<P, R, 2><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
+  return hipGetLastError();
+}
+
+template <int P>
+hipError_t launch_run_p(const RunConfig& c, const RunArgs& a, double alpha, double beta, hipStream_t s) {
+  if (a.np < 64 || a.np % 64 || a.np * a.subs > 512 || c.halo < 0 || c.halo > 2 || c.lds > kMaxLds || c.grid % kXcds)
+    return hipErrorInvalidValue;
+  if constexpr (P == F64) {
+    return c.width == 1 ? launch_run_k<P, 1>(c, a, alpha, beta, s) : hipErrorInvalidValue;
+  } else {
+    switch (c.width) {
+      case 1: return launch_run_k<P, 1>(c, a, alpha, beta, s);
+      case 2: return launch_run_k<P, 2>(c, a, alpha, beta, s);
+      case 3: return launch_run_k<P, 3>(c, a, alpha, beta, s);
+      case 4: return launch_run_k<P, 4>(c, a, alpha, beta, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
+}
+
+template <int P, int R>
+hipError_t run_allow_lds() {
+  for (const void* f : {reinterpret_cast<const void*>(&smear_run<P, R, 0>), reinterpret_cast<const void*>(&smear_run<P, R, 1>),
+                        reinterpret_cast<const void*>(&smear_run<P, R, 2>)}) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+template <int P>
+hipError_t run_attributes() {
+  hipError_t e = run_allow_lds<P, 1>();
+  if constexpr (P != F64) {
+    for (hipError_t r : {run_allow_lds<P, 2>(), run_allow_lds<P, 3>(), run_allow_lds<P, 4>()})
+      if (r != hipSuccess) e = r;
+  }
+  return e;
+}
+
+}  // namespace
+
+}  // namespace tl

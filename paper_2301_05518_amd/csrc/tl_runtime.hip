@@ -31,8 +31,9 @@ static_assert(TL_F64 == tl::F64 && TL_F32 == tl::F32 && TL_F16S == tl::F16S && T
 static_assert((TL_W12 & 3) == 0 && (TL_ONELINK & 3) == 0 && TL_W12 != TL_ONELINK,
               "TL_W12 and TL_ONELINK are bits above the precision codes");
 
-// A tuned step tiling: cfg, and when cfg runs two steps per launch (variant 8) the one-step
-// tiling `single` that an odd step count ends with (single.variant < 0: none).
+// A tuned step tiling: cfg, and when cfg runs several steps per launch the one-step tiling
+// `single` that an odd step count ends with (variant 8) or that runs of fewer than kRunMinSteps
+// steps use (variant 9); single.variant < 0: none.
 struct Tuned {
   StepConfig cfg{0, 256, 4, 0, 0, 0, 0};
   StepConfig single{-1, 0, 0, 0, 0, 0, 0};
@@ -50,6 +51,7 @@ struct tl_ctx {
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
+  uint32_t* run_fail = nullptr;   // pinned host word a whole-run kernel sets when a wait between workgroups ran out
   double* noalloc = nullptr;  // this device's fixed partial-sum area of tl_reduce_noalloc
   std::string noalloc_err;    // why it is missing (lookup failed at tl_create)
   std::map<std::string, Tuned> tune;       // tuned step tilings by workload key
@@ -185,6 +187,14 @@ int ctx_scratch(tl_ctx* c, size_t bytes, char** out) {
   return TL_OK;
 }
 
+// A whole-run launch whose wait between workgroups ran out (it ended, its output is not valid)
+// is reported once, by the next call that looks.
+int run_check(tl_ctx* c) {
+  if (!c->run_fail || *static_cast<volatile uint32_t*>(c->run_fail) == 0) return TL_OK;
+  *c->run_fail = 0;
+  return fail(c, TL_ERR_HIP, "a whole-run smearing launch gave up waiting for another workgroup");
+}
+
 // Synchronous upload of a small host table onto the context stream.
 int upload(tl_ctx* c, void* dst, const void* src, size_t bytes) {
   if (bytes == 0) return TL_OK;
@@ -228,7 +238,7 @@ double max_step(bool one) { return one ? 1.0 / 6.0 : 2.0 / 3.0; }
 
 // A step configuration a cache entry or TL_TILE may name.
 bool valid_cfg(const StepConfig& g) {
-  return g.variant >= 0 && g.variant <= 8 && g.block >= 64 && g.block <= (g.variant >= 5 ? 512 : 256) &&
+  return g.variant >= 0 && g.variant <= 9 && g.block >= 64 && g.block <= (g.variant >= 5 ? 512 : 256) &&
          g.block % 64 == 0 && g.tz >= 1 && (g.nt == 0 || g.nt == 1) && (g.flip == 0 || g.flip == 1) &&
          g.width >= 0 && g.width <= 4;
 }
@@ -262,12 +272,12 @@ bool parse_tuned(const char* v, int n_min, Tuned* out) {
   if (n < n_min || !valid_cfg(t.cfg)) return false;
   if (*end == ';') {
     if (n < 6 || parse_cfg(end + 1, &t.single, &end) < 6 || *end != '\0' || !valid_cfg(t.single) ||
-        t.single.variant == 8)
+        t.single.variant >= 8)
       return false;
   } else if (*end != '\0') {
     return false;
   }
-  if (t.cfg.variant != 8) t.single = StepConfig{-1, 0, 0, 0, 0, 0, 0};
+  if (t.cfg.variant < 8) t.single = StepConfig{-1, 0, 0, 0, 0, 0, 0};
   else if (t.single.variant < 0) t.single = StepConfig{0, 256, 4, 0, 0, 0, 0};
   *out = t;
   return true;
@@ -316,7 +326,7 @@ void tune_file_save(const tl_ctx* c) {
     for (const auto& kv : c->tune) {
       const Tuned& g = kv.second;
       out << "  \"" << kv.first << "\": \"" << cfg_text(g.cfg)
-          << (g.cfg.variant == 8 ? ";" + cfg_text(g.single) : std::string()) << "\""
+          << (g.cfg.variant >= 8 ? ";" + cfg_text(g.single) : std::string()) << "\""
           << (++k < c->tune.size() ? ",\n" : "\n");
     }
     out << "}\n";
@@ -328,6 +338,14 @@ void tune_file_save(const tl_ctx* c) {
 }  // namespace
 
 // ====================================================================== plans
+
+// A whole-run launch (variant 9): its units and everything the launch needs but the pointers.
+struct RunShape {
+  tl::RunConfig cfg{};
+  std::vector<tl::RunUnit> units;
+  int np = 0, subs = 1, team_size = 1, n_teams = 0, n_tiles = 0;
+  size_t scratch = 0;
+};
 
 struct tl_plan {
   tl_ctx* ctx = nullptr;
@@ -376,10 +394,16 @@ struct tl_plan {
     std::vector<StepGroup> host;
     int n_tiles = 0;
     int64_t lds = 0;                    // dynamic LDS bytes of its launches (variants 5-8)
+    RunShape run;                       // variant 9: its units and launch (host, n_tiles unused but for info)
   };
   Tiling tile;                          // the step tiling
   Tiling single;                        // when tile runs two steps per launch: the one-step
                                         // tiling of the last step of an odd count
+  // whole-run launches: units table, control block, exchange scratch (allocated when first used)
+  tl::RunUnit* run_units = nullptr;
+  tl::RunCtl* run_ctl = nullptr;
+  char* run_scratch = nullptr;
+  size_t run_scratch_bytes = 0;
   bool ready = false;                   // tuning done (or not requested) and tables uploaded
 
   hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -458,8 +482,128 @@ int64_t plan_lds(const tl_plan* p, const StepConfig& cfg, const std::vector<Step
   return mx <= 160 * 1024 ? mx : -1;
 }
 
+// Runs of fewer steps use one launch per step: a whole-run launch reads every two-link twice
+// (once as the forward and once as the backward one of a site) before its first step.
+constexpr int kRunMinSteps = 4;
+
+// Cut a cell of extents c into at most `team` tiles of at most `sites` sites: the fewest waves
+// per tile (its arithmetic time), then the fewest sites to exchange, whole x rows where that
+// costs nothing (their x hops need no exchange).  Returns the tile count, 0 if none fits.
+int cut_cell(const int32_t c[3], int sites, int team, int32_t b[3], int32_t t[3], int* halo) {
+  int best = 0;
+  int64_t best_cost = 0;
+  for (int tx = 1; tx <= c[0] && tx <= team; tx++) {
+    const int bx = (c[0] + tx - 1) / tx;
+    if ((c[0] + bx - 1) / bx != tx) continue;
+    for (int ty = 1; ty <= c[1] && tx * ty <= team; ty++) {
+      const int by = (c[1] + ty - 1) / ty;
+      if ((c[1] + by - 1) / by != ty) continue;
+      for (int tz = 1; tz <= c[2] && tx * ty * tz <= team; tz++) {
+        const int bz = (c[2] + tz - 1) / tz;
+        if ((c[2] + bz - 1) / bz != tz || (int64_t)bx * by * bz > sites) continue;
+        const int h = 2 * ((tx > 1 ? by * bz : 0) + (ty > 1 ? bx * bz : 0) + (tz > 1 ? bx * by : 0));
+        const int64_t cost = ((int64_t)((bx * by * bz + 63) / 64) << 32) + ((int64_t)h << 1) + (tx > 1 ? 1 : 0);
+        if (best && cost >= best_cost) continue;
+        best = tx * ty * tz;
+        best_cost = cost;
+        *halo = h;
+        b[0] = bx; b[1] = by; b[2] = bz;
+        t[0] = tx; t[1] = ty; t[2] = tz;
+      }
+    }
+  }
+  return best;
+}
+
+// The whole-run launch of a plan for configuration cfg (block: threads per workgroup at most, tz:
+// workgroups per team at most, grid: workgroups, width: RHS per thread; the RHS of a group that do
+// not share a thread get threads of their own).  Returns the reason it does not apply, or NULL.
+const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
+  const int prec = tl::vprec(p->prec), hop = tl::hop_of(p->prec);
+  RunShape r;
+  r.cfg.width = eff_width(p, cfg);
+  if (p->flags & TL_PLAIN) return "TL_PLAIN runs one step per launch";
+  if (prec == tl::F64 && r.cfg.width > 1) return "the whole-run kernel takes FP64 threads of one RHS only";
+  r.subs = (p->width + r.cfg.width - 1) / r.cfg.width;
+  const int sites = cfg.block / r.subs / 64 * 64;
+  if (sites < 64) return "too few threads per RHS";
+  int halo = 0;
+  for (const auto& gr : p->groups) {
+    const auto& jc = p->jobs[gr.job];
+    const tl_geom& g = jc.job.g;
+    tl::RunUnit u{};
+    u.W = static_cast<const char*>(jc.job.W) + (int64_t)gr.slot * 3 * jc.Vp * tl::kWBytes[p->prec];
+    u.w_mu_stride = jc.Vp * tl::kWBytes[p->prec];
+    u.psi_off = p->res[gr.first].off;
+    u.rhs_stride = gr.nr > 1 ? p->res[gr.first + 1].off - p->res[gr.first].off : 0;
+    u.Lx = g.L[0];
+    u.Ly = g.L[1];
+    u.Lz = g.L[2];
+    u.Vp = (int32_t)jc.Vp;
+    u.nr = gr.nr;
+    int chains[3];
+    for (int d = 0; d < 3; d++) {
+      chains[d] = (hop == 2 && !(g.L[d] & 1)) ? 2 : 1;
+      u.c[d] = g.L[d] / chains[d];
+    }
+    int h = 0;
+    int n = 0;
+    // groups of one lattice are neighbours in the list: reuse the cut
+    if (!r.units.empty() && r.units.back().Lx == u.Lx && r.units.back().Ly == u.Ly && r.units.back().Lz == u.Lz) {
+      std::copy(r.units.back().b, r.units.back().b + 3, u.b);
+      std::copy(r.units.back().t, r.units.back().t + 3, u.t);
+      n = u.t[0] * u.t[1] * u.t[2];
+    } else {
+      n = cut_cell(u.c, sites, cfg.tz, u.b, u.t, &h);
+      if (n == 0) return "a cell does not fit a team of workgroups";
+      r.np = std::max(r.np, (u.b[0] * u.b[1] * u.b[2] + 63) / 64 * 64);
+      halo = std::max(halo, h);
+      r.team_size = std::max(r.team_size, n);
+    }
+    for (int z = 0; z < chains[2]; z++)
+      for (int y = 0; y < chains[1]; y++)
+        for (int x = 0; x < chains[0]; x++) {
+          u.p[0] = x;
+          u.p[1] = y;
+          u.p[2] = z;
+          r.units.push_back(u);
+          r.n_tiles += n;
+        }
+  }
+  // the largest cells first: teams take units in this order
+  std::stable_sort(r.units.begin(), r.units.end(), [](const tl::RunUnit& a, const tl::RunUnit& b) {
+    return (int64_t)a.c[0] * a.c[1] * a.c[2] > (int64_t)b.c[0] * b.c[1] * b.c[2];
+  });
+  r.cfg.halo = (halo + r.np - 1) / r.np;
+  if (r.cfg.halo > 2) return "tiles with too many outer sites";
+  r.cfg.lds = tl::run_lds(prec, r.cfg.width, r.subs, r.np, r.cfg.halo);
+  if (r.cfg.lds > 160 * 1024) return "tiling needs more LDS than this device allows";
+  r.cfg.grid = std::max(8, (cfg.grid > 0 ? cfg.grid : std::max(p->ctx->n_cu, 1)) / 8 * 8);
+  const int per = r.cfg.grid / 8;
+  if (per >= r.team_size) {
+    r.n_teams = 8 * (per / r.team_size);
+  } else {
+    int xpt = 2;
+    while (xpt < 8 && xpt * per < r.team_size) xpt *= 2;
+    r.n_teams = 8 / xpt;
+  }
+  const int64_t plane = (int64_t)r.subs * r.cfg.width * tl::kRunWords[prec] * r.team_size * r.np * 16;
+  if (r.n_teams > tl::kMaxRunTeams || plane > INT32_MAX || r.units.size() > p->res.size() * 8 ||
+      (int64_t)r.units.size() * p->n_steps > INT32_MAX)
+    return "work list too long for the whole-run kernel";
+  r.scratch = r.cfg.halo ? (size_t)(r.n_teams * 2 * plane) : 0;
+  *out = std::move(r);
+  return nullptr;
+}
+
 // Whether cfg applies to this plan (its work list exists and fits in LDS); reason on failure.
 bool tiling_applies(const tl_plan* p, const StepConfig& cfg, const char** reason) {
+  if (cfg.variant == 9) {
+    RunShape r;
+    *reason = make_run(p, cfg, &r);
+    if (!*reason && !p->ctx->big_lds) *reason = "tiling needs more LDS than this device allows";
+    return !*reason;
+  }
   if (tl::is_one(p->prec) && cfg.variant != 0 && cfg.variant != 4 && cfg.variant != 7 && cfg.variant != 8) {
     *reason = "one-link smearing runs the step variants 0, 4, 7 and 8 only";
     return false;
@@ -485,10 +629,56 @@ bool tiling_applies(const tl_plan* p, const StepConfig& cfg, const char** reason
   return true;
 }
 
+// Build a whole-run tiling: units table, control block and exchange scratch.  The control block
+// and new scratch start as zeros; afterwards tags only grow, so scratch is never cleared again.
+int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
+  tl_ctx* c = p->ctx;
+  RunShape r;
+  const char* why = make_run(p, cfg, &r);
+  if (why) return fail(c, TL_ERR_UNSUPPORTED, "%s", why);
+  if (!c->run_fail) {
+    if (c->fault_alloc) return fail(c, TL_ERR_NOMEM, "host allocation failed (TL_FAULT=alloc)");
+    void* h = nullptr;
+    if (hipHostMalloc(&h, 64, hipHostMallocMapped) != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(c, TL_ERR_NOMEM, "hipHostMalloc failed");
+    }
+    c->run_fail = static_cast<uint32_t*>(h);
+    *c->run_fail = 0;
+  }
+  if (!p->run_ctl) {
+    const size_t ub = align256(p->res.size() * 8 * sizeof(tl::RunUnit));
+    void* m = nullptr;
+    TL_TRY(dev_alloc(c, &m, align256(sizeof(tl::RunCtl)) + ub));
+    p->run_ctl = static_cast<tl::RunCtl*>(m);
+    p->run_units = reinterpret_cast<tl::RunUnit*>(static_cast<char*>(m) + align256(sizeof(tl::RunCtl)));
+    HIP_TRY(c, hipMemsetAsync(m, 0, sizeof(tl::RunCtl), c->stream));
+  }
+  if (r.scratch > p->run_scratch_bytes) {
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
+    if (p->run_scratch) (void)hipFree(p->run_scratch);
+    p->run_scratch = nullptr;
+    p->run_scratch_bytes = 0;
+    void* m = nullptr;
+    TL_TRY(dev_alloc(c, &m, r.scratch));
+    p->run_scratch = static_cast<char*>(m);
+    p->run_scratch_bytes = r.scratch;
+    HIP_TRY(c, hipMemsetAsync(m, 0, r.scratch, c->stream));
+  }
+  TL_TRY(upload(c, p->run_units, r.units.data(), r.units.size() * sizeof(tl::RunUnit)));
+  t->cfg = cfg;
+  t->lds = r.cfg.lds;
+  t->n_tiles = r.n_tiles;
+  t->host.clear();
+  t->run = std::move(r);
+  return TL_OK;
+}
+
 // Build cfg's work list and upload it into tiling t's device table.
 int upload_tiling(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
   const char* why = nullptr;
   if (!tiling_applies(p, cfg, &why)) return fail(p->ctx, TL_ERR_UNSUPPORTED, "%s", why);
+  if (cfg.variant == 9) return upload_run(p, cfg, t);
   std::vector<StepGroup> gs;
   (void)make_groups(p, cfg, &gs);
   if (gs.size() > p->group_cap)   // the device table holds one entry per RHS at most
@@ -504,16 +694,35 @@ int upload_tiling(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
 
 // The plan's tilings from a tuned pair.
 int upload_tuned(tl_plan* p, const Tuned& tu) {
+  if (tu.cfg.variant == 9 && p->n_steps < kRunMinSteps) return upload_tiling(p, tu.single, &p->tile);
   TL_TRY(upload_tiling(p, tu.cfg, &p->tile));
   if (tu.cfg.variant == 8) TL_TRY(upload_tiling(p, tu.single, &p->single));
   return TL_OK;
 }
 
 // One launch of tiling t over every group (batched) or over one group (plain mode, g >= 0),
-// from buffer `in` to buffer `out`: one step, or two for variant 8.  k: index of the launch
+// from buffer `in` to buffer `out`: one step, two for variant 8, all for variant 9.  k: index of the launch
 // in its sequence (odd launches run reversed when the tiling flips).
 int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char* in, char* out, int g, int k) {
   tl_ctx* c = p->ctx;
+  if (t.cfg.variant == 9) {
+    tl::RunArgs a{};
+    a.units = p->run_units;
+    a.ctl = p->run_ctl;
+    a.scratch = p->run_scratch;
+    a.fail = c->run_fail;
+    a.in = in;
+    a.out = out;
+    a.n_units = (int32_t)t.run.units.size();
+    a.n_steps = p->n_steps;
+    a.n_teams = t.run.n_teams;
+    a.team_size = t.run.team_size;
+    a.np = t.run.np;
+    a.subs = t.run.subs;
+    a.hop = tl::hop_of(p->prec);
+    a.w12 = tl::is_w12(p->prec);
+    return launch(c, "smearing run", [&] { return tl::launch_run(tl::vprec(p->prec), t.run.cfg, a, p->alpha, p->beta, s); });
+  }
   int base = 0, n = t.n_tiles;
   if (g >= 0) {
     base = t.host[g].tile_begin;
@@ -533,7 +742,7 @@ int plan_step(tl_plan* p, hipStream_t s, int parity, int g, int k) {
 
 // Launches of one run of the n steps (each flips the resident buffer).
 int plan_launches(const tl_plan* p) {
-  return p->tile.cfg.variant == 8 ? p->n_steps / 2 + (p->n_steps & 1) : p->n_steps;
+  return p->tile.cfg.variant == 9 ? 1 : p->tile.cfg.variant == 8 ? p->n_steps / 2 + (p->n_steps & 1) : p->n_steps;
 }
 
 // Queue the n steps starting from buffer `parity` on stream s.
@@ -546,6 +755,8 @@ int plan_enqueue(tl_plan* p, hipStream_t s, int parity) {
         q ^= 1;
       }
     }
+  } else if (p->tile.cfg.variant == 9) {
+    TL_TRY(plan_step(p, s, parity, -1, 0));
   } else if (p->tile.cfg.variant == 8) {
     int q = parity;
     for (int k = 0; k < p->n_steps / 2; k++) {
@@ -588,7 +799,7 @@ int plan_autotune(tl_plan* p) {
     // version of the library, or edited) is dropped and the plan tuned again
     const char* why = nullptr;
     const Tuned& tu = hit->second;
-    if (tiling_applies(p, tu.cfg, &why) && (tu.cfg.variant != 8 || tiling_applies(p, tu.single, &why))) {
+    if (tiling_applies(p, tu.cfg, &why) && (tu.cfg.variant < 8 || tiling_applies(p, tu.single, &why))) {
       c->stats.tune_hits++;
       return upload_tuned(p, tu);
     }
@@ -630,6 +841,16 @@ int plan_autotune(tl_plan* p) {
         for (int grid : {0, cu})
           for (int nt : {0, 1})
             for (int flip : {0, 1}) cands2.push_back({8, block, tz, grid, nt, flip, 0});
+  // whole-run launches: every team size that changes the cut, RHS of a group sharing threads or not
+  std::vector<StepConfig> cands9;
+  if (!(p->flags & (TL_PLAIN | TL_ONE_STEP)) && p->n_steps >= kRunMinSteps && c->big_lds)
+    for (int wd : widths)
+      for (int block : {512, 256})
+        for (int team : {1, 2, 4, 8, 16, 32, 64, 128, 256}) {
+          StepConfig g{9, block, team, 0, 0, 0, 0};
+          g.width = wd;
+          cands9.push_back(g);
+        }
   void* ref = nullptr;
   void* flag_mem = nullptr;
   TL_TRY(dev_alloc(c, &ref, p->buf_bytes));
@@ -641,7 +862,6 @@ int plan_autotune(tl_plan* p) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
     rc = fail(c, TL_ERR_HIP, "hipEventCreate failed");
-  const int reps = 10;
   // Batched plans time their one launch per step.  Plain plans (one launch per group) time one
   // group of each distinct lattice shape and weigh it by the number of groups of that shape,
   // so that the tiling suits every shape of the batch, not only the first.
@@ -663,11 +883,11 @@ int plan_autotune(tl_plan* p) {
     }
   }
   // time reps launches of p->tile (after two untimed) for each timed group, then compare the
-  // output with ref (have_ref false: keep it as ref instead); ms: per step
-  auto trial = [&](bool have_ref, float* ms, bool* same) -> int {
+  // output with ref (have_ref false: keep it as ref instead); ms: per launch
+  auto trial = [&](bool have_ref, float* ms, bool* same, int warm = 2, int reps = 10) -> int {
     *ms = 0.0f;
     for (const auto& tw : timed) {
-      for (int w = 0; w < 2; w++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, w));
+      for (int w = 0; w < warm; w++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, w));
       (void)hipEventRecord(e0, c->stream);
       for (int k = 0; k < reps; k++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, k));
       (void)hipEventRecord(e1, c->stream);
@@ -743,6 +963,38 @@ int plan_autotune(tl_plan* p) {
     if (rc == TL_OK && best2 < best) {
       tu.cfg = best2_cfg;
       tu.single = best_cfg;
+      best = best2;
+    }
+  }
+  if (rc == TL_OK && !cands9.empty()) {
+    // whole-run launches (all n steps each), against n launches of the one-step winner
+    rc = upload_tiling(p, best_cfg, &p->single);
+    char* pair[2] = {p->buf[p->cur ^ 1], static_cast<char*>(ref)};
+    for (int k = 0; k < p->n_steps && rc == TL_OK; k++)
+      rc = plan_launch(p, p->single, c->stream, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k);
+    if (rc == TL_OK && (p->n_steps & 1) &&
+        hipMemcpyAsync(ref, pair[0], p->buf_bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
+      rc = fail(c, TL_ERR_HIP, "autotune reference copy failed");
+    float best9 = 1e30f;
+    StepConfig best9_cfg{};
+    for (size_t ci = 0; ci < cands9.size() && rc == TL_OK; ci++) {
+      const char* why = nullptr;
+      if (!tiling_applies(p, cands9[ci], &why)) continue;
+      rc = upload_tiling(p, cands9[ci], &p->tile);
+      if (rc != TL_OK) break;
+      float ms = 0.0f;
+      bool same = true;
+      rc = trial(true, &ms, &same, 1, 3);
+      if (rc != TL_OK) break;
+      log(p->tile.cfg, ms / p->n_steps, same);
+      if (same && ms / p->n_steps < best9) {
+        best9 = ms / p->n_steps;
+        best9_cfg = p->tile.cfg;
+      }
+    }
+    if (rc == TL_OK && best9 < best) {
+      tu.cfg = best9_cfg;
+      tu.single = best_cfg;
     }
   }
   (void)hipStreamSynchronize(c->stream);
@@ -810,6 +1062,8 @@ void plan_free(tl_plan* p) {
     for (auto& b : p->buf)
       if (b) (void)hipFree(b);
     if (p->tables) (void)hipFree(p->tables);
+    if (p->run_ctl) (void)hipFree(p->run_ctl);
+    if (p->run_scratch) (void)hipFree(p->run_scratch);
   }
   delete p;
 }
@@ -903,6 +1157,7 @@ int tl_destroy(tl_ctx* c) {
       DeviceGuard dg(c->device);   // teardown goes on even if the switch fails
       (void)hipStreamSynchronize(c->stream);
       if (c->scratch) (void)hipFree(c->scratch);
+      if (c->run_fail) (void)hipHostFree(c->run_fail);
     }
     delete c;
     return TL_OK;
@@ -941,7 +1196,7 @@ int tl_sync(tl_ctx* c) {
     TL_ON_DEVICE(c);
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipGetLastError());
-    return TL_OK;
+    return run_check(c);
   } catch (...) {
     return host_failure(c);
   }
@@ -1265,8 +1520,9 @@ int tl_plan_run(tl_plan* p) {
     tl_ctx* c = p->ctx;
     if (p->n_steps == 0) return TL_OK;
     TL_ON_DEVICE(c);
+    TL_TRY(run_check(c));
     TL_TRY(plan_prepare(p));
-    if (p->flags & TL_GRAPH) {
+    if ((p->flags & TL_GRAPH) && p->tile.cfg.variant != 9) {   // one launch needs no graph
       TL_TRY(plan_capture(p, p->cur));
       if (c->fault_launch) return fail(c, TL_ERR_HIP, "graph launch failed (TL_FAULT=launch)");
       HIP_TRY(c, hipGraphLaunch(p->graph[p->cur], c->stream));
@@ -1391,12 +1647,13 @@ int tl_plan_get_info(const tl_plan* p, tl_plan_info* info) {
   try {
     if (!p || !info) return TL_ERR_ARG;
     *info = p->info;
+    info->resident_bytes += (int64_t)p->run_scratch_bytes + (p->run_ctl ? (int64_t)sizeof(tl::RunCtl) : 0);
     const tl_plan::Tiling& t = p->tile;
     info->n_tiles = t.n_tiles;
     info->variant = t.cfg.variant;
     info->block = t.cfg.block;
     info->tz = t.cfg.tz;
-    info->grid = t.cfg.grid > 0 ? std::min(t.cfg.grid, t.n_tiles) : t.n_tiles;
+    info->grid = t.cfg.variant == 9 ? t.run.cfg.grid : t.cfg.grid > 0 ? std::min(t.cfg.grid, t.n_tiles) : t.n_tiles;
     info->nt = t.cfg.nt;
     info->flip = t.cfg.flip;
     info->steps_per_launch = t.cfg.variant == 8 ? 2 : 1;
