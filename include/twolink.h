@@ -160,7 +160,8 @@ typedef struct {
                                   ends with one launch of a one-step tiling), else 1 (also for
                                   variant 9, whose one launch per run is timed per step) */
     int32_t tile_width;        /* RHS per step group in the launches: group_width, or 1 when the
-                                  tuned tiling gives every RHS its own tiles */
+                                  tuned tiling gives every RHS its own tiles (variant 9: 1, every
+                                  RHS is advanced by itself) */
     int64_t rhs_sites;         /* sum over RHS of Lx*Ly*Lz */
     double bytes_per_step;     /* algorithmic bytes of one step: W once per group + psi in and out */
     double flops_per_step;     /* 444 per RHS-site-update */
@@ -181,7 +182,8 @@ int tl_version(void);
  *                                    one-step tiling an odd step count ends with after a ';'
  *                                    (default "0,256,4,0,0,0"); variant 9 (all steps in one
  *                                    launch; fields: threads per workgroup at most, workgroups
- *                                    per team at most, workgroups, 0, 0, RHS per thread) the
+ *                                    per team at most, workgroups, 0, 1 if the RHS of a group
+ *                                    get threads of their own) the
  *                                    one that runs of fewer than four steps use
  *   TL_LOG=1                         print autotuning candidates to stderr
  *   TL_FAULT=alloc|launch            make internal allocations or launches fail

@@ -196,8 +196,9 @@ constexpr int kRunMsgBytes = 16;   // LDS in front of the vectors
 // subset two generations of np vectors and the halo;
 // FP64 adds the backward two-links of np sites.
 constexpr int run_record(int prec, int width) { return prec == F64 ? 48 * width : width == 4 ? 104 : 24 * width; }
+constexpr int run_entries(int width, int halo) { return 2 + (width == 1 ? 2 : 1) * halo; }
 inline int64_t run_lds(int prec, int width, int subs, int np, int halo) {
-  return kRunMsgBytes + (int64_t)subs * (2 + halo) * np * run_record(prec, width) +
+  return kRunMsgBytes + (int64_t)subs * run_entries(width, halo) * np * run_record(prec, width) +
          (prec == F64 ? 27 * 16 * (int64_t)np : 0);
 }
 

@@ -369,8 +369,8 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   const int cx = tl.o[0] + ax, cy = tl.o[1] + ay, cz = tl.o[2] + az;
   const int site = run_site(g, a.hop, cx, cy, cz);
   const int64_t Vp = g.Vp;
-  // LDS entries per RHS: own vectors of even and odd steps, then the halo
-  const int ne = (2 + K) * np;
+  // LDS entries: own vectors of even and odd steps, then the halo
+  const int ne = run_entries(R, K) * np;
   unsigned char* const wl = lds + (int64_t)a.subs * ne * REC;
   unsigned char* const vl = lds + (int64_t)sub * ne * REC;
   // halo faces x-, x+, y-, y+, z-, z+ (those of directions cut into several tiles)
@@ -437,10 +437,6 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
       run_load_w<P>(a.w12, W, Vp, bs, wb[mu]);
     }
   }
-  uint32_t dw[R][X::ND];
-#pragma unroll
-  for (int r = 0; r < R; r++)
-    X::load(a.in + g.psi_off + (int64_t)min(sub * R + r, g.nr - 1) * g.rhs_stride, Vp, site, dw[r]);
   const int slots = a.team_size * np;
   const int64_t plane = (int64_t)a.subs * R * X::NW * slots * 16;
   char* const base = a.scratch + team * 2 * plane;
@@ -448,128 +444,114 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   const __amdgpu_buffer_rsrc_t res1 = __builtin_amdgcn_make_buffer_rsrc(base + plane, 0, (int)plane, 0x00027000);
   const int q0 = sub * R * X::NW;
   const int mine = (tile * np + i) * 16;
-  const bool x_in = f[0] == 0;   // x neighbours are inside the tile
   bool dead = false;
+  auto publish = [&](int r, int s, const uint32_t (&d)[X::ND]) {
+    if (!pub) return;
+    const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
+#pragma unroll
+    for (int q = 0; q < X::NW; q++)
+      exch_store(exch_word<P>(d, q, tag0 + (uint32_t)s), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+  };
+  v4u hw[K > 0 ? K : 1][X::NW];
+  auto halo_load = [&](int k, int r, int s) {
+    const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
+#pragma unroll
+    for (int q = 0; q < X::NW; q++)
+      hw[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, hsrc[k], (q0 + r * X::NW + q) * slots * 16, kDeviceScope);
+  };
+  auto halo_issue = [&](int r, int s) {
+#pragma unroll
+    for (int k = 0; k < K; k++)
+      if (hsrc[k] >= 0) halo_load(k, r, s);
+  };
+#pragma unroll
+  for (int r = 0; r < R; r++) {
+    uint32_t d[X::ND];
+    X::load(a.in + g.psi_off + (int64_t)min(sub * R + r, g.nr - 1) * g.rhs_stride, Vp, site, d);
+    if constexpr (K > 0) publish(r, 0, d);
+    real v[6];
+    X::decode(d, v);
+    rec_put<R>(vl + i * REC, r, v);
+  }
   // everything loaded so far has arrived: inside the loop only halo words are awaited, so that
   // no wait there has to let the step's own stores finish first
   __builtin_amdgcn_s_waitcnt(0);
-  lds_barrier();   // backward two-links, and the previous unit's last reads of LDS
+  if constexpr (K > 0) halo_issue(0, 0);
   for (int s = 0; s < a.n_steps; s++) {
     const uint32_t tag = tag0 + (uint32_t)s;
     const int own = (s & 1) ? np * REC : 0;
-    const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
-    if constexpr (K > 0) {
-      if (pub) {
-#pragma unroll
-        for (int r = 0; r < R; r++)
-#pragma unroll
-          for (int q = 0; q < X::NW; q++)
-            exch_store(exch_word<P>(dw[r], q, tag), rs, mine + (q0 + r * X::NW + q) * slots * 16);
-      }
-    }
-    real v[R][6];
+    const bool last = s + 1 == a.n_steps;
 #pragma unroll
     for (int r = 0; r < R; r++) {
-      X::decode(dw[r], v[r]);
-      rec_put<R>(vl + own + i * REC, r, v[r]);
-    }
-    v4u hw[K > 0 ? K : 1][R][X::NW];
-    auto halo_load = [&](int k) {
+      if constexpr (K > 0) {
 #pragma unroll
-      for (int r = 0; r < R; r++)
+        for (int k = 0; k < K; k++) {
+          if (hsrc[k] >= 0) {
+            int spin = 0;
+            while (true) {
+              bool ok = true;
 #pragma unroll
-        for (int q = 0; q < X::NW; q++)
-          hw[k][r][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, hsrc[k], (q0 + r * X::NW + q) * slots * 16, kDeviceScope);
-    };
-    if constexpr (K > 0) {
-#pragma unroll
-      for (int k = 0; k < K; k++)
-        if (hsrc[k] >= 0) halo_load(k);
-    }
-    lds_barrier();
-    real acc[R][6];
-#pragma unroll
-    for (int r = 0; r < R; r++)
-#pragma unroll
-      for (int c = 0; c < 6; c++) acc[r][c] = (real)0;
-    auto hops = [&](auto mu_c) {
-      constexpr int mu = decltype(mu_c)::value;
-      const unsigned char* const ef = vl + nb[2 * mu] + (nb[2 * mu] < np * REC ? own : 0);
-      const unsigned char* const eb = vl + nb[2 * mu + 1] + (nb[2 * mu + 1] < np * REC ? own : 0);
-#pragma unroll
-      for (int r = 0; r < R; r++) {
-        real u[6];
-        rec_get<R>(ef, r, u);
-        mv_acc(wf[mu], u, acc[r]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      if constexpr (kLdsW) {
-        real m[18];
-#pragma unroll
-        for (int c = 0; c < 9; c++) {
-          const v2d w = reinterpret_cast<const v2d*>(wl)[(9 * mu + c) * np + i];
-          m[2 * c] = w.x;
-          m[2 * c + 1] = w.y;
-        }
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-          real u[6];
-          rec_get<R>(eb, r, u);
-          mdv_acc(m, u, acc[r]);
-        }
-      } else {
-#pragma unroll
-        for (int r = 0; r < R; r++) {
-          real u[6];
-          rec_get<R>(eb, r, u);
-          mdv_acc(wb[mu], u, acc[r]);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    if (K == 0 || x_in) hops(std::integral_constant<int, 0>{});
-    if constexpr (K > 0) {
-#pragma unroll
-      for (int k = 0; k < K; k++) {
-        if (hsrc[k] >= 0) {
-          int spin = 0;
-          while (true) {
-            bool ok = true;
-#pragma unroll
-            for (int r = 0; r < R; r++)
-#pragma unroll
-              for (int q = 0; q < X::NW; q++) ok = ok && hw[k][r][q].w == tag;
-            if (ok || dead) break;
-            if (++spin > kSpinLimit) {
-              run_failed(a.fail);
-              dead = true;
+              for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
+              if (ok || dead) break;
+              if (++spin > kSpinLimit) {
+                run_failed(a.fail);
+                dead = true;
+              }
+              asm volatile("" ::: "memory");
+              halo_load(k, r, s);
             }
-            asm volatile("" ::: "memory");
-            halo_load(k);
-          }
-#pragma unroll
-          for (int r = 0; r < R; r++) {
             uint32_t d[X::ND];
-            exch_dwords<P>(hw[k][r], d);
+            exch_dwords<P>(hw[k], d);
             real u[6];
             X::decode(d, u);
-            rec_put<R>(vl + (2 * np + k * np + i) * REC, r, u);
+            rec_put<R>(vl + (2 * np + (R == 1 && (s & 1) ? K * np : 0) + k * np + i) * REC, r, u);
           }
         }
       }
       lds_barrier();
-      if (!x_in) hops(std::integral_constant<int, 0>{});
-    }
-    hops(std::integral_constant<int, 1>{});
-    hops(std::integral_constant<int, 2>{});
+      // the next phase's halo: its words were published R - 1 phases ago
+      if constexpr (K > 0 && R > 1) {
+        if (r + 1 < R) halo_issue(r + 1, s);
+        else if (!last) halo_issue(0, s + 1);
+      }
+      real acc[6];
 #pragma unroll
-    for (int r = 0; r < R; r++) {
+      for (int c = 0; c < 6; c++) acc[c] = (real)0;
+      const int hal = R == 1 && (s & 1) ? K * np * REC : 0;
+#pragma unroll
+      for (int mu = 0; mu < 3; mu++) {
+        const unsigned char* const ef = vl + nb[2 * mu] + (nb[2 * mu] < np * REC ? own : hal);
+        const unsigned char* const eb = vl + nb[2 * mu + 1] + (nb[2 * mu + 1] < np * REC ? own : hal);
+        real u[6];
+        rec_get<R>(ef, r, u);
+        mv_acc(wf[mu], u, acc);
+        rec_get<R>(eb, r, u);
+        if constexpr (kLdsW) {
+          real m[18];
+#pragma unroll
+          for (int c = 0; c < 9; c++) {
+            const v2d w = reinterpret_cast<const v2d*>(wl)[(9 * mu + c) * np + i];
+            m[2 * c] = w.x;
+            m[2 * c + 1] = w.y;
+          }
+          mdv_acc(m, u, acc);
+        } else {
+          mdv_acc(wb[mu], u, acc);
+        }
+      }
       real o[6], w[6];
       rec_get<R>(vl + own + i * REC, r, w);
 #pragma unroll
-      for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[r][c], alpha * w[c]);
-      if (s + 1 < a.n_steps) {
-        X::encode(o, dw[r]);
+      for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[c], alpha * w[c]);
+      if (!last) {
+        uint32_t d[X::ND];
+        X::encode(o, d);
+        if constexpr (K > 0) {
+          publish(r, s + 1, d);
+          if constexpr (R == 1) halo_issue(0, s + 1);
+        }
+        X::decode(d, w);
+        rec_put<R>(vl + (np * REC - own) + i * REC, r, w);
       } else if (active && sub * R + r < g.nr) {
         Fmt<P>::template store_v<real, false>(a.out + g.psi_off + (int64_t)(sub * R + r) * g.rhs_stride, Vp, site, o);
       }
@@ -679,16 +661,12 @@ template <int P>
 hipError_t launch_run_p(const RunConfig& c, const RunArgs& a, double alpha, double beta, hipStream_t s) {
   if (a.np < 64 || a.np % 64 || a.np * a.subs > 512 || c.halo < 0 || c.halo > 2 || c.lds > kMaxLds || c.grid % kXcds)
     return hipErrorInvalidValue;
-  if constexpr (P == F64) {
-    return c.width == 1 ? launch_run_k<P, 1>(c, a, alpha, beta, s) : hipErrorInvalidValue;
-  } else {
-    switch (c.width) {
-      case 1: return launch_run_k<P, 1>(c, a, alpha, beta, s);
-      case 2: return launch_run_k<P, 2>(c, a, alpha, beta, s);
-      case 3: return launch_run_k<P, 3>(c, a, alpha, beta, s);
-      case 4: return launch_run_k<P, 4>(c, a, alpha, beta, s);
-      default: return hipErrorInvalidValue;
-    }
+  switch (c.width) {
+    case 1: return launch_run_k<P, 1>(c, a, alpha, beta, s);
+    case 2: return launch_run_k<P, 2>(c, a, alpha, beta, s);
+    case 3: return launch_run_k<P, 3>(c, a, alpha, beta, s);
+    case 4: return launch_run_k<P, 4>(c, a, alpha, beta, s);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -704,11 +682,9 @@ hipError_t run_allow_lds() {
 
 template <int P>
 hipError_t run_attributes() {
-  hipError_t e = run_allow_lds<P, 1>();
-  if constexpr (P != F64) {
-    for (hipError_t r : {run_allow_lds<P, 2>(), run_allow_lds<P, 3>(), run_allow_lds<P, 4>()})
-      if (r != hipSuccess) e = r;
-  }
+  hipError_t e = hipSuccess;
+  for (hipError_t r : {run_allow_lds<P, 1>(), run_allow_lds<P, 2>(), run_allow_lds<P, 3>(), run_allow_lds<P, 4>()})
+    if (r != hipSuccess) e = r;
   return e;
 }
 

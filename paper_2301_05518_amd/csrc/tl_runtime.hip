@@ -516,15 +516,14 @@ int cut_cell(const int32_t c[3], int sites, int team, int32_t b[3], int32_t t[3]
 }
 
 // The whole-run launch of a plan for configuration cfg (block: threads per workgroup at most, tz:
-// workgroups per team at most, grid: workgroups, width: RHS per thread; the RHS of a group that do
-// not share a thread get threads of their own).  Returns the reason it does not apply, or NULL.
+// workgroups per team at most, grid: workgroups, flip: 0 the RHS of a group take turns in a thread,
+// 1 they get threads of their own).  Returns the reason it does not apply, or NULL.
 const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
   const int prec = tl::vprec(p->prec), hop = tl::hop_of(p->prec);
   RunShape r;
-  r.cfg.width = eff_width(p, cfg);
   if (p->flags & TL_PLAIN) return "TL_PLAIN runs one step per launch";
-  if (prec == tl::F64 && r.cfg.width > 1) return "the whole-run kernel takes FP64 threads of one RHS only";
-  r.subs = (p->width + r.cfg.width - 1) / r.cfg.width;
+  r.cfg.width = cfg.flip ? 1 : p->width;
+  r.subs = cfg.flip ? p->width : 1;
   const int sites = cfg.block / r.subs / 64 * 64;
   if (sites < 64) return "too few threads per RHS";
   int halo = 0;
@@ -667,6 +666,7 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
   }
   TL_TRY(upload(c, p->run_units, r.units.data(), r.units.size() * sizeof(tl::RunUnit)));
   t->cfg = cfg;
+  t->cfg.width = 1;   // every RHS is advanced by itself
   t->lds = r.cfg.lds;
   t->n_tiles = r.n_tiles;
   t->host.clear();
@@ -844,13 +844,10 @@ int plan_autotune(tl_plan* p) {
   // whole-run launches: every team size that changes the cut, RHS of a group sharing threads or not
   std::vector<StepConfig> cands9;
   if (!(p->flags & (TL_PLAIN | TL_ONE_STEP)) && p->n_steps >= kRunMinSteps && c->big_lds)
-    for (int wd : widths)
+    for (int split : {0, 1})
       for (int block : {512, 256})
-        for (int team : {1, 2, 4, 8, 16, 32, 64, 128, 256}) {
-          StepConfig g{9, block, team, 0, 0, 0, 0};
-          g.width = wd;
-          cands9.push_back(g);
-        }
+        for (int team : {1, 2, 4, 8, 16, 32, 64, 128, 256})
+          if (!split || p->width > 1) cands9.push_back({9, block, team, 0, 0, split, 0});
   void* ref = nullptr;
   void* flag_mem = nullptr;
   TL_TRY(dev_alloc(c, &ref, p->buf_bytes));

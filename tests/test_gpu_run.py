@@ -19,8 +19,8 @@ DIRECT = "0,64,1,0"
 CASES = [((8, 6, 10, 3), [0, 2, 0, 0]), ((4, 4, 2, 1), [0, 0]), ((7, 9, 5, 2), [1, 0]),
          ((32, 24, 20, 2), [0, 1, 1]), ((26, 11, 24, 1), [0, 0, 0, 0]), ((64, 8, 6, 1), [0, 0])]
 
-# "9,threads per workgroup,workgroups per team,grid,0,0[,RHS per thread]"
-TILES = ["9,512,32,0,0,0", "9,256,64,0,0,0,1", "9,512,8,64,0,0,1", "9,512,256,0,0,0", "9,512,64,8,0,0"]
+# "9,threads per workgroup,workgroups per team,grid,0,RHS of a group on threads of their own"
+TILES = ["9,512,32,0,0,0", "9,256,64,0,0,1", "9,512,8,64,0,1", "9,512,256,0,0,0", "9,512,64,8,0,0"]
 
 
 @pytest.fixture(scope="module")
@@ -82,8 +82,6 @@ def test_whole_run_bit_identical(ctx, orc, torch, prec, monkeypatch):
     _, (ref,) = smear(ctx, torch, lats, n, sigma, prec)
     ran = 0
     for tile in TILES:
-        if prec.startswith("f64") and tile.count(",") == 5:   # FP64 threads take one RHS
-            tile += ",1"
         for part in (lats, lats[:3], lats[3:4], lats[4:5]):   # the batch, and lattices on their own
             monkeypatch.setenv("TL_TILE", tile)
             log(f"whole run {prec}: tile {tile}, {[p[0] for p in part]}")
@@ -94,7 +92,7 @@ def test_whole_run_bit_identical(ctx, orc, torch, prec, monkeypatch):
                 log("  not applicable")
                 continue
             ran += 1
-            assert info["variant"] == 9 and info["steps_per_launch"] == 1
+            assert info["variant"] == 9 and info["steps_per_launch"] == 1 and info["tile_width"] == 1
             for (L, _, _, psi), a in zip(part, out):
                 b = next(r for q, r in zip(lats, ref) if q[0] == L)
                 assert np.array_equal(a, b), (tile, L)
@@ -117,7 +115,7 @@ def test_runs_of_one_plan(ctx, torch, n, monkeypatch):
     lats = lattices(30, [((24, 20, 18, 2), [0, 1, 0, 0])])
     monkeypatch.setenv("TL_TILE", DIRECT)
     _, (ref,) = smear(ctx, torch, lats, n, 0.3 * n, "f32")
-    for tile in ("9,512,16,0,0,0", "9,256,32,0,0,0,1"):
+    for tile in ("9,512,16,0,0,0", "9,256,32,0,0,1"):
         monkeypatch.setenv("TL_TILE", tile)
         for flags in (tl.TL_GRAPH, 0):
             log(f"repeated runs n={n}: tile {tile} flags {flags}")
@@ -182,8 +180,7 @@ def test_autotuned(ctx, torch, monkeypatch):
 def test_refusals(ctx, torch, monkeypatch):
     import paper_2301_05518_amd as tl
     lats = lattices(60, [((12, 8, 10, 1), [0, 0])])
-    for tile, prec, flags in (("9,512,32,0", "f32", tl.TL_PLAIN), ("9,512,32,0", "f64", 0),
-                              ("9,64,32,0,0,0,1", "f32", 0), ("9,64,1,0", "f32", 0)):
+    for tile, prec, flags in (("9,512,32,0", "f32", tl.TL_PLAIN), ("9,64,32,0,0,1", "f32", 0), ("9,64,1,0", "f32", 0)):
         monkeypatch.setenv("TL_TILE", tile)
         with pytest.raises(tl.TwolinkError, match="TL_ERR_UNSUPPORTED"):
             smear(ctx, torch, lats, 4, 2.0, prec, flags)
