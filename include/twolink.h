@@ -182,8 +182,9 @@ int tl_version(void);
  *                                    one-step tiling an odd step count ends with after a ';'
  *                                    (default "0,256,4,0,0,0"); variant 9 (all steps in one
  *                                    launch; fields: threads per workgroup at most, workgroups
- *                                    per team at most, workgroups, 0, 1 if the RHS of a group
- *                                    get threads of their own) the
+ *                                    per team at most, workgroups, 1 if two sets of threads
+ *                                    share a group's RHS, 1 if each RHS has threads of its
+ *                                    own) the
  *                                    one that runs of fewer than four steps use
  *   TL_LOG=1                         print autotuning candidates to stderr
  *   TL_FAULT=alloc|launch            make internal allocations or launches fail

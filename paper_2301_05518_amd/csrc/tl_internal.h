@@ -160,11 +160,13 @@ struct alignas(128) RunTeam {
   uint32_t enrolled, size, arrived;
 };
 constexpr int kMaxRunTeams = 1024;
+constexpr int kMaxRunGrid = 8192;
 struct RunCtl {
   alignas(128) uint32_t epoch;
   alignas(128) uint32_t next_unit;
   alignas(128) uint32_t finished;
   RunTeam team[kMaxRunTeams];
+  uint32_t xcc[kMaxRunGrid];   // [team][rank]: the XCD of each workgroup
 };
 
 struct RunArgs {
@@ -177,6 +179,7 @@ struct RunArgs {
   int32_t n_units, n_steps, n_teams, team_size;
   int32_t np;             // threads per RHS subset (a tile's sites, rounded up to waves)
   int32_t subs;           // RHS subsets of a group on separate threads
+  int32_t halo;           // LDS entries of a tile's halo (at least the sites it reads from other tiles)
   int32_t hop;            // hop distance
   bool w12;
 };
@@ -193,12 +196,12 @@ constexpr int kRunWords[4] = {4, 2, 2, 1};
 constexpr int kRunMsgBytes = 16;   // LDS in front of the vectors
 
 // LDS bytes of a site's `width` vectors, and the dynamic LDS bytes of a whole-run launch: per RHS
-// subset two generations of np vectors and the halo;
+// subset two generations of np vectors and the halo (two generations of it where a thread has one
+// RHS only);
 // FP64 adds the backward two-links of np sites.
 constexpr int run_record(int prec, int width) { return prec == F64 ? 48 * width : width == 4 ? 104 : 24 * width; }
-constexpr int run_entries(int width, int halo) { return 2 + (width == 1 ? 2 : 1) * halo; }
 inline int64_t run_lds(int prec, int width, int subs, int np, int halo) {
-  return kRunMsgBytes + (int64_t)subs * run_entries(width, halo) * np * run_record(prec, width) +
+  return kRunMsgBytes + (int64_t)subs * (2 * np + (width == 1 ? 2 : 1) * halo) * run_record(prec, width) +
          (prec == F64 ? 27 * 16 * (int64_t)np : 0);
 }
 

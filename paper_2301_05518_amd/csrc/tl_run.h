@@ -17,9 +17,11 @@
 // step; a reader loads a word until it holds the tag it waits for.  So there is no flag, no
 // fence and no barrier between workgroups: one store-to-load latency per step (about 1.3 us,
 // against 4 us with separate flags, and 40 us with the agent-scope fences that plain loads
-// would need).  The stores and loads are device-scope (they bypass the per-CU and are kept
-// coherent across the per-XCD caches), and a lane's aligned 16-byte word is one request, so
-// a tag never arrives without its payload.  Two scratch planes alternate; a tile overwrites
+// would need).  The loads are device-scope: they bypass the per-CU caches and are coherent.
+// The stores are device-scope where a reader sits on another XCD, plain otherwise (they then
+// stay in the L2 both share; device-scope stores write through to memory, which alone took a
+// 48^3 FP32 step from 4.1 to 5.6 us).  A lane's aligned 16-byte word is one request, so a
+// tag never arrives without its payload.  Two scratch planes alternate; a tile overwrites
 // step s - 1 with step s + 1 only after it has read step s of all its neighbour tiles, each
 // of which published step s after it had read step s - 1 completely.  Tags never repeat
 // within a launch, and every launch begins at a new epoch (kept in device memory, advanced
@@ -163,9 +165,12 @@ constexpr int kDeviceScope = 16;   // sc1 in a buffer instruction's cache policy
 // scalar register the compiler (which then sees no hazard) reuses the data registers in the
 // next instruction, and under load a store has been seen to write the next word's payload
 // under this word's tag, four lanes at a time.
+template <int Scope>
 __device__ __forceinline__ void exch_store(v4u w, __amdgpu_buffer_rsrc_t rs, int off) {
-  __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, kDeviceScope);
+  __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, Scope);
 }
+// The XCD this wave runs on (hardware register XCC_ID).
+__device__ __forceinline__ uint32_t xcd_id() { return __builtin_amdgcn_s_getreg(20 | (3 << 11)); }
 
 __device__ __forceinline__ uint32_t ctl_load(const uint32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -338,7 +343,7 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
         const __amdgpu_buffer_rsrc_t ws = ((par0 + s + 1) & 1) ? res[1] : res[0];
 #pragma unroll
         for (int q = 0; q < X::NW; q++)
-          exch_store(exch_word<P>(d, q, tag + 1), ws, (own + (q0 + q) * slots) * 16);
+          exch_store<kDeviceScope>(exch_word<P>(d, q, tag + 1), ws, (own + (q0 + q) * slots) * 16);
       }
     }
   }
@@ -350,7 +355,7 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
 // backward ones in LDS (27 planes of np 16-byte words, shared by the RHS subsets).
 template <int P, int R, int K>
 __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
-                                               int team, unsigned char* lds, typename Fmt<P>::real alpha,
+                                               int team, bool full, unsigned char* lds, typename Fmt<P>::real alpha,
                                                typename Fmt<P>::real beta) {
   using real = typename Fmt<P>::real;
   using X = Exch<P>;
@@ -370,7 +375,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   const int site = run_site(g, a.hop, cx, cy, cz);
   const int64_t Vp = g.Vp;
   // LDS entries: own vectors of even and odd steps, then the halo
-  const int ne = run_entries(R, K) * np;
+  const int ne = 2 * np + (R == 1 ? 2 : 1) * a.halo;
   unsigned char* const wl = lds + (int64_t)a.subs * ne * REC;
   unsigned char* const vl = lds + (int64_t)sub * ne * REC;
   // halo faces x-, x+, y-, y+, z-, z+ (those of directions cut into several tiles)
@@ -387,13 +392,28 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
       nb[2 * d + 1] = l[d] > 0 ? me - st[d] : f[d] ? hb[d] + face[d] : me + (tl.e[d] - 1) * st[d];
     }
   }
-  bool pub = false;
+  // readers of this site's words: tiles on this XCD see a plain store through their common L2
+  // (loads of the words bypass the per-CU caches), tiles on another one need a device-scope store
+  bool pub = false, far = false;
+  if constexpr (K > 0) {
+    const uint32_t* const xcc = a.ctl->xcc + team * a.team_size;
+    const int it[3] = {tile % g.t[0], tile / g.t[0] % g.t[1], tile / g.t[0] / g.t[1]};
+    const int ts[3] = {1, g.t[0], g.t[0] * g.t[1]};
+    const uint32_t here = full ? ctl_load(xcc + tile) : 0;
 #pragma unroll
-  for (int d = 0; d < 6; d++) {
-    pub = pub || nb[d] >= 2 * np;
-    nb[d] *= REC;
+    for (int d = 0; d < 6; d++) {
+      const int e = d / 2, n = ring(it[e] + (d % 2 ? -1 : 1), g.t[e]);
+      const bool away = !full || (f[e] > 0 && ctl_load(xcc + tile + (n - it[e]) * ts[e]) != here);
+      if (nb[d] >= 2 * np) {
+        pub = true;
+        far = far || away;
+      }
+    }
+    pub = pub && active && !far;
+    far = far && active;
   }
-  pub = pub && active;
+#pragma unroll
+  for (int d = 0; d < 6; d++) nb[d] *= REC;
   int hsrc[K > 0 ? K : 1];
 #pragma unroll
   for (int k = 0; k < K; k++) {
@@ -446,11 +466,17 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   const int mine = (tile * np + i) * 16;
   bool dead = false;
   auto publish = [&](int r, int s, const uint32_t (&d)[X::ND]) {
-    if (!pub) return;
     const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
+    if (pub) {
 #pragma unroll
-    for (int q = 0; q < X::NW; q++)
-      exch_store(exch_word<P>(d, q, tag0 + (uint32_t)s), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+      for (int q = 0; q < X::NW; q++)
+        exch_store<0>(exch_word<P>(d, q, tag0 + (uint32_t)s), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+    }
+    if (far) {
+#pragma unroll
+      for (int q = 0; q < X::NW; q++)
+        exch_store<kDeviceScope>(exch_word<P>(d, q, tag0 + (uint32_t)s), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+    }
   };
   v4u hw[K > 0 ? K : 1][X::NW];
   auto halo_load = [&](int k, int r, int s) {
@@ -504,7 +530,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
             exch_dwords<P>(hw[k], d);
             real u[6];
             X::decode(d, u);
-            rec_put<R>(vl + (2 * np + (R == 1 && (s & 1) ? K * np : 0) + k * np + i) * REC, r, u);
+            rec_put<R>(vl + (2 * np + (R == 1 && (s & 1) ? a.halo : 0) + k * np + i) * REC, r, u);
           }
         }
       }
@@ -517,7 +543,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
       real acc[6];
 #pragma unroll
       for (int c = 0; c < 6; c++) acc[c] = (real)0;
-      const int hal = R == 1 && (s & 1) ? K * np * REC : 0;
+      const int hal = R == 1 && (s & 1) ? a.halo * REC : 0;
 #pragma unroll
       for (int mu = 0; mu < 3; mu++) {
         const unsigned char* const ef = vl + nb[2 * mu] + (nb[2 * mu] < np * REC ? own : hal);
@@ -569,6 +595,10 @@ __global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::rea
   if (threadIdx.x == 0) {
     uint32_t e = 1u << 20, size = 0;
     if (pl.rank < pl.expect) {
+      if constexpr (K > 0) {
+        ctl_store(a.ctl->xcc + pl.team * a.team_size + pl.rank, xcd_id());
+        __builtin_amdgcn_s_waitcnt(0);   // there before this workgroup counts as enrolled
+      }
       e = ctl_add(&tm->enrolled, 1u);
       if (e == 0) {
         for (int k = 0; k < kEnrolSpins && ctl_load(&tm->enrolled) < (uint32_t)pl.expect; k++) __builtin_amdgcn_s_sleep(2);
@@ -588,6 +618,7 @@ __global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::rea
   const int size = uniform((int)sh[0]), me = uniform((int)sh[1]);
   const uint32_t epoch = (uint32_t)uniform((int)sh[2]);
   const bool leader = uniform((int)sh[3]) == 0;
+  const bool full = size == pl.expect;
   __syncthreads();
   if (me < size) {
     for (uint32_t seq = 0;; seq++) {
@@ -618,7 +649,7 @@ __global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::rea
       const int n_tiles = g.t[0] * g.t[1] * g.t[2];
       const uint32_t pubs = seq * (uint32_t)a.n_steps;
       if (size >= n_tiles) {
-        if (me < n_tiles) run_tile_steps<P, R, K>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, lds, alpha, beta);
+        if (me < n_tiles) run_tile_steps<P, R, K>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, full, lds, alpha, beta);
       } else if constexpr (K > 0) {
         run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
       }

@@ -343,7 +343,7 @@ void tune_file_save(const tl_ctx* c) {
 struct RunShape {
   tl::RunConfig cfg{};
   std::vector<tl::RunUnit> units;
-  int np = 0, subs = 1, team_size = 1, n_teams = 0, n_tiles = 0;
+  int np = 0, subs = 1, halo = 0, team_size = 1, n_teams = 0, n_tiles = 0;
   size_t scratch = 0;
 };
 
@@ -516,14 +516,14 @@ int cut_cell(const int32_t c[3], int sites, int team, int32_t b[3], int32_t t[3]
 }
 
 // The whole-run launch of a plan for configuration cfg (block: threads per workgroup at most, tz:
-// workgroups per team at most, grid: workgroups, flip: 0 the RHS of a group take turns in a thread,
-// 1 they get threads of their own).  Returns the reason it does not apply, or NULL.
+// workgroups per team at most, grid: workgroups, flip: 1 every RHS of a group gets threads of its
+// own, else nt: 1 two sets of threads share a group's RHS, 0 one thread takes them in turn).  Returns the reason it does not apply, or NULL.
 const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
   const int prec = tl::vprec(p->prec), hop = tl::hop_of(p->prec);
   RunShape r;
   if (p->flags & TL_PLAIN) return "TL_PLAIN runs one step per launch";
-  r.cfg.width = cfg.flip ? 1 : p->width;
-  r.subs = cfg.flip ? p->width : 1;
+  r.subs = cfg.flip ? p->width : cfg.nt ? std::min(2, p->width) : 1;
+  r.cfg.width = (p->width + r.subs - 1) / r.subs;
   const int sites = cfg.block / r.subs / 64 * 64;
   if (sites < 64) return "too few threads per RHS";
   int halo = 0;
@@ -575,7 +575,8 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
   });
   r.cfg.halo = (halo + r.np - 1) / r.np;
   if (r.cfg.halo > 2) return "tiles with too many outer sites";
-  r.cfg.lds = tl::run_lds(prec, r.cfg.width, r.subs, r.np, r.cfg.halo);
+  r.halo = halo;
+  r.cfg.lds = tl::run_lds(prec, r.cfg.width, r.subs, r.np, halo);
   if (r.cfg.lds > 160 * 1024) return "tiling needs more LDS than this device allows";
   r.cfg.grid = std::max(8, (cfg.grid > 0 ? cfg.grid : std::max(p->ctx->n_cu, 1)) / 8 * 8);
   const int per = r.cfg.grid / 8;
@@ -587,7 +588,7 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
     r.n_teams = 8 / xpt;
   }
   const int64_t plane = (int64_t)r.subs * r.cfg.width * tl::kRunWords[prec] * r.team_size * r.np * 16;
-  if (r.n_teams > tl::kMaxRunTeams || plane > INT32_MAX || r.units.size() > p->res.size() * 8 ||
+  if (r.n_teams > tl::kMaxRunTeams || r.cfg.grid > tl::kMaxRunGrid || plane > INT32_MAX || r.units.size() > p->res.size() * 8 ||
       (int64_t)r.units.size() * p->n_steps > INT32_MAX)
     return "work list too long for the whole-run kernel";
   r.scratch = r.cfg.halo ? (size_t)(r.n_teams * 2 * plane) : 0;
@@ -719,6 +720,7 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.team_size = t.run.team_size;
     a.np = t.run.np;
     a.subs = t.run.subs;
+    a.halo = t.run.halo;
     a.hop = tl::hop_of(p->prec);
     a.w12 = tl::is_w12(p->prec);
     return launch(c, "smearing run", [&] { return tl::launch_run(tl::vprec(p->prec), t.run.cfg, a, p->alpha, p->beta, s); });
@@ -844,10 +846,11 @@ int plan_autotune(tl_plan* p) {
   // whole-run launches: every team size that changes the cut, RHS of a group sharing threads or not
   std::vector<StepConfig> cands9;
   if (!(p->flags & (TL_PLAIN | TL_ONE_STEP)) && p->n_steps >= kRunMinSteps && c->big_lds)
-    for (int split : {0, 1})
+    for (int subs = 1; subs <= 3; subs++)   // one set of threads per group, two, one per RHS
       for (int block : {512, 256})
         for (int team : {1, 2, 4, 8, 16, 32, 64, 128, 256})
-          if (!split || p->width > 1) cands9.push_back({9, block, team, 0, 0, split, 0});
+          if (subs == 1 || (subs == 2 ? p->width > 2 : p->width > 1))
+            cands9.push_back({9, block, team, 0, subs == 2, subs == 3, 0});
   void* ref = nullptr;
   void* flag_mem = nullptr;
   TL_TRY(dev_alloc(c, &ref, p->buf_bytes));

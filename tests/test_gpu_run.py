@@ -19,8 +19,10 @@ DIRECT = "0,64,1,0"
 CASES = [((8, 6, 10, 3), [0, 2, 0, 0]), ((4, 4, 2, 1), [0, 0]), ((7, 9, 5, 2), [1, 0]),
          ((32, 24, 20, 2), [0, 1, 1]), ((26, 11, 24, 1), [0, 0, 0, 0]), ((64, 8, 6, 1), [0, 0])]
 
-# "9,threads per workgroup,workgroups per team,grid,0,RHS of a group on threads of their own"
-TILES = ["9,512,32,0,0,0", "9,256,64,0,0,1", "9,512,8,64,0,1", "9,512,256,0,0,0", "9,512,64,8,0,0"]
+# "9,threads per workgroup,workgroups per team,grid,two thread sets per group,one per RHS"; teams
+# of more than 32 workgroups of a full grid span several XCDs
+TILES = ["9,512,32,0,0,0", "9,256,64,0,0,1", "9,512,8,64,0,1", "9,512,256,0,0,0", "9,512,64,8,0,0",
+         "9,512,32,0,1,0", "9,256,128,0,1,0"]
 
 
 @pytest.fixture(scope="module")
