@@ -485,6 +485,12 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
     for (int q = 0; q < X::NW; q++)
       hw[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, hsrc[k], (q0 + r * X::NW + q) * slots * 16, kDeviceScope);
   };
+  auto arrived = [&](int k, uint32_t tag) {
+    bool ok = true;
+#pragma unroll
+    for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
+    return ok;
+  };
   auto halo_issue = [&](int r, int s) {
 #pragma unroll
     for (int k = 0; k < K; k++)
@@ -502,6 +508,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   // everything loaded so far has arrived: inside the loop only halo words are awaited, so that
   // no wait there has to let the step's own stores finish first
   __builtin_amdgcn_s_waitcnt(0);
+  bool ready[K > 0 ? K : 1] = {};
   if constexpr (K > 0) halo_issue(0, 0);
   for (int s = 0; s < a.n_steps; s++) {
     const uint32_t tag = tag0 + (uint32_t)s;
@@ -514,11 +521,9 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
         for (int k = 0; k < K; k++) {
           if (hsrc[k] >= 0) {
             int spin = 0;
-            while (true) {
-              bool ok = true;
-#pragma unroll
-              for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
-              if (ok || dead) break;
+            while (!ready[k]) {
+              ready[k] = arrived(k, tag) || dead;
+              if (ready[k]) break;
               if (++spin > kSpinLimit) {
                 run_failed(a.fail);
                 dead = true;
@@ -569,6 +574,10 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
       rec_get<R>(vl + own + i * REC, r, w);
 #pragma unroll
       for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[c], alpha * w[c]);
+      // the next phase's halo words, looked at before this phase's stores are issued: a wait for
+      // loads counts the stores issued after them as well
+#pragma unroll
+      for (int k = 0; k < K; k++) ready[k] = R > 1 && hsrc[k] >= 0 && arrived(k, r + 1 < R ? tag : tag + 1);
       if (!last) {
         uint32_t d[X::ND];
         X::encode(o, d);
