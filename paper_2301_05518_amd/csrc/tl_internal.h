@@ -187,9 +187,14 @@ struct RunArgs {
 struct RunConfig {
   int grid;               // workgroups, a multiple of 8
   int width;              // RHS per thread
-  int halo;               // halo entries fetched per thread and step: 0, 1 or 2
+  int fetch;              // fetch waves per workgroup (0: every cell is one tile)
   int64_t lds;            // dynamic LDS bytes
 };
+
+// Threads per workgroup at most: FP32 arithmetic fits 168 registers (three waves per SIMD), FP64
+// takes up to 256 (two).
+constexpr int run_max_threads(int prec) { return prec == F64 ? 512 : 768; }
+constexpr int kFetch = 4;   // halo entries a fetch thread takes per phase at most
 
 // 16-byte exchange words of a colour vector per precision.
 constexpr int kRunWords[4] = {4, 2, 2, 1};

@@ -273,8 +273,9 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
   const int slots = a.team_size * a.np;
   const int64_t plane = (int64_t)a.subs * R * X::NW * slots * 16;
   char* const base = a.scratch + team * 2 * plane;
-  const __amdgpu_buffer_rsrc_t res[2] = {__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)plane, 0x00027000),
-                                         __builtin_amdgcn_make_buffer_rsrc(base + plane, 0, (int)plane, 0x00027000)};
+  auto scratch_plane = [&](int s) {
+    return __builtin_amdgcn_make_buffer_rsrc(base + ((par0 + s) & 1) * plane, 0, (int)plane, 0x00027000);
+  };
   bool dead = false;
   for (int s = -1; s < a.n_steps; s++) {   // s = -1 publishes the input
     for (int tile = me; tile < n_tiles; tile += size) {
@@ -294,7 +295,7 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
           X::load(a.in + off, g.Vp, site, d);
         } else {
           auto fetch = [&](int slot, real(&v)[6]) {
-            const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res[1] : res[0];
+            const __amdgpu_buffer_rsrc_t rs = scratch_plane(s);
             v4u w[X::NW];
             int spin = 0;
             while (true) {
@@ -340,7 +341,7 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
           }
           X::encode(o, d);
         }
-        const __amdgpu_buffer_rsrc_t ws = ((par0 + s + 1) & 1) ? res[1] : res[0];
+        const __amdgpu_buffer_rsrc_t ws = scratch_plane(s + 1);
 #pragma unroll
         for (int q = 0; q < X::NW; q++)
           exch_store<kDeviceScope>(exch_word<P>(d, q, tag + 1), ws, (own + (q0 + q) * slots) * 16);
@@ -349,14 +350,72 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
   }
 }
 
-// One unit, one tile per workgroup: `tile` of this workgroup.  np threads per RHS subset,
-// one site each; K: halo entries each thread fetches per step (0: the unit is one tile).
+// Geometry of a workgroup's tile that its compute and fetch waves share.
+struct RunFaces {
+  int f[3];    // sites of a face across direction d (0: the direction is not cut, its ends meet)
+  int hb[3];   // LDS entry of the first halo site of direction d: faces d-, then d+
+};
+__device__ __forceinline__ RunFaces run_faces(const RunUnit& g, int np) {
+  RunFaces q;
+  q.f[0] = g.t[0] > 1 ? g.b[1] * g.b[2] : 0;
+  q.f[1] = g.t[1] > 1 ? g.b[0] * g.b[2] : 0;
+  q.f[2] = g.t[2] > 1 ? g.b[0] * g.b[1] : 0;
+  q.hb[0] = 2 * np;
+  q.hb[1] = q.hb[0] + 2 * q.f[0];
+  q.hb[2] = q.hb[1] + 2 * q.f[1];
+  return q;
+}
+
+// Scratch slot of halo site h of a tile (h counts from the first halo entry), -1 for an entry
+// past the halo or past a ragged tile's edge.
+__device__ __forceinline__ int halo_slot(const RunUnit& g, const RunTile& tl, const RunFaces& fc, int np, int h) {
+  int d = -1, q = 0;
+  bool plus = false;
+#pragma unroll
+  for (int e = 0; e < 3; e++) {
+    const int u = h - (fc.hb[e] - 2 * np);
+    if (fc.f[e] > 0 && u >= 0 && u < 2 * fc.f[e]) {
+      d = e;
+      plus = u >= fc.f[e];
+      q = plus ? u - fc.f[e] : u;
+    }
+  }
+  if (d < 0) return -1;
+  const int w = d == 0 ? g.b[1] : g.b[0];   // fast extent of the face
+  const int u = q % w, v = q / w;
+  const int l[3] = {d == 0 ? 0 : u, d == 0 ? u : d == 1 ? 0 : v, d == 2 ? 0 : v};
+  int c[3];
+  bool ok = true;
+#pragma unroll
+  for (int e = 0; e < 3; e++) {
+    ok = ok && (d == e || l[e] < tl.e[e]);
+    c[e] = e == d ? ring(plus ? tl.o[e] + tl.e[e] : tl.o[e] - 1, g.c[e]) : min(tl.o[e] + l[e], g.c[e] - 1);
+  }
+  return ok ? run_slot(g, np, c[0], c[1], c[2]) : -1;
+}
+
+// What both kinds of waves of run_tile know of the exchange.
+struct RunExch {
+  char* base;                      // the team's two scratch planes, one after the other
+  int plane_bytes;
+  int stride;                      // bytes between the word planes of a scratch plane
+  uint32_t tag0;                   // tag of the input; step s: tag0 + s
+  int par0;                        // scratch plane of the input
+  int ne;                          // LDS entries per RHS subset
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane(int s) const {
+    return __builtin_amdgcn_make_buffer_rsrc(base + (int64_t)((par0 + s) & 1) * plane_bytes, 0, plane_bytes, 0x00027000);
+  }
+};
+
+// The compute waves: np threads per RHS subset, one site each; the RHS of a subset take turns.
 // FP32 arithmetic keeps both two-links of every direction in registers; FP64 keeps the
-// backward ones in LDS (27 planes of np 16-byte words, shared by the RHS subsets).
-template <int P, int R, int K>
-__device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
-                                               int team, bool full, unsigned char* lds, typename Fmt<P>::real alpha,
-                                               typename Fmt<P>::real beta) {
+// backward ones in LDS (27 planes of np 16-byte words, shared by the subsets).  Inside the
+// step loop these waves wait for LDS and the barrier only: loads in their own instruction
+// stream would make every wait for a halo word wait for their stores as well.
+template <int P, int R, bool CUT>
+__device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile, int team,
+                                            bool full, unsigned char* lds, typename Fmt<P>::real alpha,
+                                            typename Fmt<P>::real beta) {
   using real = typename Fmt<P>::real;
   using X = Exch<P>;
   constexpr bool kLdsW = P == F64;
@@ -364,6 +423,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   const int np = a.np;
   const int sub = uniform((int)threadIdx.x / np), i = (int)threadIdx.x - sub * np;
   const RunTile tl = run_tile(g, tile);
+  const RunFaces fc = run_faces(g, np);
   const int bx = g.b[0], by = g.b[1], bz = g.b[2];
   const bool in = i < bx * by * bz;
   const int i0 = in ? i : 0;
@@ -374,13 +434,8 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   const int cx = tl.o[0] + ax, cy = tl.o[1] + ay, cz = tl.o[2] + az;
   const int site = run_site(g, a.hop, cx, cy, cz);
   const int64_t Vp = g.Vp;
-  // LDS entries: own vectors of even and odd steps, then the halo
-  const int ne = 2 * np + (R == 1 ? 2 : 1) * a.halo;
-  unsigned char* const wl = lds + (int64_t)a.subs * ne * REC;
-  unsigned char* const vl = lds + (int64_t)sub * ne * REC;
-  // halo faces x-, x+, y-, y+, z-, z+ (those of directions cut into several tiles)
-  const int f[3] = {g.t[0] > 1 ? by * bz : 0, g.t[1] > 1 ? bx * bz : 0, g.t[2] > 1 ? bx * by : 0};
-  const int hb[3] = {2 * np, 2 * np + 2 * f[0], 2 * np + 2 * (f[0] + f[1])};
+  unsigned char* const wl = lds + (int64_t)a.subs * x.ne * REC;
+  unsigned char* const vl = lds + (int64_t)sub * x.ne * REC;
   int nb[6];   // LDS offset of the neighbour x+, x-, y+, y-, z+, z- (own entries: those of even steps)
   {
     const int l[3] = {ax, ay, az}, st[3] = {1, bx, bx * by};
@@ -388,14 +443,14 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
     const int me = (az * by + ay) * bx + ax;
 #pragma unroll
     for (int d = 0; d < 3; d++) {
-      nb[2 * d] = l[d] + 1 < tl.e[d] ? me + st[d] : f[d] ? hb[d] + f[d] + face[d] : me - l[d] * st[d];
-      nb[2 * d + 1] = l[d] > 0 ? me - st[d] : f[d] ? hb[d] + face[d] : me + (tl.e[d] - 1) * st[d];
+      nb[2 * d] = l[d] + 1 < tl.e[d] ? me + st[d] : fc.f[d] ? fc.hb[d] + fc.f[d] + face[d] : me - l[d] * st[d];
+      nb[2 * d + 1] = l[d] > 0 ? me - st[d] : fc.f[d] ? fc.hb[d] + face[d] : me + (tl.e[d] - 1) * st[d];
     }
   }
   // readers of this site's words: tiles on this XCD see a plain store through their common L2
   // (loads of the words bypass the per-CU caches), tiles on another one need a device-scope store
   bool pub = false, far = false;
-  if constexpr (K > 0) {
+  if constexpr (CUT) {
     const uint32_t* const xcc = a.ctl->xcc + team * a.team_size;
     const int it[3] = {tile % g.t[0], tile / g.t[0] % g.t[1], tile / g.t[0] / g.t[1]};
     const int ts[3] = {1, g.t[0], g.t[0] * g.t[1]};
@@ -403,7 +458,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
 #pragma unroll
     for (int d = 0; d < 6; d++) {
       const int e = d / 2, n = ring(it[e] + (d % 2 ? -1 : 1), g.t[e]);
-      const bool away = !full || (f[e] > 0 && ctl_load(xcc + tile + (n - it[e]) * ts[e]) != here);
+      const bool away = !full || (fc.f[e] > 0 && ctl_load(xcc + tile + (n - it[e]) * ts[e]) != here);
       if (nb[d] >= 2 * np) {
         pub = true;
         far = far || away;
@@ -414,32 +469,6 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   }
 #pragma unroll
   for (int d = 0; d < 6; d++) nb[d] *= REC;
-  int hsrc[K > 0 ? K : 1];
-#pragma unroll
-  for (int k = 0; k < K; k++) {
-    int h = k * np + i, d = -1, q = 0;
-    bool plus = false;
-#pragma unroll
-    for (int e = 0; e < 3; e++) {
-      const int u = h - (hb[e] - 2 * np);
-      if (f[e] > 0 && u >= 0 && u < 2 * f[e]) {
-        d = e;
-        plus = u >= f[e];
-        q = plus ? u - f[e] : u;
-      }
-    }
-    hsrc[k] = -1;
-    if (d >= 0) {
-      const int w = d == 0 ? by : bx;              // fast extent of the face
-      const int u = q % w, v = q / w;
-      int c[3] = {d == 0 ? 0 : u, d == 0 ? u : d == 1 ? 0 : v, d == 2 ? 0 : v};
-      const bool ok = (d == 0 || c[0] < tl.e[0]) && (d == 1 || c[1] < tl.e[1]) && (d == 2 || c[2] < tl.e[2]);
-#pragma unroll
-      for (int e = 0; e < 3; e++)
-        c[e] = e == d ? ring(plus ? tl.o[e] + tl.e[e] : tl.o[e] - 1, g.c[e]) : min(tl.o[e] + c[e], g.c[e] - 1);
-      if (ok) hsrc[k] = run_slot(g, np, c[0], c[1], c[2]) * 16;
-    }
-  }
   real wf[3][18], wb[kLdsW ? 1 : 3][18];
 #pragma unroll
   for (int mu = 0; mu < 3; mu++) {
@@ -457,98 +486,40 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
       run_load_w<P>(a.w12, W, Vp, bs, wb[mu]);
     }
   }
-  const int slots = a.team_size * np;
-  const int64_t plane = (int64_t)a.subs * R * X::NW * slots * 16;
-  char* const base = a.scratch + team * 2 * plane;
-  const __amdgpu_buffer_rsrc_t res0 = __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)plane, 0x00027000);
-  const __amdgpu_buffer_rsrc_t res1 = __builtin_amdgcn_make_buffer_rsrc(base + plane, 0, (int)plane, 0x00027000);
-  const int q0 = sub * R * X::NW;
-  const int mine = (tile * np + i) * 16;
-  bool dead = false;
+  const int mine = sub * R * X::NW * x.stride + (tile * np + i) * 16;
   auto publish = [&](int r, int s, const uint32_t (&d)[X::ND]) {
-    const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
+    const __amdgpu_buffer_rsrc_t rs = x.plane(s);
     if (pub) {
 #pragma unroll
       for (int q = 0; q < X::NW; q++)
-        exch_store<0>(exch_word<P>(d, q, tag0 + (uint32_t)s), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+        exch_store<0>(exch_word<P>(d, q, x.tag0 + (uint32_t)s), rs, mine + (r * X::NW + q) * x.stride);
     }
     if (far) {
 #pragma unroll
       for (int q = 0; q < X::NW; q++)
-        exch_store<kDeviceScope>(exch_word<P>(d, q, tag0 + (uint32_t)s), rs, mine + (q0 + r * X::NW + q) * slots * 16);
+        exch_store<kDeviceScope>(exch_word<P>(d, q, x.tag0 + (uint32_t)s), rs, mine + (r * X::NW + q) * x.stride);
     }
-  };
-  v4u hw[K > 0 ? K : 1][X::NW];
-  auto halo_load = [&](int k, int r, int s) {
-    const __amdgpu_buffer_rsrc_t rs = ((par0 + s) & 1) ? res1 : res0;
-#pragma unroll
-    for (int q = 0; q < X::NW; q++)
-      hw[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, hsrc[k], (q0 + r * X::NW + q) * slots * 16, kDeviceScope);
-  };
-  auto arrived = [&](int k, uint32_t tag) {
-    bool ok = true;
-#pragma unroll
-    for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
-    return ok;
-  };
-  auto halo_issue = [&](int r, int s) {
-#pragma unroll
-    for (int k = 0; k < K; k++)
-      if (hsrc[k] >= 0) halo_load(k, r, s);
   };
 #pragma unroll
   for (int r = 0; r < R; r++) {
     uint32_t d[X::ND];
     X::load(a.in + g.psi_off + (int64_t)min(sub * R + r, g.nr - 1) * g.rhs_stride, Vp, site, d);
-    if constexpr (K > 0) publish(r, 0, d);
+    if constexpr (CUT) publish(r, 0, d);
     real v[6];
     X::decode(d, v);
     rec_put<R>(vl + i * REC, r, v);
   }
-  // everything loaded so far has arrived: inside the loop only halo words are awaited, so that
-  // no wait there has to let the step's own stores finish first
-  __builtin_amdgcn_s_waitcnt(0);
-  bool ready[K > 0 ? K : 1] = {};
-  if constexpr (K > 0) halo_issue(0, 0);
+  __builtin_amdgcn_s_waitcnt(0);   // the two-links have arrived: no wait for them in the loop
   for (int s = 0; s < a.n_steps; s++) {
-    const uint32_t tag = tag0 + (uint32_t)s;
     const int own = (s & 1) ? np * REC : 0;
+    const int hal = R == 1 && (s & 1) ? a.halo * REC : 0;
     const bool last = s + 1 == a.n_steps;
 #pragma unroll
     for (int r = 0; r < R; r++) {
-      if constexpr (K > 0) {
-#pragma unroll
-        for (int k = 0; k < K; k++) {
-          if (hsrc[k] >= 0) {
-            int spin = 0;
-            while (!ready[k]) {
-              ready[k] = arrived(k, tag) || dead;
-              if (ready[k]) break;
-              if (++spin > kSpinLimit) {
-                run_failed(a.fail);
-                dead = true;
-              }
-              asm volatile("" ::: "memory");
-              halo_load(k, r, s);
-            }
-            uint32_t d[X::ND];
-            exch_dwords<P>(hw[k], d);
-            real u[6];
-            X::decode(d, u);
-            rec_put<R>(vl + (2 * np + (R == 1 && (s & 1) ? a.halo : 0) + k * np + i) * REC, r, u);
-          }
-        }
-      }
       lds_barrier();
-      // the next phase's halo: its words were published R - 1 phases ago
-      if constexpr (K > 0 && R > 1) {
-        if (r + 1 < R) halo_issue(r + 1, s);
-        else if (!last) halo_issue(0, s + 1);
-      }
       real acc[6];
 #pragma unroll
       for (int c = 0; c < 6; c++) acc[c] = (real)0;
-      const int hal = R == 1 && (s & 1) ? a.halo * REC : 0;
 #pragma unroll
       for (int mu = 0; mu < 3; mu++) {
         const unsigned char* const ef = vl + nb[2 * mu] + (nb[2 * mu] < np * REC ? own : hal);
@@ -574,17 +545,10 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
       rec_get<R>(vl + own + i * REC, r, w);
 #pragma unroll
       for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[c], alpha * w[c]);
-      // the next phase's halo words, looked at before this phase's stores are issued: a wait for
-      // loads counts the stores issued after them as well
-#pragma unroll
-      for (int k = 0; k < K; k++) ready[k] = R > 1 && hsrc[k] >= 0 && arrived(k, r + 1 < R ? tag : tag + 1);
       if (!last) {
         uint32_t d[X::ND];
         X::encode(o, d);
-        if constexpr (K > 0) {
-          publish(r, s + 1, d);
-          if constexpr (R == 1) halo_issue(0, s + 1);
-        }
+        if constexpr (CUT) publish(r, s + 1, d);
         X::decode(d, w);
         rec_put<R>(vl + (np * REC - own) + i * REC, r, w);
       } else if (active && sub * R + r < g.nr) {
@@ -594,8 +558,92 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   }
 }
 
-template <int P, int R, int K>
-__global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
+// The fetch waves: between two barriers they collect the halo of the next phase.  Its words
+// were published R - 1 phases ago (by the phase before, where a thread has one RHS), so with
+// several RHS per thread both the store's and the load's latency run behind arithmetic.
+template <int P, int R>
+__device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile,
+                                          unsigned char* lds) {
+  using real = typename Fmt<P>::real;
+  using X = Exch<P>;
+  constexpr int REC = run_record(P, R);
+  const int np = a.np;
+  const int lane = (int)threadIdx.x - np * a.subs, lanes = (int)blockDim.x - np * a.subs;
+  const RunTile tl = run_tile(g, tile);
+  const RunFaces fc = run_faces(g, np);
+  int src[kFetch];            // byte offset of the first word, -1: no entry
+  unsigned char* dst[kFetch];
+#pragma unroll
+  for (int k = 0; k < kFetch; k++) {
+    const int e = lane + k * lanes;
+    const int sub = e / a.halo, h = e - sub * a.halo;
+    const int slot = sub < a.subs ? halo_slot(g, tl, fc, np, h) : -1;
+    src[k] = slot < 0 ? -1 : sub * R * X::NW * x.stride + slot * 16;
+    dst[k] = lds + ((int64_t)(sub < a.subs ? sub : 0) * x.ne + 2 * np + h) * REC;
+  }
+  bool dead = false;
+  __builtin_amdgcn_s_setprio(3);   // few instructions, on which every wave of the workgroup waits
+  for (int s = 0; s < a.n_steps; s++) {
+    const uint32_t tag = x.tag0 + (uint32_t)s;
+    const __amdgpu_buffer_rsrc_t rs = x.plane(s);
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      v4u hw[kFetch][X::NW];
+      auto load = [&](int k) {
+#pragma unroll
+        for (int q = 0; q < X::NW; q++)
+          hw[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, src[k], (r * X::NW + q) * x.stride, kDeviceScope);
+      };
+#pragma unroll
+      for (int k = 0; k < kFetch; k++)
+        if (src[k] >= 0) load(k);
+#pragma unroll
+      for (int k = 0; k < kFetch; k++) {
+        if (src[k] < 0) continue;
+        int spin = 0;
+        while (true) {
+          bool ok = true;
+#pragma unroll
+          for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
+          if (ok || dead) break;
+          if (++spin > kSpinLimit) {
+            run_failed(a.fail);
+            dead = true;
+          }
+          asm volatile("" ::: "memory");
+          load(k);
+        }
+        uint32_t d[X::ND];
+        exch_dwords<P>(hw[k], d);
+        real u[6];
+        X::decode(d, u);
+        rec_put<R>(dst[k] + (R == 1 && (s & 1) ? a.halo * REC : 0), r, u);
+      }
+      lds_barrier();
+    }
+  }
+  __builtin_amdgcn_s_setprio(0);
+}
+
+// One unit, one tile per workgroup: `tile` of this workgroup.
+template <int P, int R, bool CUT>
+__device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
+                                               int team, bool full, unsigned char* lds, typename Fmt<P>::real alpha,
+                                               typename Fmt<P>::real beta) {
+  RunExch x;
+  x.stride = a.team_size * a.np * 16;
+  const int64_t plane = (int64_t)a.subs * R * Exch<P>::NW * x.stride;
+  x.base = a.scratch + team * 2 * plane;
+  x.plane_bytes = (int)plane;
+  x.tag0 = tag0;
+  x.par0 = par0;
+  x.ne = 2 * a.np + (R == 1 ? 2 : 1) * a.halo;
+  if (CUT && uniform((int)threadIdx.x) >= a.np * a.subs) run_fetch<P, R>(a, g, x, tile, lds);
+  else run_compute<P, R, CUT>(a, g, x, tile, team, full, lds, alpha, beta);
+}
+
+template <int P, int R, bool CUT>
+__global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   uint32_t* const sh = reinterpret_cast<uint32_t*>(lds_raw);   // 16 bytes of messages, then the vectors
   unsigned char* const lds = lds_raw + 16;
@@ -604,7 +652,7 @@ __global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::rea
   if (threadIdx.x == 0) {
     uint32_t e = 1u << 20, size = 0;
     if (pl.rank < pl.expect) {
-      if constexpr (K > 0) {
+      if constexpr (CUT) {
         ctl_store(a.ctl->xcc + pl.team * a.team_size + pl.rank, xcd_id());
         __builtin_amdgcn_s_waitcnt(0);   // there before this workgroup counts as enrolled
       }
@@ -658,9 +706,9 @@ __global__ __launch_bounds__(512) void smear_run(RunArgs a, typename Fmt<P>::rea
       const int n_tiles = g.t[0] * g.t[1] * g.t[2];
       const uint32_t pubs = seq * (uint32_t)a.n_steps;
       if (size >= n_tiles) {
-        if (me < n_tiles) run_tile_steps<P, R, K>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, full, lds, alpha, beta);
-      } else if constexpr (K > 0) {
-        run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
+        if (me < n_tiles) run_tile_steps<P, R, CUT>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, full, lds, alpha, beta);
+      } else if constexpr (CUT) {
+        if ((int)threadIdx.x < a.np * a.subs) run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
       }
       __syncthreads();   // every thread has read what it waited for before the team may move on
     }
@@ -690,16 +738,16 @@ template <int P, int R>
 hipError_t launch_run_k(const RunConfig& c, const RunArgs& a, double alpha, double beta, hipStream_t s) {
   using real = typename Fmt<P>::real;
   const real al = (real)alpha, be = (real)beta;
-  const int threads = a.np * a.subs;
-  if (c.halo == 0) smear_run<P, R, 0><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
-  else if (c.halo == 1) smear_run<P, R, 1><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
-  else smear_run<P, R, 2><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
+  const int threads = a.np * a.subs + 64 * c.fetch;
+  if (c.fetch == 0) smear_run<P, R, false><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
+  else smear_run<P, R, true><<<c.grid, threads, (size_t)c.lds, s>>>(a, al, be);
   return hipGetLastError();
 }
 
 template <int P>
 hipError_t launch_run_p(const RunConfig& c, const RunArgs& a, double alpha, double beta, hipStream_t s) {
-  if (a.np < 64 || a.np % 64 || a.np * a.subs > 512 || c.halo < 0 || c.halo > 2 || c.lds > kMaxLds || c.grid % kXcds)
+  if (a.np < 64 || a.np % 64 || a.np * a.subs + 64 * c.fetch > run_max_threads(P) || c.lds > kMaxLds || c.grid % kXcds ||
+      (c.fetch > 0) != (a.halo > 0) || a.subs * a.halo > 64 * c.fetch * kFetch)
     return hipErrorInvalidValue;
   switch (c.width) {
     case 1: return launch_run_k<P, 1>(c, a, alpha, beta, s);
@@ -712,8 +760,8 @@ hipError_t launch_run_p(const RunConfig& c, const RunArgs& a, double alpha, doub
 
 template <int P, int R>
 hipError_t run_allow_lds() {
-  for (const void* f : {reinterpret_cast<const void*>(&smear_run<P, R, 0>), reinterpret_cast<const void*>(&smear_run<P, R, 1>),
-                        reinterpret_cast<const void*>(&smear_run<P, R, 2>)}) {
+  for (const void* f : {reinterpret_cast<const void*>(&smear_run<P, R, false>),
+                        reinterpret_cast<const void*>(&smear_run<P, R, true>)}) {
     const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
     if (e != hipSuccess) return e;
   }

@@ -573,8 +573,10 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
   std::stable_sort(r.units.begin(), r.units.end(), [](const tl::RunUnit& a, const tl::RunUnit& b) {
     return (int64_t)a.c[0] * a.c[1] * a.c[2] > (int64_t)b.c[0] * b.c[1] * b.c[2];
   });
-  r.cfg.halo = (halo + r.np - 1) / r.np;
-  if (r.cfg.halo > 2) return "tiles with too many outer sites";
+  // fetch waves: one halo entry per thread as far as the workgroup has room
+  const int room = (tl::run_max_threads(prec) - r.np * r.subs) / 64, entries = r.subs * halo;
+  r.cfg.fetch = std::min(room, (entries + 63) / 64);
+  if (64 * tl::kFetch * r.cfg.fetch < entries) return "too many threads per workgroup";
   r.halo = halo;
   r.cfg.lds = tl::run_lds(prec, r.cfg.width, r.subs, r.np, halo);
   if (r.cfg.lds > 160 * 1024) return "tiling needs more LDS than this device allows";
@@ -591,7 +593,7 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
   if (r.n_teams > tl::kMaxRunTeams || r.cfg.grid > tl::kMaxRunGrid || plane > INT32_MAX || r.units.size() > p->res.size() * 8 ||
       (int64_t)r.units.size() * p->n_steps > INT32_MAX)
     return "work list too long for the whole-run kernel";
-  r.scratch = r.cfg.halo ? (size_t)(r.n_teams * 2 * plane) : 0;
+  r.scratch = r.cfg.fetch ? (size_t)(r.n_teams * 2 * plane) : 0;
   *out = std::move(r);
   return nullptr;
 }
