@@ -548,7 +548,10 @@ __device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, 
       if (!last) {
         uint32_t d[X::ND];
         X::encode(o, d);
-        if constexpr (CUT) publish(r, s + 1, d);
+        if constexpr (CUT) {
+          publish(r, s + 1, d);
+          if constexpr (R == 1) __builtin_amdgcn_s_barrier();   // the fetch waves start here (see run_fetch)
+        }
         X::decode(d, w);
         rec_put<R>(vl + (np * REC - own) + i * REC, r, w);
       } else if (active && sub * R + r < g.nr) {
@@ -558,10 +561,12 @@ __device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, 
   }
 }
 
-// The fetch waves: between two barriers they collect the halo of the next phase.  Its words
-// were published R - 1 phases ago (by the phase before, where a thread has one RHS), so with
-// several RHS per thread both the store's and the load's latency run behind arithmetic.
-template <int P, int R>
+// The fetch waves: they collect the halo of each phase, E entries a thread, and write it to LDS
+// before the barrier that opens the phase.  A phase's words were published R - 1 phases ago (by
+// the phase before, where a thread has one RHS), so with several RHS per thread the store's and
+// the load's latency run behind arithmetic.  (Requesting them a phase earlier still finds most
+// of them not published yet and asks again: 70 instead of 60 us per step at 64^3 FP32 24 RHS.)
+template <int P, int R, int E>
 __device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile,
                                           unsigned char* lds) {
   using real = typename Fmt<P>::real;
@@ -571,54 +576,61 @@ __device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, co
   const int lane = (int)threadIdx.x - np * a.subs, lanes = (int)blockDim.x - np * a.subs;
   const RunTile tl = run_tile(g, tile);
   const RunFaces fc = run_faces(g, np);
-  int src[kFetch];            // byte offset of the first word, -1: no entry
-  unsigned char* dst[kFetch];
+  int src[E];            // byte offset of the first word; outside the plane (read as zeros) without an entry
+  bool has[E];
+  unsigned char* dst[E];
 #pragma unroll
-  for (int k = 0; k < kFetch; k++) {
+  for (int k = 0; k < E; k++) {
     const int e = lane + k * lanes;
     const int sub = e / a.halo, h = e - sub * a.halo;
     const int slot = sub < a.subs ? halo_slot(g, tl, fc, np, h) : -1;
-    src[k] = slot < 0 ? -1 : sub * R * X::NW * x.stride + slot * 16;
+    has[k] = slot >= 0;
+    src[k] = has[k] ? sub * R * X::NW * x.stride + slot * 16 : x.plane_bytes;
     dst[k] = lds + ((int64_t)(sub < a.subs ? sub : 0) * x.ne + 2 * np + h) * REC;
   }
   bool dead = false;
-  __builtin_amdgcn_s_setprio(3);   // few instructions, on which every wave of the workgroup waits
-  for (int s = 0; s < a.n_steps; s++) {
-    const uint32_t tag = x.tag0 + (uint32_t)s;
+  // loads of phase (s, r); unconditional, so that the number of loads in flight is known
+  auto load = [&](int k, int s, int r, v4u(&w)[X::NW]) {
     const __amdgpu_buffer_rsrc_t rs = x.plane(s);
 #pragma unroll
-    for (int r = 0; r < R; r++) {
-      v4u hw[kFetch][X::NW];
-      auto load = [&](int k) {
+    for (int q = 0; q < X::NW; q++)
+      w[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, src[k], (r * X::NW + q) * x.stride, kDeviceScope);
+  };
+  auto take = [&](int s, int r, v4u(&hw)[E][X::NW]) {
+    const uint32_t tag = x.tag0 + (uint32_t)s;
 #pragma unroll
-        for (int q = 0; q < X::NW; q++)
-          hw[k][q] = __builtin_amdgcn_raw_buffer_load_b128(rs, src[k], (r * X::NW + q) * x.stride, kDeviceScope);
-      };
+    for (int k = 0; k < E; k++) {
+      int spin = 0;
+      while (true) {
+        bool ok = true;
 #pragma unroll
-      for (int k = 0; k < kFetch; k++)
-        if (src[k] >= 0) load(k);
-#pragma unroll
-      for (int k = 0; k < kFetch; k++) {
-        if (src[k] < 0) continue;
-        int spin = 0;
-        while (true) {
-          bool ok = true;
-#pragma unroll
-          for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
-          if (ok || dead) break;
-          if (++spin > kSpinLimit) {
-            run_failed(a.fail);
-            dead = true;
-          }
-          asm volatile("" ::: "memory");
-          load(k);
+        for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
+        if (ok || !has[k] || dead) break;
+        if (++spin > kSpinLimit) {
+          run_failed(a.fail);
+          dead = true;
         }
-        uint32_t d[X::ND];
-        exch_dwords<P>(hw[k], d);
-        real u[6];
-        X::decode(d, u);
-        rec_put<R>(dst[k] + (R == 1 && (s & 1) ? a.halo * REC : 0), r, u);
+        asm volatile("" ::: "memory");
+        load(k, s, r, hw[k]);
       }
+      uint32_t d[X::ND];
+      exch_dwords<P>(hw[k], d);
+      real u[6];
+      X::decode(d, u);
+      if (has[k]) rec_put<R>(dst[k] + (R == 1 && (s & 1) ? a.halo * REC : 0), r, u);
+    }
+  };
+  __builtin_amdgcn_s_setprio(3);   // few instructions, on which every wave of the workgroup waits
+  for (int s = 0; s < a.n_steps; s++) {
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+      // One RHS per thread: its words are published when the neighbours' phase ends, about when
+      // this workgroup's does; polling from the phase's start would only load the caches.
+      if (R == 1 && s > 0) __builtin_amdgcn_s_barrier();
+      v4u hw[E][X::NW];
+#pragma unroll
+      for (int k = 0; k < E; k++) load(k, s, r, hw[k]);
+      take(s, r, hw);
       lds_barrier();
     }
   }
@@ -638,8 +650,14 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   x.tag0 = tag0;
   x.par0 = par0;
   x.ne = 2 * a.np + (R == 1 ? 2 : 1) * a.halo;
-  if (CUT && uniform((int)threadIdx.x) >= a.np * a.subs) run_fetch<P, R>(a, g, x, tile, lds);
-  else run_compute<P, R, CUT>(a, g, x, tile, team, full, lds, alpha, beta);
+  if (CUT && uniform((int)threadIdx.x) >= a.np * a.subs) {
+    const int lanes = (int)blockDim.x - a.np * a.subs, entries = a.subs * a.halo;
+    if (entries <= lanes) run_fetch<P, R, 1>(a, g, x, tile, lds);
+    else if (entries <= 2 * lanes) run_fetch<P, R, 2>(a, g, x, tile, lds);
+    else run_fetch<P, R, kFetch>(a, g, x, tile, lds);
+  } else {
+    run_compute<P, R, CUT>(a, g, x, tile, team, full, lds, alpha, beta);
+  }
 }
 
 template <int P, int R, bool CUT>

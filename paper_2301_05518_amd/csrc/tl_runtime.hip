@@ -969,11 +969,27 @@ int plan_autotune(tl_plan* p) {
     }
   }
   if (rc == TL_OK && !cands9.empty()) {
-    // whole-run launches (all n steps each), against n launches of the one-step winner
+    // whole-run launches (all n steps each), against n launches of the one-step winner from
+    // buffer to buffer.  The winner so far is timed over such a run too: launches that all read
+    // one buffer find their input in the caches, those of a run do not.
     rc = upload_tiling(p, best_cfg, &p->single);
+    if (rc == TL_OK && tu.cfg.variant == 8) rc = upload_tiling(p, tu.cfg, &p->tile);
     char* pair[2] = {p->buf[p->cur ^ 1], static_cast<char*>(ref)};
-    for (int k = 0; k < p->n_steps && rc == TL_OK; k++)
-      rc = plan_launch(p, p->single, c->stream, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k);
+    auto sequence = [&](const tl_plan::Tiling& t, int launches) -> int {
+      for (int k = 0; k < launches; k++)
+        TL_TRY(plan_launch(p, t, c->stream, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k));
+      return TL_OK;
+    };
+    for (int rep = 0; rep < 2 && rc == TL_OK; rep++) {
+      (void)hipEventRecord(e0, c->stream);
+      rc = tu.cfg.variant == 8 ? sequence(p->tile, p->n_steps / 2) : sequence(p->single, p->n_steps);
+      (void)hipEventRecord(e1, c->stream);
+      float ms = 0.0f;
+      if (rc == TL_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
+        rc = fail(c, TL_ERR_HIP, "autotune timing failed");
+      best = ms / (tu.cfg.variant == 8 ? p->n_steps / 2 * 2 : p->n_steps);
+    }
+    if (rc == TL_OK) rc = sequence(p->single, p->n_steps);
     if (rc == TL_OK && (p->n_steps & 1) &&
         hipMemcpyAsync(ref, pair[0], p->buf_bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
       rc = fail(c, TL_ERR_HIP, "autotune reference copy failed");
