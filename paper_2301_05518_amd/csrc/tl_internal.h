@@ -213,7 +213,10 @@ inline int64_t run_lds(int prec, int width, int subs, int np, int halo) {
 #define TL_RUN_DECL(name)                                                                                \
   hipError_t launch_run_##name(const RunConfig& cfg, const RunArgs& args, double alpha, double beta,     \
                                hipStream_t stream);                                                      \
-  hipError_t run_attributes_##name();
+  hipError_t run_attributes_##name();                                                                    \
+  hipError_t launch_laplacian_##name(const char* W, int64_t w_mu_stride, int Vp, const int32_t L[4],     \
+                                     int hop, bool w12, const void* in, void* out, double alpha,         \
+                                     double beta, hipStream_t stream);
 TL_RUN_DECL(f64)
 TL_RUN_DECL(f32)
 TL_RUN_DECL(f16s)
@@ -228,6 +231,18 @@ inline hipError_t launch_run(int prec, const RunConfig& cfg, const RunArgs& args
     case F16S: return launch_run_f16s(cfg, args, alpha, beta, stream);
     default: return launch_run_bf16(cfg, args, alpha, beta, stream);
   }
+}
+
+// out = alpha in + beta sum_hops on one slice of natural complex128 vectors, rounded to format `code`'s
+// precision before and after (tl_laplacian.h); W: the slice's packed link slot.
+inline hipError_t launch_laplacian(int code, const char* W, int Vp, const int32_t L[4], const void* in, void* out,
+                                   double alpha, double beta, hipStream_t stream) {
+  const int64_t stride = (int64_t)Vp * kWBytes[code];
+  const auto f = vprec(code) == F64   ? launch_laplacian_f64
+                 : vprec(code) == F32 ? launch_laplacian_f32
+                 : vprec(code) == F16S ? launch_laplacian_f16s
+                                       : launch_laplacian_bf16;
+  return f(W, stride, Vp, L, hop_of(code), is_w12(code), in, out, alpha, beta, stream);
 }
 
 // W slots slot_first .. slot_first+n-1 from slices t_first .. t_first+n-1, in format `code`:

@@ -1,4 +1,6 @@
-// Whole-run kernels stored in F32: every link form (two-links or one-links, 18 or 12 reals).
+// Whole-run kernels and the Laplacian stored in F32: every link form (two-links or one-links, 18
+// or 12 reals).
+#include "tl_laplacian.h"
 #include "tl_run.h"
 
 namespace tl {
@@ -8,5 +10,10 @@ hipError_t launch_run_f32(const RunConfig& cfg, const RunArgs& args, double alph
 }
 
 hipError_t run_attributes_f32() { return run_attributes<F32>(); }
+
+hipError_t launch_laplacian_f32(const char* W, int64_t w_mu_stride, int Vp, const int32_t L[4], int hop, bool w12,
+                               const void* in, void* out, double alpha, double beta, hipStream_t stream) {
+  return launch_laplacian_p<F32>(W, w_mu_stride, Vp, L, hop, w12, in, out, alpha, beta, stream);
+}
 
 }  // namespace tl

@@ -1315,39 +1315,11 @@ int tl_laplacian(tl_ctx* c, const tl_geom* g, const void* W, const int32_t* w_sl
     if (a < b + nat_bytes && b < a + nat_bytes) return fail(c, TL_ERR_ARG, "in and out overlap");
     TL_TRY(need_device(c));
     TL_ON_DEVICE(c);
-    const int code = fmt_code(prec), vp = tl::vprec(code);
-    const size_t fb = align256((size_t)Vp * tl::kVBytes[vp]);
-    char* s = nullptr;
-    TL_TRY(ctx_scratch(c, 1024 + 2 * fb, &s));
-    StepGroup sg{};
-    StepConfig cfg{0, 256, 4, 0, 0};
-    sg.W = static_cast<const char*>(W) + (int64_t)slot * 3 * Vp * tl::kWBytes[code];
-    sg.w_mu_stride = Vp * tl::kWBytes[code];
-    sg.psi_off = 0;
-    sg.rhs_stride = 0;
-    sg.Lx = g->L[0];
-    sg.Ly = g->L[1];
-    sg.Lz = g->L[2];
-    sg.Vp = (int32_t)Vp;
-    sg.nr = 1;
-    sg.n_xy_tiles = (int32_t)(((int64_t)g->L[0] * g->L[1] + cfg.block - 1) / cfg.block);
-    sg.n_z_tiles = (g->L[2] + cfg.tz - 1) / cfg.tz;
-    sg.tile_begin = 0;
-    struct {
-      StepGroup g;
-      int64_t off0;
-    } tab{sg, 0};
-    TL_TRY(upload(c, s, &tab, sizeof tab));
-    const StepGroup* gdev = reinterpret_cast<const StepGroup*>(s);
-    const int64_t* offdev = reinterpret_cast<const int64_t*>(s + offsetof(decltype(tab), off0));
-    char* A = s + 1024;
-    char* B = A + fb;
-    TL_TRY(launch(c, "pack", [&] { return tl::launch_pack(vp, in, A, offdev, 1, V3, Vp, c->stream); }));
+    const int code = fmt_code(prec);
+    const char* slice = static_cast<const char*>(W) + (int64_t)slot * 3 * Vp * tl::kWBytes[code];
     // Lap = alpha in + beta sum_hops: two-link -3/2, 1/4 (eq. tlLapl1); one-link -6, 1 (H - 6)
     const double la = tl::is_one(code) ? -6.0 : -1.5, lb = tl::is_one(code) ? 1.0 : 0.25;
-    TL_TRY(launch(c, "laplacian", [&] { return tl::launch_step(code, 1, cfg, gdev, 1, 0, sg.n_xy_tiles * sg.n_z_tiles, A, B, la, lb,
-                                        0, c->stream); }));
-    return launch(c, "unpack", [&] { return tl::launch_unpack(vp, B, out, offdev, 1, V3, Vp, c->stream); });
+    return launch(c, "laplacian", [&] { return tl::launch_laplacian(code, slice, (int)Vp, g->L, in, out, la, lb, c->stream); });
   } catch (...) {
     return host_failure(c);
   }
