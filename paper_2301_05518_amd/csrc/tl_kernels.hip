@@ -160,7 +160,16 @@ __global__ __launch_bounds__(256) void unpack_kernel(const char* __restrict__ pa
 // ------------------------------------------------------------------ reductions
 
 constexpr int kRedBlock = 256;
-constexpr int kRedSitesPerBlock = 4096;
+
+// Sites per block of a reduction's first pass.  4096 (16 sites a thread) while that gives every
+// CU eight blocks; below, the blocks shrink to two sites a thread, because what bounds a small
+// reduction is how many loads are in flight (12 fields of 48^3: 324 blocks of 4096 sites read
+// at 1.8 TB/s).  Depends on the sizes only, so a result is the same bits every time.
+inline int red_sites_per_block(int n_rhs, int64_t max_v3) {
+  int spb = 4096;
+  while (spb > 512 && (int64_t)std::max(n_rhs, 1) * ((max_v3 + spb - 1) / spb) < 2048) spb /= 2;
+  return spb;
+}
 
 // Natural complex128 vectors: [..][site][3].
 struct NatLoad {
@@ -215,14 +224,14 @@ struct FlatFields {
 // and in-block orders make the result reproducible run to run.
 template <class LD, class F>
 __global__ __launch_bounds__(kRedBlock) void reduce_partial_kernel(int kind, const char* __restrict__ a,
-                                                                   const char* __restrict__ b, F f,
+                                                                   const char* __restrict__ b, F f, int spb,
                                                                    double* __restrict__ partials) {
   __shared__ double lds[kRedBlock / 64];
   const int r = blockIdx.y;
   const int nb = gridDim.x;
   const RedField fr = f(r);
-  const int64_t s0 = (int64_t)blockIdx.x * kRedSitesPerBlock;
-  const int64_t s1 = min(s0 + (int64_t)kRedSitesPerBlock, fr.V3);
+  const int64_t s0 = (int64_t)blockIdx.x * spb;
+  const int64_t s1 = min(s0 + (int64_t)spb, fr.V3);
   double re = 0.0, im = 0.0;
   for (int64_t i = s0 + threadIdx.x; i < s1; i += blockDim.x) {
     double v[6];
@@ -250,15 +259,63 @@ __global__ __launch_bounds__(kRedBlock) void reduce_partial_kernel(int kind, con
   }
 }
 
-__global__ void reduce_finish_kernel(int kind, const double* __restrict__ partials, int nb, int n_rhs,
-                                     double* __restrict__ out) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= n_rhs) return;
+// The same for natural fields of n sites each: a sum over sites and colours is one over 3 n
+// complex numbers, read by consecutive lanes.  D: phi's inner product with psi, else norm.
+template <bool D>
+__global__ __launch_bounds__(kRedBlock) void reduce_flat_kernel(const v2d* __restrict__ psi, const v2d* __restrict__ phi,
+                                                                int64_t n, int spb, double* __restrict__ partials) {
+  __shared__ double lds[kRedBlock / 64];
+  const int r = blockIdx.y, nb = gridDim.x;
+  const int64_t base = 3 * (int64_t)r * n;
+  const int64_t e0 = 3 * (int64_t)blockIdx.x * spb, e1 = min(e0 + 3 * (int64_t)spb, 3 * n);
+  constexpr int U = 6;   // loads in flight per thread and field
   double re = 0.0, im = 0.0;
-  for (int k = 0; k < nb; k++) {
-    re += partials[((int64_t)r * nb + k) * 2];
-    im += partials[((int64_t)r * nb + k) * 2 + 1];
+  for (int64_t e = e0 + threadIdx.x; e < e1; e += U * kRedBlock) {
+    v2d v[U], u[U];
+#pragma unroll
+    for (int k = 0; k < U; k++) {   // past the end: the last number again, not added
+      const int64_t i = base + min(e + k * kRedBlock, e1 - 1);
+      v[k] = psi[i];
+      if constexpr (D) u[k] = phi[i];
+    }
+#pragma unroll
+    for (int k = 0; k < U; k++) {
+      if (e + k * kRedBlock >= e1) continue;
+      if constexpr (D) {   // conj(u) v
+        re = fma_(u[k].x, v[k].x, re);
+        re = fma_(u[k].y, v[k].y, re);
+        im = fma_(u[k].x, v[k].y, im);
+        im = fma_(-u[k].y, v[k].x, im);
+      } else {
+        re = fma_(v[k].x, v[k].x, re);
+        re = fma_(v[k].y, v[k].y, re);
+      }
+    }
   }
+  re = block_sum(re, lds);
+  if constexpr (D) im = block_sum(im, lds);
+  if (threadIdx.x == 0) {
+    partials[((int64_t)r * nb + blockIdx.x) * 2] = re;
+    partials[((int64_t)r * nb + blockIdx.x) * 2 + 1] = im;
+  }
+}
+
+// One wave per RHS: lane l sums the partial sums l, l + 64, ..., then a butterfly.
+__global__ __launch_bounds__(64) void reduce_finish_kernel(int kind, const double* __restrict__ partials, int nb,
+                                                           double* __restrict__ out) {
+  const int r = blockIdx.x, lane = threadIdx.x;
+  double re = 0.0, im = 0.0;
+  for (int k = lane; k < nb; k += 64) {
+    const v2d w = *reinterpret_cast<const v2d*>(partials + ((int64_t)r * nb + k) * 2);
+    re += w.x;
+    im += w.y;
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    re += __shfl_xor(re, o, 64);
+    im += __shfl_xor(im, o, 64);
+  }
+  if (lane != 0) return;
   if (kind == 0) {
     out[r] = re;
   } else {
@@ -415,7 +472,8 @@ hipError_t launch_unpack(int prec, const char* packed, void* nat, const int64_t*
 }
 
 int64_t red_partials_doubles(int n_rhs, int64_t max_v3) {
-  const int64_t nb = std::max<int64_t>(1, (max_v3 + kRedSitesPerBlock - 1) / kRedSitesPerBlock);
+  const int spb = red_sites_per_block(n_rhs, max_v3);
+  const int64_t nb = std::max<int64_t>(1, (max_v3 + spb - 1) / spb);
   return 2 * nb * std::max(n_rhs, 1);
 }
 
@@ -427,8 +485,11 @@ hipError_t reduce_with(int kind, int prec, const char* a, const char* b, F f, in
   if (n_rhs <= 0 || max_v3 <= 0) return hipSuccess;
   if (kind == 2) {
     const dim3 grid((unsigned)((max_v3 + kRedBlock - 1) / kRedBlock), (unsigned)n_rhs);
+    if constexpr (std::is_same_v<F, FlatFields>) {
+      site_norm_kernel<NatLoad><<<grid, kRedBlock, 0, s>>>(a, f, out);
+      return hipGetLastError();
+    }
     switch (prec) {
-      case -1: site_norm_kernel<NatLoad><<<grid, kRedBlock, 0, s>>>(a, f, out); break;
       case F64: site_norm_kernel<PackedLoad<F64>><<<grid, kRedBlock, 0, s>>>(a, f, out); break;
       case F32: site_norm_kernel<PackedLoad<F32>><<<grid, kRedBlock, 0, s>>>(a, f, out); break;
       case F16S: site_norm_kernel<PackedLoad<F16S>><<<grid, kRedBlock, 0, s>>>(a, f, out); break;
@@ -437,19 +498,25 @@ hipError_t reduce_with(int kind, int prec, const char* a, const char* b, F f, in
     }
     return hipGetLastError();
   }
-  const int nb = (int)((max_v3 + kRedSitesPerBlock - 1) / kRedSitesPerBlock);
+  const int spb = red_sites_per_block(n_rhs, max_v3);
+  const int nb = (int)((max_v3 + spb - 1) / spb);
   const dim3 grid((unsigned)nb, (unsigned)n_rhs);
-  switch (prec) {
-    case -1: reduce_partial_kernel<NatLoad><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, partials); break;
-    case F64: reduce_partial_kernel<PackedLoad<F64>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, partials); break;
-    case F32: reduce_partial_kernel<PackedLoad<F32>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, partials); break;
-    case F16S: reduce_partial_kernel<PackedLoad<F16S>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, partials); break;
-    case BF16: reduce_partial_kernel<PackedLoad<BF16>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, partials); break;
-    default: return hipErrorInvalidValue;
+  if constexpr (std::is_same_v<F, FlatFields>) {   // natural fields
+    const v2d *x = reinterpret_cast<const v2d*>(a), *y = reinterpret_cast<const v2d*>(b);
+    if (kind == 1) reduce_flat_kernel<true><<<grid, kRedBlock, 0, s>>>(x, y, f.n, spb, partials);
+    else reduce_flat_kernel<false><<<grid, kRedBlock, 0, s>>>(x, nullptr, f.n, spb, partials);
+  } else {
+    switch (prec) {
+      case F64: reduce_partial_kernel<PackedLoad<F64>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, spb, partials); break;
+      case F32: reduce_partial_kernel<PackedLoad<F32>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, spb, partials); break;
+      case F16S: reduce_partial_kernel<PackedLoad<F16S>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, spb, partials); break;
+      case BF16: reduce_partial_kernel<PackedLoad<BF16>><<<grid, kRedBlock, 0, s>>>(kind, a, b, f, spb, partials); break;
+      default: return hipErrorInvalidValue;
+    }
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  reduce_finish_kernel<<<(n_rhs + 63) / 64, 64, 0, s>>>(kind, partials, nb, n_rhs, out);
+  reduce_finish_kernel<<<n_rhs, 64, 0, s>>>(kind, partials, nb, out);
   return hipGetLastError();
 }
 

@@ -1785,17 +1785,10 @@ int tl_reduce(tl_ctx* c, int kind, int64_t n_sites, int n_rhs, const void* psi, 
     TL_TRY(check_reduce_args(c, kind, n_sites, n_rhs, psi, phi, out));
     TL_TRY(need_device(c));
     TL_ON_DEVICE(c);
-    std::vector<tl::RedField> rf(n_rhs);
-    for (int r = 0; r < n_rhs; r++) rf[r] = {(int64_t)r * n_sites * 3, (int64_t)r * n_sites * 3, n_sites, 0, (int64_t)r * n_sites};
-    const size_t fbytes = align256(rf.size() * sizeof(tl::RedField));
-    const size_t pbytes = (size_t)tl::red_partials_doubles(n_rhs, n_sites) * sizeof(double);
     char* s = nullptr;
-    TL_TRY(ctx_scratch(c, fbytes + pbytes, &s));
-    TL_TRY(upload(c, s, rf.data(), rf.size() * sizeof(tl::RedField)));
-    // a = psi, b = phi: <phi, psi>
-    return launch(c, "reduction", [&] { return tl::launch_reduce(kind, -1, static_cast<const char*>(psi), static_cast<const char*>(phi),
-                                          reinterpret_cast<const tl::RedField*>(s), n_rhs, n_sites,
-                                          reinterpret_cast<double*>(s + fbytes), out, c->stream); });
+    if (kind != TL_SITE_NORM) TL_TRY(ctx_scratch(c, (size_t)tl::red_partials_doubles(n_rhs, n_sites) * sizeof(double), &s));
+    // psi, phi: <phi, psi>
+    return launch(c, "reduction", [&] { return tl::launch_reduce_flat(kind, psi, phi, n_sites, n_rhs, reinterpret_cast<double*>(s), out, c->stream); });
   } catch (...) {
     return host_failure(c);
   }

@@ -1,4 +1,5 @@
-"""The Laplacian as one launch on natural fields."""
+"""The Laplacian as one launch on natural fields, and the FP64 reductions at the sizes where the
+number of blocks per field changes."""
 import numpy as np
 import pytest
 
@@ -54,3 +55,25 @@ def test_laplacian(ctx, orc, torch, prec, L):
     plan.close()
     if not prec.startswith("f16s"):     # an F16S scale may change when a rounded site is rounded again
         assert torch.equal(again, out)
+
+
+# 2048 blocks of 4096 down to 512 sites: block counts on both sides of every halving
+@pytest.mark.parametrize("n_rhs,n_sites", [(1, 1), (3, 511), (2, 513), (5, 4095), (7, 4097), (1, 100003),
+                                           (12, 110592), (31, 66 * 4096), (33, 62 * 4096 + 1)])
+def test_reductions(ctx, torch, n_rhs, n_sites):
+    g = torch.Generator(device="cuda").manual_seed(7710 + n_rhs)
+    psi = torch.randn((n_rhs, n_sites, 3), dtype=torch.complex128, device="cuda", generator=g)
+    phi = torch.randn((n_rhs, n_sites, 3), dtype=torch.complex128, device="cuda", generator=g)
+    norm, dot, site = ctx.reduce("norm2", psi), ctx.reduce("dot", psi, phi), ctx.reduce("site_norm", psi)
+    sq = psi.real ** 2 + psi.imag ** 2
+    want_n, want_d = sq.sum((1, 2)), (phi.conj() * psi).sum((1, 2))
+    # rounding of a sum of N terms in any tree or chain order: below N u times the sum of their sizes;
+    # u = 2^-53, and both sides carry it
+    u = 2.0 ** -53
+    assert ((norm - want_n).abs() <= 2 * 6 * n_sites * u * want_n).all()
+    size = (phi.abs() * psi.abs()).sum((1, 2))
+    assert ((dot - want_d).abs() <= 2 * 12 * n_sites * u * size).all()
+    assert torch.allclose(site, sq.sum(-1).sqrt(), rtol=8 * u, atol=0)
+    for kind, a, b in (("norm2", norm, None), ("dot", dot, phi)):    # the same bits every time, and without allocation
+        assert torch.equal(ctx.reduce(kind, psi, b), a)
+        assert torch.equal(ctx.reduce_noalloc(kind, psi, b), a)
