@@ -286,6 +286,11 @@ hipError_t launch_reduce_flat(int kind, const void* psi, const void* phi, int64_
 // sum of planes 0 .. n_in - 1.  kinds bit 0: nontemporal loads, bit 1: nontemporal stores.
 hipError_t launch_stream(void* buf, int64_t n_words, int n_in, int kinds, int grid, hipStream_t stream);
 
+// dst[0 .. bytes) = src (host), bytes a multiple of 4 up to kUploadArgs: the data travels in the
+// launch's arguments.
+constexpr size_t kUploadArgs = 3072;
+hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t stream);
+
 // flag[0] = 1 if the n_bytes at a and b differ anywhere (flag must be cleared by the caller).
 hipError_t launch_compare(const char* a, const char* b, int64_t n_bytes, int* flag, hipStream_t stream);
 

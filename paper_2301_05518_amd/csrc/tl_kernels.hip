@@ -3,8 +3,11 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+#include <cstring>
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 #include "tl_format.h"
 #include "tl_internal.h"
@@ -362,6 +365,13 @@ __global__ __launch_bounds__(256) void stream_kernel(const v4f* __restrict__ in,
   }
 }
 
+struct UploadArgs {
+  uint32_t w[kUploadArgs / 4];
+};
+__global__ void upload_kernel(UploadArgs a, uint32_t* __restrict__ dst, int n) {
+  for (int i = threadIdx.x; i < n; i += blockDim.x) dst[i] = a.w[i];
+}
+
 __global__ void compare_kernel(const uint4* __restrict__ a, const uint4* __restrict__ b, int64_t n16,
                                const unsigned char* __restrict__ ta, const unsigned char* __restrict__ tb,
                                int64_t ntail, int* __restrict__ flag) {
@@ -572,6 +582,14 @@ hipError_t launch_stream(void* buf, int64_t n_words, int n_in, int kinds, int gr
     case 2: stream_kernel<false, true><<<grid, 256, 0, s>>>(in, n_in, out, n_words); break;
     default: stream_kernel<true, true><<<grid, 256, 0, s>>>(in, n_in, out, n_words); break;
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_upload(void* dst, const void* src, size_t bytes, hipStream_t s) {
+  if (bytes % 4 || bytes > kUploadArgs) return hipErrorInvalidValue;
+  UploadArgs a;
+  std::memcpy(a.w, src, bytes);
+  upload_kernel<<<1, 256, 0, s>>>(a, static_cast<uint32_t*>(dst), (int)(bytes / 4));
   return hipGetLastError();
 }
 

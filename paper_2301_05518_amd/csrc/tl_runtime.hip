@@ -39,6 +39,14 @@ struct Tuned {
   StepConfig single{-1, 0, 0, 0, 0, 0, 0};
 };
 
+// What whole-run launches of one plan share: control block and exchange scratch.  Their tags only
+// grow, so a pair is never cleared again, and never separated.
+struct RunMem {
+  tl::RunCtl* ctl = nullptr;
+  char* scratch = nullptr;
+  size_t bytes = 0;   // of scratch
+};
+
 struct tl_ctx {
   int device = -1;
   hipStream_t stream = nullptr;
@@ -51,6 +59,14 @@ struct tl_ctx {
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
+  // device memory of destroyed plans, kept for the next ones (see mem_get)
+  struct MemBlock {
+    void* p;
+    size_t bytes;
+  };
+  std::vector<MemBlock> pool;
+  size_t pool_bytes = 0;
+  std::vector<RunMem> run_pool;
   uint32_t* run_fail = nullptr;   // pinned host word a whole-run kernel sets when a wait between workgroups ran out
   double* noalloc = nullptr;  // this device's fixed partial-sum area of tl_reduce_noalloc
   std::string noalloc_err;    // why it is missing (lookup failed at tl_create)
@@ -161,6 +177,44 @@ int dev_alloc(tl_ctx* c, void** p, size_t bytes) {
   return TL_OK;
 }
 
+// Plan memory.  A block given back serves a later plan of the same context without a wait: all
+// work on it is queued on the context's stream (a new stream waits for the old one).  At most
+// kPoolBlocks blocks and kPoolBytes in all are kept, none over twice the size asked for is
+// handed out, and tl_destroy frees them.
+constexpr size_t kPoolBlocks = 12, kPoolBytes = size_t(256) << 20;
+
+int mem_get(tl_ctx* c, void** p, size_t* bytes) {
+  *bytes = std::max<size_t>((*bytes + 4095) / 4096 * 4096, 4096);
+  size_t best = c->pool.size();
+  if (!c->fault_alloc)
+    for (size_t i = 0; i < c->pool.size(); i++)
+      if (c->pool[i].bytes >= *bytes && c->pool[i].bytes <= 2 * *bytes &&
+          (best == c->pool.size() || c->pool[i].bytes < c->pool[best].bytes))
+        best = i;
+  if (best < c->pool.size()) {
+    *p = c->pool[best].p;
+    *bytes = c->pool[best].bytes;
+    c->pool_bytes -= *bytes;
+    c->pool.erase(c->pool.begin() + (std::ptrdiff_t)best);
+    return TL_OK;
+  }
+  return dev_alloc(c, p, *bytes);
+}
+
+void mem_put(tl_ctx* c, void* p, size_t bytes) {
+  if (!p) return;
+  if (c->pool.size() < kPoolBlocks && c->pool_bytes + bytes <= kPoolBytes) {
+    try {
+      c->pool.push_back({p, bytes});
+      c->pool_bytes += bytes;
+      return;
+    } catch (...) {   // no host memory for the list: free the block
+    }
+  }
+  (void)hipStreamSynchronize(c->stream);
+  (void)hipFree(p);
+}
+
 // Queue one library launch; TL_FAULT=launch makes it fail before anything is queued.
 template <class F>
 int launch(tl_ctx* c, const char* what, F&& f) {
@@ -195,9 +249,14 @@ int run_check(tl_ctx* c) {
   return fail(c, TL_ERR_HIP, "a whole-run smearing launch gave up waiting for another workgroup");
 }
 
-// Synchronous upload of a small host table onto the context stream.
+// Upload of a host table onto the context stream.  A small one travels in a kernel's arguments,
+// which are copied when the launch is queued, so nothing has to wait for it.
 int upload(tl_ctx* c, void* dst, const void* src, size_t bytes) {
   if (bytes == 0) return TL_OK;
+  if (bytes <= tl::kUploadArgs && bytes % 4 == 0 && !c->fault_launch) {
+    HIP_TRY(c, tl::launch_upload(dst, src, bytes, c->stream));
+    return TL_OK;
+  }
   HIP_TRY(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   return TL_OK;
@@ -374,11 +433,12 @@ struct tl_plan {
   int width = 1;
 
   size_t buf_bytes = 0;
+  size_t buf_cap[2] = {0, 0}, tables_cap = 0;   // bytes of the blocks behind buf and tables
   char* buf[2] = {nullptr, nullptr};
   int cur = 0;
 
-  // device tables: the step groups of both tilings (group_cap entries each), per-job pack
-  // offsets, reduction fields, partials
+  // device tables: the step groups of both tilings (group_cap entries each), whole-run units,
+  // per-job pack offsets, reduction fields, partials
   char* tables = nullptr;
   size_t group_cap = 0;
   int64_t* packoff_dev = nullptr;
@@ -399,11 +459,8 @@ struct tl_plan {
   Tiling tile;                          // the step tiling
   Tiling single;                        // when tile runs two steps per launch: the one-step
                                         // tiling of the last step of an odd count
-  // whole-run launches: units table, control block, exchange scratch (allocated when first used)
-  tl::RunUnit* run_units = nullptr;
-  tl::RunCtl* run_ctl = nullptr;
-  char* run_scratch = nullptr;
-  size_t run_scratch_bytes = 0;
+  tl::RunUnit* run_units = nullptr;     // whole-run launches: units table (in tables)
+  RunMem run;                           // and their shared memory (taken when first used)
   bool ready = false;                   // tuning done (or not requested) and tables uploaded
 
   hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -637,6 +694,7 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
   tl_ctx* c = p->ctx;
   RunShape r;
   const char* why = make_run(p, cfg, &r);
+  if (!why && !c->big_lds) why = "tiling needs more LDS than this device allows";
   if (why) return fail(c, TL_ERR_UNSUPPORTED, "%s", why);
   if (!c->run_fail) {
     if (c->fault_alloc) return fail(c, TL_ERR_NOMEM, "host allocation failed (TL_FAULT=alloc)");
@@ -648,23 +706,34 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
     c->run_fail = static_cast<uint32_t*>(h);
     *c->run_fail = 0;
   }
-  if (!p->run_ctl) {
-    const size_t ub = align256(p->res.size() * 8 * sizeof(tl::RunUnit));
-    void* m = nullptr;
-    TL_TRY(dev_alloc(c, &m, align256(sizeof(tl::RunCtl)) + ub));
-    p->run_ctl = static_cast<tl::RunCtl*>(m);
-    p->run_units = reinterpret_cast<tl::RunUnit*>(static_cast<char*>(m) + align256(sizeof(tl::RunCtl)));
-    HIP_TRY(c, hipMemsetAsync(m, 0, sizeof(tl::RunCtl), c->stream));
+  if (!p->run.ctl) {
+    // a pair whose scratch is large enough, else any (its scratch is replaced below)
+    auto it = c->run_pool.end();
+    for (auto k = c->run_pool.begin(); k != c->run_pool.end(); ++k)
+      if (it == c->run_pool.end() || (it->bytes < r.scratch && k->bytes > it->bytes) ||
+          (k->bytes >= r.scratch && k->bytes < it->bytes))
+        it = k;
+    if (it != c->run_pool.end() && !c->fault_alloc) {
+      p->run = *it;
+      c->run_pool.erase(it);
+    } else {
+      void* m = nullptr;
+      TL_TRY(dev_alloc(c, &m, sizeof(tl::RunCtl)));
+      p->run.ctl = static_cast<tl::RunCtl*>(m);
+      HIP_TRY(c, hipMemsetAsync(m, 0, sizeof(tl::RunCtl), c->stream));
+    }
   }
-  if (r.scratch > p->run_scratch_bytes) {
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    if (p->run_scratch) (void)hipFree(p->run_scratch);
-    p->run_scratch = nullptr;
-    p->run_scratch_bytes = 0;
+  if (r.scratch > p->run.bytes) {
+    if (p->run.scratch) {
+      HIP_TRY(c, hipStreamSynchronize(c->stream));
+      (void)hipFree(p->run.scratch);
+    }
+    p->run.scratch = nullptr;
+    p->run.bytes = 0;
     void* m = nullptr;
     TL_TRY(dev_alloc(c, &m, r.scratch));
-    p->run_scratch = static_cast<char*>(m);
-    p->run_scratch_bytes = r.scratch;
+    p->run.scratch = static_cast<char*>(m);
+    p->run.bytes = r.scratch;
     HIP_TRY(c, hipMemsetAsync(m, 0, r.scratch, c->stream));
   }
   TL_TRY(upload(c, p->run_units, r.units.data(), r.units.size() * sizeof(tl::RunUnit)));
@@ -677,22 +746,27 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
   return TL_OK;
 }
 
-// Build cfg's work list and upload it into tiling t's device table.
-int upload_tiling(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
+// Tiling t's host side for a step configuration: its work list and launch numbers.
+int describe_tiling(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
   const char* why = nullptr;
   if (!tiling_applies(p, cfg, &why)) return fail(p->ctx, TL_ERR_UNSUPPORTED, "%s", why);
-  if (cfg.variant == 9) return upload_run(p, cfg, t);
   std::vector<StepGroup> gs;
   (void)make_groups(p, cfg, &gs);
   if (gs.size() > p->group_cap)   // the device table holds one entry per RHS at most
     return fail(p->ctx, TL_ERR_UNSUPPORTED, "work list of %zu groups exceeds the table (%zu)", gs.size(), p->group_cap);
-  TL_TRY(upload(p->ctx, t->dev, gs.data(), gs.size() * sizeof(StepGroup)));
   t->cfg = cfg;
   t->cfg.rows64 = std::all_of(gs.begin(), gs.end(), [](const StepGroup& g) { return g.Lx == 64; }) ? 1 : 0;
   t->lds = plan_lds(p, cfg, gs);
-  t->host = gs;
   t->n_tiles = gs.empty() ? 0 : gs.back().tile_begin + gs.back().n_xy_tiles * gs.back().n_z_tiles;
+  t->host = std::move(gs);
   return TL_OK;
+}
+
+// Build cfg's work list and upload it into tiling t's device table.
+int upload_tiling(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
+  if (cfg.variant == 9) return upload_run(p, cfg, t);
+  TL_TRY(describe_tiling(p, cfg, t));
+  return upload(p->ctx, t->dev, t->host.data(), t->host.size() * sizeof(StepGroup));
 }
 
 // The plan's tilings from a tuned pair.
@@ -711,8 +785,8 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
   if (t.cfg.variant == 9) {
     tl::RunArgs a{};
     a.units = p->run_units;
-    a.ctl = p->run_ctl;
-    a.scratch = p->run_scratch;
+    a.ctl = p->run.ctl;
+    a.scratch = p->run.scratch;
     a.fail = c->run_fail;
     a.in = in;
     a.out = out;
@@ -1034,13 +1108,50 @@ bool tile_override(Tuned* tu) {
   return e && parse_tuned(e, 4, tu);
 }
 
+// The tiling of a plan that is neither tuned nor fixed: all steps in one launch where the cells
+// fit teams of one XCD (up to 32 workgroups) or a few, else the direct kernel, one step per
+// launch.  A launch costs about 5 us, the whole-run kernel 1 to 4 us a step plus about 10, so it
+// wins from four steps on (20 steps of 16^3 FP32: 30 instead of 320 us).  Team size: every unit
+// at once if the chip has room, a wave or more of sites per tile; FP64 threads hold one RHS
+// where that fits (its registers are full with one).
+bool default_run(const tl_plan* p, StepConfig* cfg) {
+  if ((p->flags & (TL_PLAIN | TL_ONE_STEP)) || p->n_steps < kRunMinSteps || !p->ctx->big_lds) return false;
+  int64_t units = 0, sites = 1;
+  for (const auto& gr : p->groups) {
+    const tl_geom& g = p->jobs[gr.job].job.g;
+    int64_t cell = 1, cells = 1;
+    for (int d = 0; d < 3; d++) {
+      const int ch = (tl::hop_of(p->prec) == 2 && !(g.L[d] & 1)) ? 2 : 1;
+      cells *= ch;
+      cell *= g.L[d] / ch;
+    }
+    units += cells;
+    sites = std::max(sites, cell);
+  }
+  int team = 1;
+  while (team < 32 && 2 * team * units <= std::max(p->ctx->n_cu, 8) && sites / (2 * team) >= 64) team *= 2;
+  RunShape r;
+  for (; team <= 256; team *= 2)
+    for (int split : {1, 0})
+      if (split == (tl::vprec(p->prec) == tl::F64 && p->width > 1) || (!split && tl::vprec(p->prec) == tl::F64)) {
+        *cfg = {9, 512, team, 0, 0, split, 0};
+        if (!make_run(p, *cfg, &r)) return true;
+      }
+  return false;
+}
+
 int plan_prepare(tl_plan* p) {
   if (p->ready) return TL_OK;
   Tuned forced;
+  StepConfig run{};
   if (tile_override(&forced)) {
     TL_TRY(upload_tuned(p, forced));
   } else if ((p->flags & TL_AUTOTUNE) && p->n_steps > 0) {
     TL_TRY(plan_autotune(p));
+  } else if (default_run(p, &run)) {
+    TL_TRY(upload_tiling(p, run, &p->tile));
+  } else {
+    TL_TRY(upload_tiling(p, p->tile.cfg, &p->tile));
   }
   p->ready = true;
   return TL_OK;
@@ -1070,18 +1181,40 @@ int plan_capture(tl_plan* p, int parity) {
   return rc;
 }
 
+void run_free(RunMem& m) {
+  if (m.ctl) (void)hipFree(m.ctl);
+  if (m.scratch) (void)hipFree(m.scratch);
+  m = RunMem{};
+}
+
+// Keeps a plan's whole-run memory for a later plan: at most four pairs, 256 MB of scratch in all.
+void run_put(tl_ctx* c, RunMem m) {
+  size_t held = m.bytes;
+  for (const auto& k : c->run_pool) held += k.bytes;
+  if (c->run_pool.size() < 4 && held <= kPoolBytes) {
+    try {
+      c->run_pool.push_back(m);
+      return;
+    } catch (...) {
+    }
+  }
+  (void)hipStreamSynchronize(c->stream);
+  run_free(m);
+}
+
 void plan_free(tl_plan* p) {
   if (!p) return;
   if (p->ctx && p->ctx->device >= 0) {
     DeviceGuard dg(p->ctx->device);
-    (void)hipStreamSynchronize(p->ctx->stream);
+    tl_ctx* c = p->ctx;
+    // On the null stream, which orders the caller's own frees and allocations after the queued
+    // work, nothing waits; on another stream the call waits, so that the jobs' fields may go.
+    if (c->stream || p->graph[0] || p->graph[1]) (void)hipStreamSynchronize(c->stream);
     for (auto& g : p->graph)
       if (g) (void)hipGraphExecDestroy(g);
-    for (auto& b : p->buf)
-      if (b) (void)hipFree(b);
-    if (p->tables) (void)hipFree(p->tables);
-    if (p->run_ctl) (void)hipFree(p->run_ctl);
-    if (p->run_scratch) (void)hipFree(p->run_scratch);
+    for (int k = 0; k < 2; k++) mem_put(c, p->buf[k], p->buf_cap[k]);
+    mem_put(c, p->tables, p->tables_cap);
+    if (p->run.ctl) run_put(c, p->run);
   }
   delete p;
 }
@@ -1175,6 +1308,8 @@ int tl_destroy(tl_ctx* c) {
       DeviceGuard dg(c->device);   // teardown goes on even if the switch fails
       (void)hipStreamSynchronize(c->stream);
       if (c->scratch) (void)hipFree(c->scratch);
+      for (auto& b : c->pool) (void)hipFree(b.p);
+      for (auto& m : c->run_pool) run_free(m);
       if (c->run_fail) (void)hipHostFree(c->run_fail);
     }
     delete c;
@@ -1325,8 +1460,14 @@ int tl_laplacian(tl_ctx* c, const tl_geom* g, const void* W, const int32_t* w_sl
   }
 }
 
-int tl_plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigma, int prec, unsigned flags,
-                   tl_plan** out) {
+}  // extern "C"
+
+namespace {
+
+// tl_plan_create; clear: the resident buffers start as zeros (a plan that is loaded before it
+// runs does not need that).
+int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigma, int prec, unsigned flags,
+                bool clear, tl_plan** out) {
   try {
     if (!c) return TL_ERR_ARG;
     if (!out) return fail(c, TL_ERR_ARG, "out is NULL");
@@ -1415,53 +1556,60 @@ int tl_plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, doubl
     int rc = TL_OK;
     for (int k = 0; k < 2 && rc == TL_OK; k++) {
       void* b = nullptr;
-      rc = dev_alloc(c, &b, p->buf_bytes);
-      p->buf[k] = static_cast<char*>(b);
+      size_t bytes = p->buf_bytes;
+      rc = mem_get(c, &b, &bytes);
+      if (rc == TL_OK) {
+        p->buf[k] = static_cast<char*>(b);
+        p->buf_cap[k] = bytes;
+      }
     }
     const size_t n_res = p->res.size();
     // two tilings' step groups: a tiling may split the plan's groups down to one RHS each
     p->group_cap = n_res;
     const size_t gbytes = 2 * align256(n_res * sizeof(StepGroup));
+    const size_t ubytes = align256(n_res * 8 * sizeof(tl::RunUnit));
     const size_t obytes = align256(n_res * sizeof(int64_t));
     const size_t rbytes = align256(n_res * sizeof(tl::RedField));
     const size_t pbytes = align256((size_t)tl::red_partials_doubles((int)n_res, p->max_v3) * sizeof(double));
     if (rc == TL_OK) {
       void* t = nullptr;
-      rc = dev_alloc(c, &t, gbytes + obytes + rbytes + pbytes);
-      p->tables = static_cast<char*>(t);
+      size_t bytes = gbytes + ubytes + obytes + rbytes + pbytes;
+      rc = mem_get(c, &t, &bytes);
+      if (rc == TL_OK) {
+        p->tables = static_cast<char*>(t);
+        p->tables_cap = bytes;
+      }
     }
     if (rc == TL_OK) {
       p->tile.dev = reinterpret_cast<StepGroup*>(p->tables);
       p->single.dev = reinterpret_cast<StepGroup*>(p->tables + gbytes / 2);
-      p->packoff_dev = reinterpret_cast<int64_t*>(p->tables + gbytes);
-      p->red_dev = reinterpret_cast<tl::RedField*>(p->tables + gbytes + obytes);
-      p->partials = reinterpret_cast<double*>(p->tables + gbytes + obytes + rbytes);
-      std::vector<int64_t> po;
-      std::vector<tl::RedField> rf;
+      p->run_units = reinterpret_cast<tl::RunUnit*>(p->tables + gbytes);
+      p->packoff_dev = reinterpret_cast<int64_t*>(p->tables + gbytes + ubytes);
+      p->red_dev = reinterpret_cast<tl::RedField*>(p->tables + gbytes + ubytes + obytes);
+      p->partials = reinterpret_cast<double*>(p->tables + gbytes + ubytes + obytes + rbytes);
+      // pack offsets and reduction fields: neighbours in the tables, one upload
+      std::vector<char> host(obytes + rbytes, 0);
+      int64_t* po = reinterpret_cast<int64_t*>(host.data());
+      tl::RedField* rf = reinterpret_cast<tl::RedField*>(host.data() + obytes);
+      int64_t k = 0, oo = 0;
       for (auto& jc : p->jobs) {
-        p->packoff_first.push_back((int64_t)po.size());
-        for (int r = 0; r < jc.job.n_rhs; r++) po.push_back(p->res[jc.res_index[r]].off);
-      }
-      for (auto& jc : p->jobs)
-        for (int r = 0; r < jc.job.n_rhs; r++) {
+        p->packoff_first.push_back(k);
+        for (int r = 0; r < jc.job.n_rhs; r++, k++) {
           const int64_t o = p->res[jc.res_index[r]].off;
-          rf.push_back({o, o, jc.V3, jc.Vp, 0});
+          po[k] = o;
+          rf[k] = {o, o, jc.V3, jc.Vp, oo};
+          oo += jc.V3;
         }
-      int64_t oo = 0;
-      for (auto& f : rf) {
-        f.out_off = oo;
-        oo += f.V3;
       }
-      rc = upload(c, p->packoff_dev, po.data(), po.size() * sizeof(int64_t));
-      if (rc == TL_OK) rc = upload(c, p->red_dev, rf.data(), rf.size() * sizeof(tl::RedField));
+      rc = upload(c, p->packoff_dev, host.data(), host.size());
     }
-    if (rc == TL_OK) {
+    if (rc == TL_OK && clear) {
       // zero the resident buffers so tuning runs never see stale bit patterns
       for (int k = 0; k < 2 && rc == TL_OK; k++)
         if (hipMemsetAsync(p->buf[k], 0, p->buf_bytes, c->stream) != hipSuccess)
           rc = fail(c, TL_ERR_HIP, "hipMemsetAsync failed");
     }
-    if (rc == TL_OK) rc = upload_tiling(p, p->tile.cfg, &p->tile);
+    if (rc == TL_OK) rc = describe_tiling(p, p->tile.cfg, &p->tile);   // uploaded by the first run
     if (rc != TL_OK) return rc;
     // info
     tl_plan_info& in = p->info;
@@ -1479,13 +1627,22 @@ int tl_plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, doubl
     in.rhs_sites = rs;
     in.bytes_per_step = bytes;
     in.flops_per_step = flops;
-    in.resident_bytes = (int64_t)(2 * p->buf_bytes + gbytes + obytes + rbytes + pbytes);
+    in.resident_bytes = (int64_t)(p->buf_cap[0] + p->buf_cap[1] + p->tables_cap);
     release.p = nullptr;
     *out = p;
     return TL_OK;
   } catch (...) {
     return host_failure(c);
   }
+}
+
+}  // namespace
+
+extern "C" {
+
+int tl_plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigma, int prec, unsigned flags,
+                   tl_plan** out) {
+  return plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, true, out);
 }
 
 int tl_plan_load(tl_plan* p) {
@@ -1512,7 +1669,8 @@ int tl_plan_run(tl_plan* p) {
     TL_ON_DEVICE(c);
     TL_TRY(run_check(c));
     TL_TRY(plan_prepare(p));
-    if ((p->flags & TL_GRAPH) && p->tile.cfg.variant != 9) {   // one launch needs no graph
+    // a tuned run that is one launch needs no graph
+    if ((p->flags & TL_GRAPH) && !(p->tile.cfg.variant == 9 && (p->flags & TL_AUTOTUNE))) {
       TL_TRY(plan_capture(p, p->cur));
       if (c->fault_launch) return fail(c, TL_ERR_HIP, "graph launch failed (TL_FAULT=launch)");
       HIP_TRY(c, hipGraphLaunch(p->graph[p->cur], c->stream));
@@ -1637,7 +1795,7 @@ int tl_plan_get_info(const tl_plan* p, tl_plan_info* info) {
   try {
     if (!p || !info) return TL_ERR_ARG;
     *info = p->info;
-    info->resident_bytes += (int64_t)p->run_scratch_bytes + (p->run_ctl ? (int64_t)sizeof(tl::RunCtl) : 0);
+    info->resident_bytes += (int64_t)p->run.bytes + (p->run.ctl ? (int64_t)sizeof(tl::RunCtl) : 0);
     const tl_plan::Tiling& t = p->tile;
     info->n_tiles = t.n_tiles;
     info->variant = t.cfg.variant;
@@ -1719,7 +1877,7 @@ int tl_smear(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigm
       }
     }
     tl_plan* p = nullptr;
-    TL_TRY(tl_plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, &p));
+    TL_TRY(plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, (flags & TL_AUTOTUNE) != 0, &p));
     int rc = tl_plan_load(p);
     if (rc == TL_OK) rc = tl_plan_run(p);
     if (rc == TL_OK) rc = tl_plan_store(p);
