@@ -543,10 +543,13 @@ int64_t plan_lds(const tl_plan* p, const StepConfig& cfg, const std::vector<Step
 // (once as the forward and once as the backward one of a site) before its first step.
 constexpr int kRunMinSteps = 4;
 
-// Cut a cell of extents c into at most `team` tiles of at most `sites` sites: the fewest waves
-// per tile (its arithmetic time), then the fewest sites to exchange, whole x rows where that
-// costs nothing (their x hops need no exchange).  Returns the tile count, 0 if none fits.
-int cut_cell(const int32_t c[3], int sites, int team, int32_t b[3], int32_t t[3], int* halo) {
+// Cut a cell of extents c into at most `team` tiles of at most `sites` sites that a workgroup of
+// `subs` thread sets can hold.  First the fewest waves per SIMD (a phase's arithmetic time), then
+// the cheapest exchange: sites read from other tiles, and eight times the 128-byte lines they lie
+// in (across x every site has its own: 64^3 FP32 24 RHS takes 52 us per step in tiles of 32x4x4
+// and 62 in 8x8x8, which read fewer sites).  Returns the tile count, 0 if none fits.
+int cut_cell(const int32_t c[3], int prec, int width, int subs, int sites, int team, int32_t b[3], int32_t t[3],
+             int* halo) {
   int best = 0;
   int64_t best_cost = 0;
   for (int tx = 1; tx <= c[0] && tx <= team; tx++) {
@@ -558,8 +561,14 @@ int cut_cell(const int32_t c[3], int sites, int team, int32_t b[3], int32_t t[3]
       for (int tz = 1; tz <= c[2] && tx * ty * tz <= team; tz++) {
         const int bz = (c[2] + tz - 1) / tz;
         if ((c[2] + bz - 1) / bz != tz || (int64_t)bx * by * bz > sites) continue;
-        const int h = 2 * ((tx > 1 ? by * bz : 0) + (ty > 1 ? bx * bz : 0) + (tz > 1 ? bx * by : 0));
-        const int64_t cost = ((int64_t)((bx * by * bz + 63) / 64) << 32) + ((int64_t)h << 1) + (tx > 1 ? 1 : 0);
+        const int np = (bx * by * bz + 63) / 64 * 64;
+        const int fx = tx > 1 ? by * bz : 0, fy = ty > 1 ? bx * bz : 0, fz = tz > 1 ? bx * by : 0;
+        const int h = 2 * (fx + fy + fz);
+        const int lines = 2 * (fx + (fy ? bz * ((bx + 7) / 8) : 0) + (fz + 7) / 8);
+        if (subs * h > 64 * tl::kFetch * ((tl::run_max_threads(prec) - np * subs) / 64) ||
+            tl::run_lds(prec, width, subs, np, h) > 160 * 1024)
+          continue;
+        const int64_t cost = ((int64_t)((np / 64 * subs + 3) / 4) << 32) + h + 8 * lines;
         if (best && cost >= best_cost) continue;
         best = tx * ty * tz;
         best_cost = cost;
@@ -610,7 +619,7 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
       std::copy(r.units.back().t, r.units.back().t + 3, u.t);
       n = u.t[0] * u.t[1] * u.t[2];
     } else {
-      n = cut_cell(u.c, sites, cfg.tz, u.b, u.t, &h);
+      n = cut_cell(u.c, prec, r.cfg.width, r.subs, sites, cfg.tz, u.b, u.t, &h);
       if (n == 0) return "a cell does not fit a team of workgroups";
       r.np = std::max(r.np, (u.b[0] * u.b[1] * u.b[2] + 63) / 64 * 64);
       halo = std::max(halo, h);
