@@ -151,19 +151,20 @@ struct RunUnit {
   int32_t c[3];           // cell extents
   int32_t b[3];           // tile extents
   int32_t t[3];           // tiles per direction
+  int32_t shape;          // equal for units with equal c, b and t
 };
 
 // A team's meeting point, and the launch's control block (device memory, zeroed once; each
 // launch leaves it ready for the next and advances the epoch).
 struct alignas(128) RunTeam {
-  uint64_t mail;          // (sequence number << 32) | unit
+  uint64_t mail;          // (number of the take << 32) | share
   uint32_t enrolled, size, arrived;
 };
 constexpr int kMaxRunTeams = 1024;
 constexpr int kMaxRunGrid = 8192;
 struct RunCtl {
   alignas(128) uint32_t epoch;
-  alignas(128) uint32_t next_unit;
+  alignas(128) uint32_t next_share;
   alignas(128) uint32_t finished;
   RunTeam team[kMaxRunTeams];
   uint32_t xcc[kMaxRunGrid];   // [team][rank]: the XCD of each workgroup
@@ -176,7 +177,7 @@ struct RunArgs {
   uint32_t* fail;         // host-visible: set when a wait ran out
   const char* in;
   char* out;
-  int32_t n_units, n_steps, n_teams, team_size;
+  int32_t n_units, n_shares, n_steps, n_teams, team_size;
   int32_t np;             // threads per RHS subset (a tile's sites, rounded up to waves)
   int32_t subs;           // RHS subsets of a group on separate threads
   int32_t halo;           // LDS entries of a tile's halo (at least the sites it reads from other tiles)
@@ -198,7 +199,8 @@ constexpr int kFetch = 4;   // halo entries a fetch thread takes per phase at mo
 
 // 16-byte exchange words of a colour vector per precision.
 constexpr int kRunWords[4] = {4, 2, 2, 1};
-constexpr int kRunMsgBytes = 16;   // LDS in front of the vectors
+constexpr int kRunMaxTeam = 256;                  // workgroups of a team at most
+constexpr int kRunMsgBytes = 16 + kRunMaxTeam;    // LDS in front of the vectors
 
 // LDS bytes of a site's `width` vectors, and the dynamic LDS bytes of a whole-run launch: per RHS
 // subset two generations of np vectors and the halo (two generations of it where a thread has one

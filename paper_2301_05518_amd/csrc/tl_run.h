@@ -31,7 +31,8 @@
 // that run: each enrols when it starts, the first one closes the team when all expected
 // members have come or after about 200 us, later ones leave.  A team that is smaller than
 // the unit's tile count runs the same exchange with several tiles per workgroup and the
-// two-links read from memory each step (run_slow).  Teams take units from a common counter.
+// two-links read from memory each step (run_slow).  Teams take their shares of the units from
+// a common counter.
 // Every wait is bounded; one that runs out sets *fail and the kernel ends.
 #pragma once
 
@@ -413,9 +414,9 @@ struct RunExch {
 // step loop these waves wait for LDS and the barrier only: loads in their own instruction
 // stream would make every wait for a halo word wait for their stores as well.
 template <int P, int R, bool CUT>
-__device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile, int team,
-                                            bool full, unsigned char* lds, typename Fmt<P>::real alpha,
-                                            typename Fmt<P>::real beta) {
+__device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile,
+                                            const uint8_t* xcc, bool full, unsigned char* lds,
+                                            typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
   using real = typename Fmt<P>::real;
   using X = Exch<P>;
   constexpr bool kLdsW = P == F64;
@@ -451,14 +452,12 @@ __device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, 
   // (loads of the words bypass the per-CU caches), tiles on another one need a device-scope store
   bool pub = false, far = false;
   if constexpr (CUT) {
-    const uint32_t* const xcc = a.ctl->xcc + team * a.team_size;
     const int it[3] = {tile % g.t[0], tile / g.t[0] % g.t[1], tile / g.t[0] / g.t[1]};
     const int ts[3] = {1, g.t[0], g.t[0] * g.t[1]};
-    const uint32_t here = full ? ctl_load(xcc + tile) : 0;
 #pragma unroll
     for (int d = 0; d < 6; d++) {
       const int e = d / 2, n = ring(it[e] + (d % 2 ? -1 : 1), g.t[e]);
-      const bool away = !full || (fc.f[e] > 0 && ctl_load(xcc + tile + (n - it[e]) * ts[e]) != here);
+      const bool away = !full || (fc.f[e] > 0 && xcc[tile + (n - it[e]) * ts[e]] != xcc[tile]);
       if (nb[d] >= 2 * np) {
         pub = true;
         far = far || away;
@@ -644,8 +643,8 @@ __device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, co
 // One unit, one tile per workgroup: `tile` of this workgroup.
 template <int P, int R, bool CUT>
 __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
-                                               int team, bool full, unsigned char* lds, typename Fmt<P>::real alpha,
-                                               typename Fmt<P>::real beta) {
+                                               int team, const uint8_t* xcc, bool full, unsigned char* lds,
+                                               typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
   RunExch x;
   x.stride = a.team_size * a.np * 16;
   const int64_t plane = (int64_t)a.subs * R * Exch<P>::NW * x.stride;
@@ -660,15 +659,17 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
     else if (entries <= 2 * lanes) run_fetch<P, R, 2>(a, g, x, tile, lds);
     else run_fetch<P, R, kFetch>(a, g, x, tile, lds);
   } else {
-    run_compute<P, R, CUT>(a, g, x, tile, team, full, lds, alpha, beta);
+    run_compute<P, R, CUT>(a, g, x, tile, xcc, full, lds, alpha, beta);
   }
 }
 
 template <int P, int R, bool CUT>
 __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  uint32_t* const sh = reinterpret_cast<uint32_t*>(lds_raw);   // 16 bytes of messages, then the vectors
-  unsigned char* const lds = lds_raw + 16;
+  // messages between the workgroup's threads, the XCD of each member of the team, then the vectors
+  uint32_t* const sh = reinterpret_cast<uint32_t*>(lds_raw);
+  uint8_t* const xcc = lds_raw + 16;
+  unsigned char* const lds = lds_raw + kRunMsgBytes;
   const RunPlace pl = run_place(a.team_size);
   RunTeam* const tm = a.ctl->team + pl.team;
   if (threadIdx.x == 0) {
@@ -698,22 +699,36 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
   const uint32_t epoch = (uint32_t)uniform((int)sh[2]);
   const bool leader = uniform((int)sh[3]) == 0;
   const bool full = size == pl.expect;
+  if (CUT && full && me < size)
+    for (int k = (int)threadIdx.x; k < size; k += (int)blockDim.x)
+      xcc[k] = (uint8_t)ctl_load(a.ctl->xcc + pl.team * a.team_size + k);
   __syncthreads();
   if (me < size) {
-    for (uint32_t seq = 0;; seq++) {
+    uint32_t barriers = 0, seq = 0;   // team barriers passed, units run
+    // Every member has finished what came before: needed before scratch slots change their readers.
+    auto team_barrier = [&] {
+      barriers++;
+      if (size > 1 && threadIdx.x == 0) {
+        __builtin_amdgcn_s_waitcnt(0);
+        ctl_add(&tm->arrived, 1u);
+        int k = 0;
+        while (ctl_load(&tm->arrived) < barriers * (uint32_t)size && ++k < kSpinLimit) {}
+        if (k >= kSpinLimit) run_failed(a.fail);
+      }
+      __syncthreads();
+    };
+    int shape = -1;   // of the unit before, -1: a barrier has to come first
+    // A team takes shares of the units (every n_shares-th one) until none is left.
+    for (uint32_t take = 1;; take++) {
       if (threadIdx.x == 0) {
-        uint32_t u = (uint32_t)a.n_units;
+        uint32_t u = (uint32_t)a.n_shares;
         if (leader) {
-          int k = 0;
-          while (ctl_load(&tm->arrived) < seq * (uint32_t)(size - 1) && ++k < kSpinLimit) {}
-          if (k >= kSpinLimit) run_failed(a.fail);
-          else u = min(ctl_add(&a.ctl->next_unit, 1u), (uint32_t)a.n_units);
-          __hip_atomic_store(&tm->mail, (uint64_t)(seq + 1) << 32 | u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          u = min(ctl_add(&a.ctl->next_share, 1u), (uint32_t)a.n_shares);
+          if (size > 1) __hip_atomic_store(&tm->mail, (uint64_t)take << 32 | u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
-          if (seq > 0) ctl_add(&tm->arrived, 1u);
           uint64_t m = 0;
           int k = 0;
-          while (((m = __hip_atomic_load(&tm->mail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != seq + 1 &&
+          while (((m = __hip_atomic_load(&tm->mail, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) >> 32) != take &&
                  ++k < kSpinLimit) {}
           if (k >= kSpinLimit) run_failed(a.fail);
           else u = (uint32_t)m;
@@ -721,18 +736,31 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
         sh[0] = u;
       }
       __syncthreads();
-      const int u = uniform((int)sh[0]);
+      const int share = uniform((int)sh[0]);
       __syncthreads();
-      if (u >= a.n_units) break;
-      const RunUnit& g = a.units[u];
-      const int n_tiles = g.t[0] * g.t[1] * g.t[2];
-      const uint32_t pubs = seq * (uint32_t)a.n_steps;
-      if (size >= n_tiles) {
-        if (me < n_tiles) run_tile_steps<P, R, CUT>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, full, lds, alpha, beta);
-      } else if constexpr (CUT) {
-        if ((int)threadIdx.x < a.np * a.subs) run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
+      if (share >= a.n_shares) break;
+      for (int u = share; u < a.n_units; u += a.n_shares, seq++) {
+        const RunUnit& g = a.units[u];
+        const int n_tiles = g.t[0] * g.t[1] * g.t[2];
+        const bool fast = size >= n_tiles;
+        // Units of one shape follow each other without a barrier: a workgroup that starts the next
+        // one overwrites words of step n - 2, which its readers have read before they published the
+        // step n - 1 it has read; and words of step n - 1 once those readers have published the
+        // next unit's input.
+        if (seq > 0 && (!fast || g.shape != shape)) team_barrier();
+        shape = fast ? g.shape : -1;
+        const uint32_t pubs = seq * (uint32_t)a.n_steps;
+        if (fast) {
+          if (me < n_tiles)
+            run_tile_steps<P, R, CUT>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, xcc, full, lds, alpha, beta);
+        } else if constexpr (CUT) {
+          if ((int)threadIdx.x < a.np * a.subs)
+            run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
+        }
+        __syncthreads();   // LDS is free for the next unit
       }
-      __syncthreads();   // every thread has read what it waited for before the team may move on
+      shape = -1;
+      team_barrier();
     }
   }
   // the launch's last workgroup leaves the control block ready for the next launch
@@ -750,7 +778,7 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
     __hip_atomic_store(&t->mail, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (threadIdx.x == 0) {
-    ctl_store(&a.ctl->next_unit, 0);
+    ctl_store(&a.ctl->next_share, 0);
     ctl_store(&a.ctl->finished, 0);
     ctl_store(&a.ctl->epoch, epoch + (uint32_t)a.n_units * (uint32_t)a.n_steps + 1u);
   }

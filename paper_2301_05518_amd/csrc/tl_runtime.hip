@@ -617,9 +617,11 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
     if (!r.units.empty() && r.units.back().Lx == u.Lx && r.units.back().Ly == u.Ly && r.units.back().Lz == u.Lz) {
       std::copy(r.units.back().b, r.units.back().b + 3, u.b);
       std::copy(r.units.back().t, r.units.back().t + 3, u.t);
+      u.shape = r.units.back().shape;
       n = u.t[0] * u.t[1] * u.t[2];
     } else {
-      n = cut_cell(u.c, prec, r.cfg.width, r.subs, sites, cfg.tz, u.b, u.t, &h);
+      n = cut_cell(u.c, prec, r.cfg.width, r.subs, sites, std::min(cfg.tz, tl::kRunMaxTeam), u.b, u.t, &h);
+      u.shape = (int32_t)r.units.size();
       if (n == 0) return "a cell does not fit a team of workgroups";
       r.np = std::max(r.np, (u.b[0] * u.b[1] * u.b[2] + 63) / 64 * 64);
       halo = std::max(halo, h);
@@ -800,6 +802,7 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.in = in;
     a.out = out;
     a.n_units = (int32_t)t.run.units.size();
+    a.n_shares = std::min<int32_t>(a.n_units, t.run.n_teams);
     a.n_steps = p->n_steps;
     a.n_teams = t.run.n_teams;
     a.team_size = t.run.team_size;
