@@ -313,6 +313,14 @@ def tile_dict(info) -> dict:
     return {**{k: info[k] for k in TILE_KEYS}, "width": info["tile_width"]}
 
 
+FP32_PEAK_TFLOPS = 78.6   # vector FP32 (and FP64) without packed instructions: 256 CUs x 64 FMA x 2.4 GHz
+
+
+def steps_per_launch(info, n_steps: int) -> int:
+    """Steps one launch of the plan runs: the whole-run kernel (variant 9) runs all of them."""
+    return n_steps if info["variant"] == 9 else info["steps_per_launch"]
+
+
 KERNEL_NAMES = ["step_direct", "step_zmarch", "step_zring", "step_zfront", "step_rolled", "step_zlds", "step_zchain",
                 "step_zpipe", "step_fuse2", "smear_run"]
 
@@ -367,7 +375,7 @@ def measure_workload(ctx, torch, tl, dev, index, prec, plain=False, passes=5):
     step_ms = plan.time(reps=5)
     info = plan.info()
     # algorithmic bytes: those of every RHS-site-update (W, the input and the output once each)
-    spl = info["steps_per_launch"]
+    spl = steps_per_launch(info, wl.n_steps)
     launch_ms = step_ms * wl.n_steps / ((wl.n_steps + spl - 1) // spl)
     gbs = info["bytes_per_step"] / (step_ms * 1e-3) / 1e9
     rec = {"workload": wl.name, "storage": prec, "rhs": sum(len(ts) for _, _, ts in lats),
@@ -556,10 +564,12 @@ def main():
     # timed region are reported beside it.
     info = plan.info()
     # one launch runs spl steps (2: the two-step kernel, which reads W and its input once and
-    # writes only the second step's output); the algorithmic bytes are those of the RHS-site-
+    # writes only the second step's output; n: the whole-run kernel, which reads W and the
+    # sources once and writes only the last step's output, and whose limit is the rate of its
+    # vector arithmetic, given as "vector"); the algorithmic bytes are those of the RHS-site-
     # updates it performs, 120 B each at FP32 and three RHS per W load (W, the input and the
     # output once per update), so a two-step launch counts two steps' bytes against its time
-    spl = info["steps_per_launch"]
+    spl = steps_per_launch(info, wl.n_steps)
     launches = max(1, info["launches_per_step"] * ((wl.n_steps + spl - 1) // spl))
     step_ms = sum(a.elapsed_time(b) for a, b in run_events) / len(run_events) / launches
     isolated_ms = plan.time(reps=3) * wl.n_steps / launches
@@ -585,7 +595,10 @@ def main():
                 "ceiling": {k: ceiling[k] for k in ("ceiling_kinds", "step_kinds_GBs", "bytes", "mix", "configs")}}
     log(f"[bench] step kernel ({spl} step(s) per launch) {step_ms * 1e3:.1f} us per launch, "
         f"{achieved:.0f} GB/s algorithmic")
-    if spl == 2 and not args.no_extra:
+    tflops = info["flops_per_step"] * spl / (step_ms * 1e-3) / 1e12
+    roofline["vector"] = {"achieved": round(tflops, 2), "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
+                          "frac": round(tflops / FP32_PEAK_TFLOPS, 4)}
+    if spl > 1 and not args.no_extra:
         # the fastest one-step tiling on the same resident data, for comparison
         p1 = ctx.plan(jobs, wl.n_steps, wl.sigma, prec, args.flags | tl.TL_ONE_STEP)
         p1.load()

@@ -25,7 +25,9 @@
  *   keeps no pointer to them after the call returns, except that a plan
  *   (tl_plan_*) keeps the job pointers given to tl_plan_create until
  *   tl_plan_destroy.  Library-internal memory (resident packed fields,
- *   work lists, reduction partials, scratch) belongs to the context or plan.
+ *   work lists, reduction partials, scratch) belongs to the context or plan;
+ *   a context keeps up to 512 MB of its destroyed plans' memory for later
+ *   plans until tl_destroy (or until an allocation fails).
  * - "device" pointers are HIP device memory of the context's device;
  *   "host" pointers are ordinary host memory read during the call.
  * - Geometry: tl_geom.L = {Lx, Ly, Lz, Lt}, every extent in [1, 4096] and
@@ -302,7 +304,10 @@ int tl_plan_create(tl_ctx *ctx, const tl_job *jobs, int n_jobs, int n_steps, dou
 /* Pack every job's psi (complex128) into the resident buffer (rounds to the storage precision). */
 int tl_plan_load(tl_plan *plan);
 /* n_steps smearing steps on the resident buffer (eq. tlSmear applied n_steps times; with a
-   two-step tiling, n_steps / 2 launches plus one one-step launch when n_steps is odd). */
+   two-step tiling, n_steps / 2 launches plus one one-step launch when n_steps is odd; with a
+   whole-run tiling one launch, which plans of four or more steps without TL_AUTOTUNE, TL_PLAIN
+   and TL_ONE_STEP use by default where their lattices fit).  TL_ERR_HIP also reports an earlier
+   whole-run launch that failed (see tl_sync). */
 int tl_plan_run(tl_plan *plan);
 /* Unpack the resident buffer into every job's psi (complex128). */
 int tl_plan_store(tl_plan *plan);

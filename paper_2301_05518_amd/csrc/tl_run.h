@@ -29,7 +29,7 @@
 //
 // Progress.  Nothing assumes that the whole grid is resident.  A team is made of workgroups
 // that run: each enrols when it starts, the first one closes the team when all expected
-// members have come or after about 200 us, later ones leave.  A team that is smaller than
+// members have come or after about 2 ms, later ones leave.  A team that is smaller than
 // the unit's tile count runs the same exchange with several tiles per workgroup and the
 // two-links read from memory each step (run_slow).  Teams take their shares of the units from
 // a common counter.
@@ -198,7 +198,7 @@ __device__ __forceinline__ void lds_barrier() {
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 constexpr uint32_t kTeamClosed = 0x40000000u;
-constexpr int kEnrolSpins = 4000;        // about 200 us of the leader's wait for its team
+constexpr int kEnrolSpins = 4000;        // about 2 ms of the leader's wait for its team
 constexpr int kSpinLimit = 1 << 23;      // polls of any other wait (seconds)
 
 // Where a workgroup stands: its team and its place there; `expect` workgroups of the grid

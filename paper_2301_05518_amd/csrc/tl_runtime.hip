@@ -164,11 +164,32 @@ int need_device(tl_ctx* c) {
   return TL_OK;
 }
 
+void run_free(RunMem& m) {
+  if (m.ctl) (void)hipFree(m.ctl);
+  if (m.scratch) (void)hipFree(m.scratch);
+  m = RunMem{};
+}
+
+// Frees everything the context keeps of destroyed plans.
+void mem_drain(tl_ctx* c) {
+  (void)hipStreamSynchronize(c->stream);
+  for (auto& b : c->pool) (void)hipFree(b.p);
+  for (auto& m : c->run_pool) run_free(m);
+  c->pool.clear();
+  c->run_pool.clear();
+  c->pool_bytes = 0;
+}
+
 int dev_alloc(tl_ctx* c, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) bytes = 256;
   if (c->fault_alloc) return fail(c, TL_ERR_NOMEM, "device allocation of %zu bytes failed (TL_FAULT=alloc)", bytes);
   hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && (!c->pool.empty() || !c->run_pool.empty())) {   // what the context keeps goes first
+    (void)hipGetLastError();
+    mem_drain(c);
+    e = hipMalloc(p, bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -1193,12 +1214,6 @@ int plan_capture(tl_plan* p, int parity) {
   return rc;
 }
 
-void run_free(RunMem& m) {
-  if (m.ctl) (void)hipFree(m.ctl);
-  if (m.scratch) (void)hipFree(m.scratch);
-  m = RunMem{};
-}
-
 // Keeps a plan's whole-run memory for a later plan: at most four pairs, 256 MB of scratch in all.
 void run_put(tl_ctx* c, RunMem m) {
   size_t held = m.bytes;
@@ -1320,8 +1335,7 @@ int tl_destroy(tl_ctx* c) {
       DeviceGuard dg(c->device);   // teardown goes on even if the switch fails
       (void)hipStreamSynchronize(c->stream);
       if (c->scratch) (void)hipFree(c->scratch);
-      for (auto& b : c->pool) (void)hipFree(b.p);
-      for (auto& m : c->run_pool) run_free(m);
+      mem_drain(c);
       if (c->run_fail) (void)hipHostFree(c->run_fail);
     }
     delete c;
