@@ -71,7 +71,7 @@ def parse():
     return ap.parse_args()
 
 
-STEP_SOURCES = ("tl_step.h", "tl_step_f64.hip", "tl_step_f32.hip", "tl_step_f16s.hip", "tl_step_bf16.hip",
+STEP_SOURCES = ("tl_step.h", "tl_run.h", "tl_step_f64.hip", "tl_step_f32.hip", "tl_step_f16s.hip", "tl_step_bf16.hip",
                 "tl_format.h", "tl_internal.h")
 
 
@@ -142,7 +142,7 @@ def summarize_counters(fetch_dir, write_dir, workload_key, tile, path=None):
     for counter, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = _counter_rows(d, counter)
         # the step-kernel instance with the most dispatches (the plan the run timed)
-        names = [r["Kernel_Name"] for r in rows if "step_" in r["Kernel_Name"]]
+        names = [r["Kernel_Name"] for r in rows if "step_" in r["Kernel_Name"] or "smear_run" in r["Kernel_Name"]]
         if names and kernel is None:
             kernel = max(set(names), key=names.count)
         step = [float(r["Counter_Value"]) * 1024 for r in rows if r["Kernel_Name"] == kernel]
