@@ -40,7 +40,7 @@
 // 8.9 -> 4.0; 48^3 3 RHS FP32 11.1 -> 3.3, F16S 9.3 -> 3.6; 24^3 + 32^3 + 48^3 BF16 21 RHS
 // 24 -> 20; 64^3 FP32 24 RHS 104 -> 55.  At 64^3 the vector units issue 91% of the cycles the
 // kernel runs (1.46 M instructions of 4 cycles per SIMD in 6.41 M cycles), so what is left there
-// is the instruction count: 270 to 285 per site and RHS, 222 of them FMAs.  A copy that does
+// is the instruction count: 253 per site and RHS, the fetch waves' included, 222 of them FMAs.  A copy that does
 // not wait for its neighbours takes 41.5 instead of 50 us a step there, 3.0 instead of 3.3 at
 // 48^3 FP32, and 2.2 instead of 4.0 at 32^3 FP64, which is the one that the exchange bounds.
 #pragma once
