@@ -200,8 +200,8 @@ int dev_alloc(tl_ctx* c, void** p, size_t bytes) {
 
 // Plan memory.  A block given back serves a later plan of the same context without a wait: all
 // work on it is queued on the context's stream (a new stream waits for the old one).  At most
-// kPoolBlocks blocks and kPoolBytes in all are kept, none over twice the size asked for is
-// handed out, and tl_destroy frees them.
+// kPoolBlocks blocks and kPoolBytes in all are kept (the newest), none over twice the size asked
+// for is handed out, and tl_destroy frees them.
 constexpr size_t kPoolBlocks = 12, kPoolBytes = size_t(256) << 20;
 
 int mem_get(tl_ctx* c, void** p, size_t* bytes) {
@@ -224,7 +224,15 @@ int mem_get(tl_ctx* c, void** p, size_t* bytes) {
 
 void mem_put(tl_ctx* c, void* p, size_t bytes) {
   if (!p) return;
-  if (c->pool.size() < kPoolBlocks && c->pool_bytes + bytes <= kPoolBytes) {
+  if (bytes <= kPoolBytes) {
+    // the blocks kept longest make room: a pool full of sizes that no plan asks for any more would
+    // send every later call to the allocator (16^3 FP32, 20 steps: 83 instead of 61 us)
+    while (!c->pool.empty() && (c->pool.size() >= kPoolBlocks || c->pool_bytes + bytes > kPoolBytes)) {
+      (void)hipStreamSynchronize(c->stream);
+      (void)hipFree(c->pool.front().p);
+      c->pool_bytes -= c->pool.front().bytes;
+      c->pool.erase(c->pool.begin());
+    }
     try {
       c->pool.push_back({p, bytes});
       c->pool_bytes += bytes;
