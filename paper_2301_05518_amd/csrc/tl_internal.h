@@ -151,7 +151,8 @@ struct RunUnit {
   int32_t c[3];           // cell extents
   int32_t b[3];           // tile extents
   int32_t t[3];           // tiles per direction
-  int32_t shape;          // equal for units with equal c, b and t
+  int32_t first, span;    // first member of the team that runs it; members its round occupies
+  int32_t shape;          // equal for units with equal c, b, t and span
 };
 
 // A team's meeting point, and the launch's control block (device memory, zeroed once; each

@@ -38,7 +38,7 @@
 // Measured, microseconds per step with everything a run does once spread over its steps, before
 // (the tuned step kernels in a graph) and now: 8^3 FP64 1 RHS 5.2 -> 1.2; 32^3 FP64 3 RHS
 // 8.9 -> 4.0; 48^3 3 RHS FP32 11.1 -> 3.3, F16S 9.3 -> 3.6; 24^3 + 32^3 + 48^3 BF16 21 RHS
-// 24 -> 20; 64^3 FP32 24 RHS 104 -> 55.  At 64^3 the vector units issue 91% of the cycles the
+// 24 -> 16.8; 64^3 FP32 24 RHS 104 -> 55.  At 64^3 the vector units issue 91% of the cycles the
 // kernel runs (1.46 M instructions of 4 cycles per SIMD in 6.41 M cycles), so what is left there
 // is the instruction count: 253 per site and RHS, the fetch waves' included, 222 of them FMAs.  A copy that does
 // not wait for its neighbours takes 41.5 instead of 50 us a step there, 3.0 instead of 3.3 at
@@ -657,7 +657,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   RunExch x;
   x.stride = a.team_size * a.np * 16;
   const int64_t plane = (int64_t)a.subs * R * Exch<P>::NW * x.stride;
-  x.base = a.scratch + team * 2 * plane;
+  x.base = a.scratch + team * 2 * plane + (int64_t)g.first * a.np * 16;   // the unit's own slots
   x.plane_bytes = (int)plane;
   x.tag0 = tag0;
   x.par0 = par0;
@@ -668,7 +668,7 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
     else if (entries <= 2 * lanes) run_fetch<P, R, 2>(a, g, x, tile, lds);
     else run_fetch<P, R, kFetch>(a, g, x, tile, lds);
   } else {
-    run_compute<P, R, CUT>(a, g, x, tile, xcc, full, lds, alpha, beta);
+    run_compute<P, R, CUT>(a, g, x, tile, xcc + g.first, full, lds, alpha, beta);
   }
 }
 
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
       xcc[k] = (uint8_t)ctl_load(a.ctl->xcc + pl.team * a.team_size + k);
   __syncthreads();
   if (me < size) {
-    uint32_t barriers = 0, seq = 0;   // team barriers passed, units run
+    uint32_t barriers = 0, seq = 0;   // team barriers passed, rounds begun (a round: the units that run at once)
     // Every member has finished what came before: needed before scratch slots change their readers.
     auto team_barrier = [&] {
       barriers++;
@@ -748,20 +748,23 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
       const int share = uniform((int)sh[0]);
       __syncthreads();
       if (share >= a.n_shares) break;
-      for (int u = share; u < a.n_units; u += a.n_shares, seq++) {
+      for (int u = share; u < a.n_units; u += a.n_shares) {
         const RunUnit& g = a.units[u];
-        const int n_tiles = g.t[0] * g.t[1] * g.t[2];
-        const bool fast = size >= n_tiles;
+        const int tile = me - g.first;
+        const bool fast = size >= g.span;
+        // The units of a round have members, scratch slots and tags of their own place in the team,
+        // so they share the round's tags; a team too small for the round runs them one by one.
+        if (g.first == 0 || !fast) seq++;
         // Units of one shape follow each other without a barrier: a workgroup that starts the next
         // one overwrites words of step n - 2, which its readers have read before they published the
         // step n - 1 it has read; and words of step n - 1 once those readers have published the
         // next unit's input.
-        if (seq > 0 && (!fast || g.shape != shape)) team_barrier();
+        if (seq > 1 && (!fast || g.shape != shape)) team_barrier();
         shape = fast ? g.shape : -1;
-        const uint32_t pubs = seq * (uint32_t)a.n_steps;
+        const uint32_t pubs = (seq - 1) * (uint32_t)a.n_steps;
         if (fast) {
-          if (me < n_tiles)
-            run_tile_steps<P, R, CUT>(a, g, me, epoch + 1u + pubs, (int)(pubs & 1), pl.team, xcc, full, lds, alpha, beta);
+          if (tile >= 0 && tile < g.t[0] * g.t[1] * g.t[2])
+            run_tile_steps<P, R, CUT>(a, g, tile, epoch + 1u + pubs, (int)(pubs & 1), pl.team, xcc, full, lds, alpha, beta);
         } else if constexpr (CUT) {
           if ((int)threadIdx.x < a.np * a.subs)
             run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);

@@ -191,3 +191,22 @@ def test_refusals(ctx, torch, monkeypatch):
     monkeypatch.setenv("TL_TILE", "9,512,256,0")
     with pytest.raises(tl.TwolinkError, match="TL_ERR_UNSUPPORTED"):
         smear(ctx, torch, lats, 4, 1.0, "f32")
+
+
+@pytest.mark.parametrize("n", [4, 5])
+@pytest.mark.parametrize("tile", ["9,512,32,0,0,0", "9,512,32,0,0,1", "9,512,32,64,0,0", "9,512,64,8,0,0"])
+def test_smaller_units_share_a_team(ctx, torch, tile, n, monkeypatch):
+    """Units of the smaller lattices of a batch run several at once in one team: even and uneven
+    numbers of them per team (3, 2 and 5 slices), one-tile cells, odd and even step counts (the
+    two scratch planes), a short grid, and a team too small for its place (run one by one)."""
+    import paper_2301_05518_amd as tl
+    lats = lattices(90, [((32, 24, 32, 1), [0]), ((16, 12, 20, 3), [0, 1, 2]), ((12, 7, 16, 2), [0, 1, 1]),
+                         ((4, 6, 4, 5), [0, 1, 2, 3, 4])])
+    monkeypatch.setenv("TL_TILE", DIRECT)
+    _, (want,) = smear(ctx, torch, lats, n, 0.1 * n, "f32")
+    monkeypatch.setenv("TL_TILE", tile)
+    info, outs = smear(ctx, torch, lats, n, 0.1 * n, "f32", tl.TL_GRAPH, runs=3)
+    assert info["variant"] == 9
+    for got in outs:
+        for w, g in zip(want, got):
+            np.testing.assert_array_equal(g, w)
