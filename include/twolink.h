@@ -298,6 +298,10 @@ int tl_smear(tl_ctx *ctx, const tl_job *jobs, int n_jobs, int n_steps, double si
  * captured step graph, so that repeated runs pay none of that again.
  * The jobs array (and the host arrays it points to) is copied; the device
  * pointers in it (W, psi) must stay valid until tl_plan_destroy.
+ * tl_plan_load, _run, _store and _reduce only queue kernels and may be captured by the caller in
+ * a graph of the context's stream, from the first run on; with TL_AUTOTUNE or the TL_TILE variable, after a
+ * first run outside the capture.  Under a capture TL_ERR_HIP: tl_plan_create, tl_smear and
+ * that first run.
  */
 int tl_plan_create(tl_ctx *ctx, const tl_job *jobs, int n_jobs, int n_steps, double sigma,
                    int prec, unsigned flags, tl_plan **out);

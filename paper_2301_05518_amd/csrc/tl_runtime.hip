@@ -278,8 +278,20 @@ int run_check(tl_ctx* c) {
   return fail(c, TL_ERR_HIP, "a whole-run smearing launch gave up waiting for another workgroup");
 }
 
-// Upload of a host table onto the context stream.  A small one travels in a kernel's arguments,
-// which are copied when the launch is queued, so nothing has to wait for it.
+// Plans are made ready (tables, memory, tuning) outside a caller's stream capture: under it the
+// uploads would only be recorded, and whatever runs before the graph is replayed would read tables
+// that were never written.
+int need_eager(tl_ctx* c, const char* what) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (!c->stream) return TL_OK;   // the null stream is never captured
+  HIP_TRY(c, hipStreamIsCapturing(c->stream, &st));
+  if (st != hipStreamCaptureStatusNone) return fail(c, TL_ERR_HIP, "%s while the context's stream is being captured", what);
+  return TL_OK;
+}
+
+// Upload of a host table onto the context stream (never under capture, see need_eager).  A small
+// one travels in a kernel's arguments, which are copied when the launch is queued, so nothing has
+// to wait for it.
 int upload(tl_ctx* c, void* dst, const void* src, size_t bytes) {
   if (bytes == 0) return TL_OK;
   if (bytes <= tl::kUploadArgs && bytes % 4 == 0 && !c->fault_launch) {
@@ -1225,18 +1237,22 @@ bool default_run(const tl_plan* p, StepConfig* cfg) {
   return false;
 }
 
+// The tiling of an untuned plan, made ready when the plan is created, so that its first run
+// queues launches only and may be captured by the caller.
+int prepare_untuned(tl_plan* p) {
+  StepConfig run{};
+  return upload_tiling(p, default_run(p, &run) ? run : p->tile.cfg, &p->tile);
+}
+
 int plan_prepare(tl_plan* p) {
   if (p->ready) return TL_OK;
   Tuned forced;
-  StepConfig run{};
   if (tile_override(&forced)) {
+    TL_TRY(need_eager(p->ctx, "first run of a plan (TL_TILE)"));
     TL_TRY(upload_tuned(p, forced));
-  } else if ((p->flags & TL_AUTOTUNE) && p->n_steps > 0) {
+  } else if (p->flags & TL_AUTOTUNE) {
+    TL_TRY(need_eager(p->ctx, "first run of a plan (TL_AUTOTUNE)"));
     TL_TRY(plan_autotune(p));
-  } else if (default_run(p, &run)) {
-    TL_TRY(upload_tiling(p, run, &p->tile));
-  } else {
-    TL_TRY(upload_tiling(p, p->tile.cfg, &p->tile));
   }
   p->ready = true;
   return TL_OK;
@@ -1575,6 +1591,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     }
     TL_TRY(need_device(c));
     TL_ON_DEVICE(c);
+    TL_TRY(need_eager(c, "plan created"));
   
     tl_plan* p = new (std::nothrow) tl_plan();
     if (!p) return fail(c, TL_ERR_NOMEM, "host allocation failed");
@@ -1687,7 +1704,8 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
         if (hipMemsetAsync(p->buf[k], 0, p->buf_bytes, c->stream) != hipSuccess)
           rc = fail(c, TL_ERR_HIP, "hipMemsetAsync failed");
     }
-    if (rc == TL_OK) rc = describe_tiling(p, p->tile.cfg, &p->tile);   // uploaded by the first run
+    if (rc == TL_OK) rc = describe_tiling(p, p->tile.cfg, &p->tile);
+    if (rc == TL_OK && !(flags & TL_AUTOTUNE)) rc = prepare_untuned(p);   // a tuned one: its first run
     if (rc != TL_OK) return rc;
     // info
     tl_plan_info& in = p->info;
@@ -1946,6 +1964,8 @@ int tl_smear(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigm
         if (it->first != sig) continue;
         c->smear_plans.splice(c->smear_plans.begin(), c->smear_plans, it);   // most recent first
         tl_plan* p = c->smear_plans.front().second;
+        TL_ON_DEVICE(c);
+        TL_TRY(need_eager(c, "tl_smear"));
         c->stats.smear_plan_hits++;
         p->cur = 0;   // the sources are packed afresh, into the buffer whose graph was captured first
         int rc = tl_plan_load(p);
