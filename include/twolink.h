@@ -26,8 +26,8 @@
  *   (tl_plan_*) keeps the job pointers given to tl_plan_create until
  *   tl_plan_destroy.  Library-internal memory (resident packed fields,
  *   work lists, reduction partials, scratch) belongs to the context or plan;
- *   a context keeps up to 512 MB of its destroyed plans' memory for later
- *   plans until tl_destroy (or until an allocation fails).
+ *   a context keeps up to 512 MB of the memory of earlier tl_smear calls for
+ *   later ones until tl_destroy (or until an allocation fails).
  * - "device" pointers are HIP device memory of the context's device;
  *   "host" pointers are ordinary host memory read during the call.
  * - Geometry: tl_geom.L = {Lx, Ly, Lz, Lt}, every extent in [1, 4096] and
@@ -278,8 +278,9 @@ int tl_laplacian(tl_ctx *ctx, const tl_geom *g, const void *W, const int32_t *w_
  * Smearing of eq. tlSmear, psi <- (1 + (sigma/n) Lap)^n psi with n = n_steps,
  * applied in place to every right-hand side of every job on its own slice.
  * Jobs may have different geometries (uneven batch).  Equivalent to
- * tl_plan_create + load + run + store + destroy, except with TL_GRAPH: the
- * context then keeps the plan (resident buffers, work list, tiling, captured
+ * tl_plan_create + load + run + store + destroy (so the call returns when the
+ * smearing is done), except with TL_GRAPH: the call then does not wait, and
+ * the context keeps the plan (resident buffers, work list, tiling, captured
  * graph) of its 4 most recent distinct calls, keyed by everything the call
  * passes (device pointers, geometries, slice lists, n, sigma, precision,
  * flags), and a repeated call replays the kept graph without capturing; the
@@ -346,6 +347,8 @@ int tl_plan_get_info(const tl_plan *plan, tl_plan_info *info);
  */
 int tl_stream_time(tl_ctx *ctx, void *buf, int64_t bytes, int n_in, int kinds, int grid, int reps,
                    double *ms);
+/* Wait until the context's stream is idle and release the plan: W and psi may be freed or reused
+ * on any stream afterwards.  Graphs that hold the plan's captured calls must not run any more. */
 int tl_plan_destroy(tl_plan *plan);
 
 /* -------------------------------------------------------- reductions */

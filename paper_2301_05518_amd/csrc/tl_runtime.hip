@@ -59,7 +59,7 @@ struct tl_ctx {
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
-  // device memory of destroyed plans, kept for the next ones (see mem_get)
+  // device memory of tl_smear's plans, kept for the next call (see mem_get)
   struct MemBlock {
     void* p;
     size_t bytes;
@@ -170,7 +170,7 @@ void run_free(RunMem& m) {
   m = RunMem{};
 }
 
-// Frees everything the context keeps of destroyed plans.
+// Frees everything the context keeps of earlier tl_smear calls.
 void mem_drain(tl_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   for (auto& b : c->pool) (void)hipFree(b.p);
@@ -198,13 +198,16 @@ int dev_alloc(tl_ctx* c, void** p, size_t bytes) {
   return TL_OK;
 }
 
-// Plan memory.  A block given back serves a later plan of the same context without a wait: all
-// work on it is queued on the context's stream (a new stream waits for the old one).  At most
-// kPoolBlocks blocks and kPoolBytes in all are kept (the newest), none over twice the size asked
-// for is handed out, and tl_destroy frees them.
+// Memory of tl_smear's plans: a block given back (after its last work has finished) serves a later
+// call of the same context, which saves the allocator's round trips.  At most kPoolBlocks blocks and
+// kPoolBytes in all are kept (the newest), none over twice the size asked for is handed out, and
+// tl_destroy frees them.  A plan of tl_plan_create takes its memory from the allocator and gives
+// it back there: graphs that the caller captured may run it on streams the context does not know,
+// which only the wait inside hipFree covers.
 constexpr size_t kPoolBlocks = 12, kPoolBytes = size_t(256) << 20;
 
-int mem_get(tl_ctx* c, void** p, size_t* bytes) {
+int mem_get(tl_ctx* c, bool pooled, void** p, size_t* bytes) {
+  if (!pooled) return dev_alloc(c, p, *bytes);
   *bytes = std::max<size_t>((*bytes + 4095) / 4096 * 4096, 4096);
   size_t best = c->pool.size();
   if (!c->fault_alloc)
@@ -222,13 +225,12 @@ int mem_get(tl_ctx* c, void** p, size_t* bytes) {
   return dev_alloc(c, p, *bytes);
 }
 
-void mem_put(tl_ctx* c, void* p, size_t bytes) {
+void mem_put(tl_ctx* c, bool pooled, void* p, size_t bytes) {
   if (!p) return;
-  if (bytes <= kPoolBytes) {
-    // the blocks kept longest make room: a pool full of sizes that no plan asks for any more would
+  if (pooled && bytes <= kPoolBytes) {
+    // the blocks kept longest make room: a pool full of sizes that no call asks for any more would
     // send every later call to the allocator (16^3 FP32, 20 steps: 83 instead of 61 us)
     while (!c->pool.empty() && (c->pool.size() >= kPoolBlocks || c->pool_bytes + bytes > kPoolBytes)) {
-      (void)hipStreamSynchronize(c->stream);
       (void)hipFree(c->pool.front().p);
       c->pool_bytes -= c->pool.front().bytes;
       c->pool.erase(c->pool.begin());
@@ -240,7 +242,6 @@ void mem_put(tl_ctx* c, void* p, size_t bytes) {
     } catch (...) {   // no host memory for the list: free the block
     }
   }
-  (void)hipStreamSynchronize(c->stream);
   (void)hipFree(p);
 }
 
@@ -477,6 +478,7 @@ struct tl_plan {
   size_t buf_cap[2] = {0, 0}, tables_cap = 0;   // bytes of the blocks behind buf and tables
   char* buf[2] = {nullptr, nullptr};
   int cur = 0;
+  bool pooled = false;                          // of a tl_smear call: its memory is kept for the next
 
   // device tables: the step groups of both tilings (group_cap entries each), whole-run units,
   // per-job pack offsets, reduction fields, partials
@@ -809,7 +811,7 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
       if (it == c->run_pool.end() || (it->bytes < r.scratch && k->bytes > it->bytes) ||
           (k->bytes >= r.scratch && k->bytes < it->bytes))
         it = k;
-    if (it != c->run_pool.end() && !c->fault_alloc) {
+    if (p->pooled && it != c->run_pool.end() && !c->fault_alloc) {
       p->run = *it;
       c->run_pool.erase(it);
     } else {
@@ -1282,34 +1284,33 @@ int plan_capture(tl_plan* p, int parity) {
   return rc;
 }
 
-// Keeps a plan's whole-run memory for a later plan: at most four pairs, 256 MB of scratch in all.
-void run_put(tl_ctx* c, RunMem m) {
+// The same for a plan's whole-run memory: at most four pairs, 256 MB of scratch in all, are kept.
+void run_put(tl_ctx* c, bool pooled, RunMem m) {
   size_t held = m.bytes;
   for (const auto& k : c->run_pool) held += k.bytes;
-  if (c->run_pool.size() < 4 && held <= kPoolBytes) {
+  if (pooled && c->run_pool.size() < 4 && held <= kPoolBytes) {
     try {
       c->run_pool.push_back(m);
       return;
     } catch (...) {
     }
   }
-  (void)hipStreamSynchronize(c->stream);
   run_free(m);
 }
 
+// Waits for the plan's queued work: afterwards its memory and the jobs' fields may go, on whatever
+// stream they are used next.
 void plan_free(tl_plan* p) {
   if (!p) return;
   if (p->ctx && p->ctx->device >= 0) {
     DeviceGuard dg(p->ctx->device);
     tl_ctx* c = p->ctx;
-    // On the null stream, which orders the caller's own frees and allocations after the queued
-    // work, nothing waits; on another stream the call waits, so that the jobs' fields may go.
-    if (c->stream || p->graph[0] || p->graph[1]) (void)hipStreamSynchronize(c->stream);
+    (void)hipStreamSynchronize(c->stream);
     for (auto& g : p->graph)
       if (g) (void)hipGraphExecDestroy(g);
-    for (int k = 0; k < 2; k++) mem_put(c, p->buf[k], p->buf_cap[k]);
-    mem_put(c, p->tables, p->tables_cap);
-    if (p->run.ctl) run_put(c, p->run);
+    for (int k = 0; k < 2; k++) mem_put(c, p->pooled, p->buf[k], p->buf_cap[k]);
+    mem_put(c, p->pooled, p->tables, p->tables_cap);
+    if (p->run.ctl) run_put(c, p->pooled, p->run);
   }
   delete p;
 }
@@ -1558,10 +1559,9 @@ int tl_laplacian(tl_ctx* c, const tl_geom* g, const void* W, const int32_t* w_sl
 
 namespace {
 
-// tl_plan_create; clear: the resident buffers start as zeros (a plan that is loaded before it
-// runs does not need that).
+// tl_plan_create; pooled: a plan of tl_smear, which is loaded before it runs.
 int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigma, int prec, unsigned flags,
-                bool clear, tl_plan** out) {
+                bool pooled, tl_plan** out) {
   try {
     if (!c) return TL_ERR_ARG;
     if (!out) return fail(c, TL_ERR_ARG, "out is NULL");
@@ -1604,6 +1604,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     p->n_steps = n_steps;
     p->sigma = sigma;
     p->flags = flags;
+    p->pooled = pooled;
     if (n_steps > 0) step_coeffs(one, n_steps, sigma, &p->alpha, &p->beta);
     const int max_width = (flags & TL_PLAIN) ? 1 : 4;
   
@@ -1652,7 +1653,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     for (int k = 0; k < 2 && rc == TL_OK; k++) {
       void* b = nullptr;
       size_t bytes = p->buf_bytes;
-      rc = mem_get(c, &b, &bytes);
+      rc = mem_get(c, pooled, &b, &bytes);
       if (rc == TL_OK) {
         p->buf[k] = static_cast<char*>(b);
         p->buf_cap[k] = bytes;
@@ -1669,7 +1670,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     if (rc == TL_OK) {
       void* t = nullptr;
       size_t bytes = gbytes + ubytes + obytes + rbytes + pbytes;
-      rc = mem_get(c, &t, &bytes);
+      rc = mem_get(c, pooled, &t, &bytes);
       if (rc == TL_OK) {
         p->tables = static_cast<char*>(t);
         p->tables_cap = bytes;
@@ -1698,7 +1699,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
       }
       rc = upload(c, p->packoff_dev, host.data(), host.size());
     }
-    if (rc == TL_OK && clear) {
+    if (rc == TL_OK && (!pooled || (flags & TL_AUTOTUNE))) {
       // zero the resident buffers so tuning runs never see stale bit patterns
       for (int k = 0; k < 2 && rc == TL_OK; k++)
         if (hipMemsetAsync(p->buf[k], 0, p->buf_bytes, c->stream) != hipSuccess)
@@ -1738,7 +1739,7 @@ extern "C" {
 
 int tl_plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigma, int prec, unsigned flags,
                    tl_plan** out) {
-  return plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, true, out);
+  return plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, false, out);
 }
 
 int tl_plan_load(tl_plan* p) {
@@ -1975,12 +1976,12 @@ int tl_smear(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigm
       }
     }
     tl_plan* p = nullptr;
-    TL_TRY(plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, (flags & TL_AUTOTUNE) != 0, &p));
+    TL_TRY(plan_create(c, jobs, n_jobs, n_steps, sigma, prec, flags, true, &p));
     int rc = tl_plan_load(p);
     if (rc == TL_OK) rc = tl_plan_run(p);
     if (rc == TL_OK) rc = tl_plan_store(p);
     if (!keep || rc != TL_OK) {
-      plan_free(p);   // waits for the queued work before releasing the resident buffers
+      plan_free(p);   // waits for the queued work
       return rc;
     }
     c->smear_plans.emplace_front(std::move(sig), p);
