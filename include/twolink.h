@@ -302,7 +302,9 @@ int tl_smear(tl_ctx *ctx, const tl_job *jobs, int n_jobs, int n_steps, double si
  * tl_plan_load, _run, _store and _reduce only queue kernels and may be captured by the caller in
  * a graph of the context's stream, from the first run on; with TL_AUTOTUNE or the TL_TILE variable, after a
  * first run outside the capture.  Under a capture TL_ERR_HIP: tl_plan_create, tl_smear and
- * that first run.
+ * that first run.  A captured run of an even number of steps that is one-step launches or a whole run
+ * (variant 9) ends in the buffer it starts from, so each replay advances the field; replays are
+ * ordered by the caller, with each other and with the plan's other calls.
  */
 int tl_plan_create(tl_ctx *ctx, const tl_job *jobs, int n_jobs, int n_steps, double sigma,
                    int prec, unsigned flags, tl_plan **out);

@@ -917,9 +917,13 @@ int plan_step(tl_plan* p, hipStream_t s, int parity, int g, int k) {
   return plan_launch(p, p->tile, s, p->buf[parity], p->buf[parity ^ 1], g, k);
 }
 
-// Launches of one run of the n steps (each flips the resident buffer).
-int plan_launches(const tl_plan* p) {
-  return p->tile.cfg.variant == 9 ? 1 : p->tile.cfg.variant == 8 ? p->n_steps / 2 + (p->n_steps & 1) : p->n_steps;
+// Whether a run of the n steps ends in the other resident buffer: every step or two-step launch
+// goes from one to the other.  A whole run ends where n one-step launches would, so that a
+// captured run of an even number of steps advances the field with every replay.  It may write the
+// buffer it reads, because a site is read and written by the one thread that holds it (its
+// neighbours get it through the exchange words), and read before anything is written.
+bool plan_flips(const tl_plan* p) {
+  return (p->tile.cfg.variant == 8 ? p->n_steps / 2 + (p->n_steps & 1) : p->n_steps) & 1;
 }
 
 // Queue the n steps starting from buffer `parity` on stream s.
@@ -933,7 +937,7 @@ int plan_enqueue(tl_plan* p, hipStream_t s, int parity) {
       }
     }
   } else if (p->tile.cfg.variant == 9) {
-    TL_TRY(plan_step(p, s, parity, -1, 0));
+    TL_TRY(plan_launch(p, p->tile, s, p->buf[parity], p->buf[plan_flips(p) ? parity ^ 1 : parity], -1, 0));
   } else if (p->tile.cfg.variant == 8) {
     int q = parity;
     for (int k = 0; k < p->n_steps / 2; k++) {
@@ -1774,7 +1778,7 @@ int tl_plan_run(tl_plan* p) {
     } else {
       TL_TRY(plan_enqueue(p, c->stream, p->cur));
     }
-    p->cur ^= (plan_launches(p) & 1);
+    if (plan_flips(p)) p->cur ^= 1;
     return TL_OK;
   } catch (...) {
     return host_failure(p ? p->ctx : nullptr);
