@@ -445,6 +445,7 @@ struct RunShape {
   tl::RunConfig cfg{};
   std::vector<tl::RunUnit> units;
   int np = 0, subs = 1, halo = 0, team_size = 1, n_teams = 0, n_tiles = 0;
+  int n_shares = 1, steps = 1;   // shares the teams take the units in; steps per launch at most
   size_t scratch = 0;
 };
 
@@ -585,6 +586,12 @@ int64_t plan_lds(const tl_plan* p, const StepConfig& cfg, const std::vector<Step
 // Runs of fewer steps use one launch per step: a whole-run launch reads every two-link twice
 // (once as the forward and once as the backward one of a site) before its first step.
 constexpr int kRunMinSteps = 4;
+
+// Unit-steps of a whole-run launch per team at most; longer runs take several launches.  A member
+// without a tile waits for the others at the end of a team's share, and every wait of the kernel
+// is given up after kSpinLimit polls (several seconds): at 2 to 10 us per unit-step a share takes
+// 0.1 to 0.3 s, so no run is long enough to run into that, and other streams get their turn.
+constexpr int kRunMaxUnitSteps = 32768;
 
 // Cut a cell of extents c into at most `team` tiles of at most `sites` sites that a workgroup of
 // `subs` thread sets can hold.  First the fewest waves per SIMD (a phase's arithmetic time), then
@@ -745,9 +752,10 @@ const char* make_run(const tl_plan* p, const StepConfig& cfg, RunShape* out) {
   r.cfg.lds = tl::run_lds(prec, r.cfg.width, r.subs, r.np, halo);
   if (r.cfg.lds > 160 * 1024) return "tiling needs more LDS than this device allows";
   const int64_t plane = (int64_t)r.subs * r.cfg.width * tl::kRunWords[prec] * r.team_size * r.np * 16;
-  if (r.n_teams > tl::kMaxRunTeams || r.cfg.grid > tl::kMaxRunGrid || plane > INT32_MAX || r.units.size() > p->res.size() * 8 ||
-      (int64_t)r.units.size() * p->n_steps > INT32_MAX)
+  if (r.n_teams > tl::kMaxRunTeams || r.cfg.grid > tl::kMaxRunGrid || plane > INT32_MAX || r.units.size() > p->res.size() * 8)
     return "work list too long for the whole-run kernel";
+  r.n_shares = std::min((int)r.units.size(), r.n_teams);
+  r.steps = std::max(1, kRunMaxUnitSteps / (((int)r.units.size() + r.n_shares - 1) / r.n_shares));
   r.scratch = r.cfg.fetch ? (size_t)(r.n_teams * 2 * plane) : 0;
   *out = std::move(r);
   return nullptr;
@@ -876,7 +884,8 @@ int upload_tuned(tl_plan* p, const Tuned& tu) {
 }
 
 // One launch of tiling t over every group (batched) or over one group (plain mode, g >= 0),
-// from buffer `in` to buffer `out`: one step, two for variant 8, all for variant 9.  k: index of the launch
+// from buffer `in` to buffer `out`: one step, two for variant 8, all for variant 9 (in launches of
+// at most run.steps steps, the later ones in place, see plan_flips).  k: index of the launch
 // in its sequence (odd launches run reversed when the tiling flips).
 int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char* in, char* out, int g, int k) {
   tl_ctx* c = p->ctx;
@@ -889,8 +898,7 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.in = in;
     a.out = out;
     a.n_units = (int32_t)t.run.units.size();
-    a.n_shares = std::min<int32_t>(a.n_units, t.run.n_teams);
-    a.n_steps = p->n_steps;
+    a.n_shares = t.run.n_shares;
     a.n_teams = t.run.n_teams;
     a.team_size = t.run.team_size;
     a.np = t.run.np;
@@ -898,7 +906,11 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.halo = t.run.halo;
     a.hop = tl::hop_of(p->prec);
     a.w12 = tl::is_w12(p->prec);
-    return launch(c, "smearing run", [&] { return tl::launch_run(tl::vprec(p->prec), t.run.cfg, a, p->alpha, p->beta, s); });
+    for (int done = 0; done < p->n_steps; done += a.n_steps, a.in = out) {
+      a.n_steps = std::min(t.run.steps, p->n_steps - done);
+      TL_TRY(launch(c, "smearing run", [&] { return tl::launch_run(tl::vprec(p->prec), t.run.cfg, a, p->alpha, p->beta, s); }));
+    }
+    return TL_OK;
   }
   int base = 0, n = t.n_tiles;
   if (g >= 0) {
