@@ -189,8 +189,10 @@ int tl_version(void);
  *                                    own) the
  *                                    one that runs of fewer than four steps use
  *   TL_LOG=1                         print autotuning candidates to stderr
- *   TL_FAULT=alloc|launch            make internal allocations or launches fail
- *                                    (read at tl_create; exercises error paths)
+ *   TL_FAULT=alloc|launch|wait       make internal allocations or launches fail, or
+ *                                    the waits between a whole-run launch's workgroups
+ *                                    run out at once (read at tl_create; exercises error
+ *                                    paths)
  *   TL_TUNE_CACHE=<path>             a JSON file of autotuning results: read at tl_create,
  *                                    rewritten after every sweep, so that a later process
  *                                    skips the sweep for batch shapes already tuned (keys name
@@ -218,8 +220,7 @@ int tl_destroy(tl_ctx *ctx);
  */
 int tl_set_stream(tl_ctx *ctx, void *stream);
 /* Block until the context's stream is idle; reports asynchronous device errors, among them
- * (TL_ERR_HIP) a whole-run launch whose wait for another workgroup ran out after several
- * seconds: that run's output is not valid. */
+ * (TL_ERR_HIP) whole-run launches that gave up (see tl_plan_run). */
 int tl_sync(tl_ctx *ctx);
 /* Message of the last failing call on ctx (ctx = NULL: last failure of tl_create on this thread). */
 const char *tl_last_error(const tl_ctx *ctx);
@@ -313,8 +314,11 @@ int tl_plan_load(tl_plan *plan);
 /* n_steps smearing steps on the resident buffer (eq. tlSmear applied n_steps times; with a
    two-step tiling, n_steps / 2 launches plus one one-step launch when n_steps is odd; with a
    whole-run tiling one launch, which plans of four or more steps without TL_AUTOTUNE, TL_PLAIN
-   and TL_ONE_STEP use by default where their lattices fit).  TL_ERR_HIP also reports an earlier
-   whole-run launch that failed (see tl_sync). */
+   and TL_ONE_STEP use by default where their lattices fit).  A whole-run launch whose wait for
+   another workgroup ran out (after several seconds) leaves NaNs in the fields, and TL_ERR_HIP
+   reports it once, from the first of these calls that follows its end: tl_plan_run, _store,
+   _reduce, _time (nothing is queued then) and _destroy (the plan is released all the same) on that
+   plan, or tl_sync.  tl_smear without TL_GRAPH reports its own. */
 int tl_plan_run(tl_plan *plan);
 /* Unpack the resident buffer into every job's psi (complex128). */
 int tl_plan_store(tl_plan *plan);

@@ -319,8 +319,8 @@ class Plan:
 
     def close(self):
         if getattr(self, "h", None):
-            self.ctx.lib.tl_plan_destroy(self.h)
-            self.h = None
+            h, self.h = self.h, None
+            self.ctx._check(self.ctx.lib.tl_plan_destroy(h))
 
     def __del__(self):
         try:

@@ -176,6 +176,7 @@ struct RunArgs {
   RunCtl* ctl;
   char* scratch;          // exchange words: [team][2][RHS word][team_size * np] of 16 bytes
   uint32_t* fail;         // host-visible: set when a wait ran out
+  int32_t spins;          // polls of a halo word before its wait is given up (kSpinLimit)
   const char* in;
   char* out;
   int32_t n_units, n_shares, n_steps, n_teams, team_size;
@@ -196,6 +197,7 @@ struct RunConfig {
 // Threads per workgroup at most: FP32 arithmetic fits 168 registers (three waves per SIMD), FP64
 // takes up to 256 (two).
 constexpr int run_max_threads(int prec) { return prec == F64 ? 512 : 768; }
+constexpr int kSpinLimit = 1 << 23;   // polls of any wait but for a team to fill (seconds)
 constexpr int kFetch = 4;   // halo entries a fetch thread takes per phase at most
 
 // 16-byte exchange words of a colour vector per precision.

@@ -33,7 +33,8 @@
 // the unit's tile count runs the same exchange with several tiles per workgroup and the
 // two-links read from memory each step (run_slow).  Teams take their shares of the units from
 // a common counter.
-// Every wait is bounded; one that runs out sets *fail and the kernel ends.
+// Every wait is bounded; where one runs out the kernel sets *fail, takes NaNs for the words that
+// did not come (so that they spread over the field), and ends.
 //
 // Measured, microseconds per step with everything a run does once spread over its steps, before
 // (the tuned step kernels in a graph) and now: 8^3 FP64 1 RHS 5.2 -> 1.2; 32^3 FP64 3 RHS
@@ -137,6 +138,9 @@ __device__ __forceinline__ void exch_dwords(const v4u (&w)[Exch<P>::NW], uint32_
   for (int k = 0; k < Exch<P>::ND; k++) d[k] = w[k / 3][k % 3];
 }
 
+// What a reader that gives up takes for a word: NaNs in every format (all exponent bits set).
+__device__ __forceinline__ v4u exch_nan() { return v4u{~0u, ~0u, ~0u, ~0u}; }
+
 // A site's R vectors in LDS: one record, so that every access of a neighbour is one address
 // plus an immediate offset (run_record bytes; the odd multiple of 8 for four RHS keeps the
 // 16 lanes of an 8-byte access phase on different banks).
@@ -208,7 +212,6 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 
 constexpr uint32_t kTeamClosed = 0x40000000u;
 constexpr int kEnrolSpins = 4000;        // about 2 ms of the leader's wait for its team
-constexpr int kSpinLimit = 1 << 23;      // polls of any other wait (seconds)
 
 // Where a workgroup stands: its team and its place there; `expect` workgroups of the grid
 // belong to the team.  Workgroups are dispatched round-robin over the XCDs, so a team of up
@@ -316,10 +319,13 @@ __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, u
               asm volatile("" ::: "memory");
 #pragma unroll
               for (int q = 0; q < X::NW; q++) ok = ok && w[q].w == tag;
-              if (ok || dead) break;
-              if (++spin > kSpinLimit) {
-                run_failed(a.fail);
+              if (ok) break;
+              if (dead || ++spin > a.spins) {
+                if (!dead) run_failed(a.fail);
                 dead = true;
+#pragma unroll
+                for (int q = 0; q < X::NW; q++) w[q] = exch_nan();
+                break;
               }
             }
             uint32_t e[X::ND];
@@ -617,10 +623,13 @@ __device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, co
         bool ok = true;
 #pragma unroll
         for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
-        if (ok || !has[k] || dead) break;
-        if (++spin > kSpinLimit) {
-          run_failed(a.fail);
+        if (ok || !has[k]) break;
+        if (dead || ++spin > a.spins) {
+          if (!dead) run_failed(a.fail);
           dead = true;
+#pragma unroll
+          for (int q = 0; q < X::NW; q++) hw[k][q] = exch_nan();
+          break;
         }
         asm volatile("" ::: "memory");
         load(k, s, r, hw[k]);

@@ -56,6 +56,7 @@ struct tl_ctx {
   bool log = false;
   bool fault_alloc = false;   // TL_FAULT=alloc: internal allocations report failure
   bool fault_launch = false;  // TL_FAULT=launch: launches report failure without running
+  bool fault_wait = false;    // TL_FAULT=wait: whole-run launches give up a halo word that is not there at once
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
@@ -67,7 +68,10 @@ struct tl_ctx {
   std::vector<MemBlock> pool;
   size_t pool_bytes = 0;
   std::vector<RunMem> run_pool;
-  uint32_t* run_fail = nullptr;   // pinned host word a whole-run kernel sets when a wait between workgroups ran out
+  // pinned host words, one per plan with whole-run launches: set by the kernel when a wait between
+  // workgroups ran out (kFailWords; plans beyond that share the last one)
+  uint32_t* run_fail = nullptr;
+  std::vector<char> fail_used;
   double* noalloc = nullptr;  // this device's fixed partial-sum area of tl_reduce_noalloc
   std::string noalloc_err;    // why it is missing (lookup failed at tl_create)
   std::map<std::string, Tuned> tune;       // tuned step tilings by workload key
@@ -271,12 +275,18 @@ int ctx_scratch(tl_ctx* c, size_t bytes, char** out) {
   return TL_OK;
 }
 
-// A whole-run launch whose wait between workgroups ran out (it ended, its output is not valid)
-// is reported once, by the next call that looks.
-int run_check(tl_ctx* c) {
-  if (!c->run_fail || *static_cast<volatile uint32_t*>(c->run_fail) == 0) return TL_OK;
-  *c->run_fail = 0;
-  return fail(c, TL_ERR_HIP, "a whole-run smearing launch gave up waiting for another workgroup");
+// A whole-run launch whose wait between workgroups ran out ends, with NaNs spreading from where it
+// gave up.  That is reported once, by the next call that looks: calls on that plan, or tl_sync.
+constexpr size_t kFailWords = 1024;
+
+bool fail_taken(uint32_t* word) {
+  if (!word || *static_cast<volatile uint32_t*>(word) == 0) return false;
+  *static_cast<volatile uint32_t*>(word) = 0;
+  return true;
+}
+
+int run_failure(tl_ctx* c) {
+  return fail(c, TL_ERR_HIP, "a whole-run smearing launch gave up waiting for another workgroup; its fields are not valid");
 }
 
 // Plans are made ready (tables, memory, tuning) outside a caller's stream capture: under it the
@@ -505,6 +515,7 @@ struct tl_plan {
                                         // tiling of the last step of an odd count
   tl::RunUnit* run_units = nullptr;     // whole-run launches: units table (in tables)
   RunMem run;                           // and their shared memory (taken when first used)
+  uint32_t* fail = nullptr;             // their failure word
   bool ready = false;                   // tuning done (or not requested) and tables uploaded
 
   hipGraphExec_t graph[2] = {nullptr, nullptr};
@@ -804,13 +815,19 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
   if (why) return fail(c, TL_ERR_UNSUPPORTED, "%s", why);
   if (!c->run_fail) {
     if (c->fault_alloc) return fail(c, TL_ERR_NOMEM, "host allocation failed (TL_FAULT=alloc)");
+    c->fail_used.resize(kFailWords, 0);
     void* h = nullptr;
-    if (hipHostMalloc(&h, 64, hipHostMallocMapped) != hipSuccess) {
+    if (hipHostMalloc(&h, kFailWords * sizeof(uint32_t), hipHostMallocMapped) != hipSuccess) {
       (void)hipGetLastError();
       return fail(c, TL_ERR_NOMEM, "hipHostMalloc failed");
     }
+    std::memset(h, 0, kFailWords * sizeof(uint32_t));
     c->run_fail = static_cast<uint32_t*>(h);
-    *c->run_fail = 0;
+  }
+  if (!p->fail) {
+    const size_t k = std::find(c->fail_used.begin(), c->fail_used.end() - 1, 0) - c->fail_used.begin();
+    c->fail_used[k] = 1;
+    p->fail = c->run_fail + k;
   }
   if (!p->run.ctl) {
     // a pair whose scratch is large enough, else any (its scratch is replaced below)
@@ -894,7 +911,8 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.units = p->run_units;
     a.ctl = p->run.ctl;
     a.scratch = p->run.scratch;
-    a.fail = c->run_fail;
+    a.fail = p->fail;
+    a.spins = c->fault_wait ? 0 : tl::kSpinLimit;
     a.in = in;
     a.out = out;
     a.n_units = (int32_t)t.run.units.size();
@@ -1193,6 +1211,7 @@ int plan_autotune(tl_plan* p) {
       bool same = true;
       rc = trial(true, &ms, &same, 1, 3);
       if (rc != TL_OK) break;
+      if (fail_taken(p->fail)) same = false;   // it gave up waiting: not a candidate
       log(p->tile.cfg, ms / p->n_steps, same);
       if (same && ms / p->n_steps < best9) {
         best9 = ms / p->n_steps;
@@ -1315,20 +1334,27 @@ void run_put(tl_ctx* c, bool pooled, RunMem m) {
 }
 
 // Waits for the plan's queued work: afterwards its memory and the jobs' fields may go, on whatever
-// stream they are used next.
-void plan_free(tl_plan* p) {
-  if (!p) return;
+// stream they are used next.  Returns whether a whole-run launch of the plan gave up unreported.
+bool plan_free(tl_plan* p) {
+  if (!p) return false;
+  bool failed = false;
   if (p->ctx && p->ctx->device >= 0) {
     DeviceGuard dg(p->ctx->device);
     tl_ctx* c = p->ctx;
     (void)hipStreamSynchronize(c->stream);
+    failed = fail_taken(p->fail);
     for (auto& g : p->graph)
       if (g) (void)hipGraphExecDestroy(g);
     for (int k = 0; k < 2; k++) mem_put(c, p->pooled, p->buf[k], p->buf_cap[k]);
     mem_put(c, p->pooled, p->tables, p->tables_cap);
     if (p->run.ctl) run_put(c, p->pooled, p->run);
+    if (p->fail) {
+      const size_t k = p->fail - c->run_fail;
+      if (k + 1 < kFailWords) c->fail_used[k] = 0;
+    }
   }
   delete p;
+  return failed;
 }
 
 }  // namespace
@@ -1357,6 +1383,7 @@ int tl_create(tl_ctx** out, int device, void* stream) {
     if (fl) {
       c->fault_alloc = strcmp(fl, "alloc") == 0;
       c->fault_launch = strcmp(fl, "launch") == 0;
+      c->fault_wait = strcmp(fl, "wait") == 0;
     }
     if (device == -1) {
       c->device = -1;
@@ -1460,7 +1487,10 @@ int tl_sync(tl_ctx* c) {
     TL_ON_DEVICE(c);
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipGetLastError());
-    return run_check(c);
+    bool failed = false;
+    if (c->run_fail)
+      for (size_t k = 0; k < kFailWords; k++) failed = fail_taken(c->run_fail + k) || failed;
+    return failed ? run_failure(c) : TL_OK;
   } catch (...) {
     return host_failure(c);
   }
@@ -1780,7 +1810,7 @@ int tl_plan_run(tl_plan* p) {
     tl_ctx* c = p->ctx;
     if (p->n_steps == 0) return TL_OK;
     TL_ON_DEVICE(c);
-    TL_TRY(run_check(c));
+    if (fail_taken(p->fail)) return run_failure(c);
     TL_TRY(plan_prepare(p));
     // a tuned run that is one launch needs no graph
     if ((p->flags & TL_GRAPH) && !(p->tile.cfg.variant == 9 && (p->flags & TL_AUTOTUNE))) {
@@ -1802,6 +1832,7 @@ int tl_plan_store(tl_plan* p) {
     if (!p) return TL_ERR_ARG;
     tl_ctx* c = p->ctx;
     TL_ON_DEVICE(c);
+    if (fail_taken(p->fail)) return run_failure(c);
     for (size_t j = 0; j < p->jobs.size(); j++) {
       const auto& jc = p->jobs[j];
       TL_TRY(launch(c, "unpack", [&] { return tl::launch_unpack(tl::vprec(p->prec), p->buf[p->cur], jc.job.psi, p->packoff_dev + p->packoff_first[j],
@@ -1829,6 +1860,7 @@ int tl_plan_reduce(tl_plan* p, int kind, const tl_plan* other, double* out) {
       b = other->buf[other->cur];
     }
     TL_ON_DEVICE(c);
+    if (fail_taken(p->fail) || (kind == TL_DOT && fail_taken(other->fail))) return run_failure(c);
     // a (this) is the second argument of <other, this>
     return launch(c, "reduction", [&] { return tl::launch_reduce(kind, tl::vprec(p->prec), p->buf[p->cur], b, p->red_dev, (int)p->res.size(), p->max_v3,
                                           p->partials, out, c->stream); });
@@ -1861,6 +1893,7 @@ int tl_plan_time(tl_plan* p, int reps, double* ms_per_step) {
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    if (rc == TL_OK && fail_taken(p->fail)) rc = run_failure(c);
     if (rc == TL_OK) *ms_per_step = ms / ((double)reps * p->n_steps * p->info.launches_per_step);
     return rc;
   } catch (...) {
@@ -1928,8 +1961,8 @@ int tl_plan_get_info(const tl_plan* p, tl_plan_info* info) {
 int tl_plan_destroy(tl_plan* p) {
   try {
     if (!p) return TL_ERR_ARG;
-    plan_free(p);
-    return TL_OK;
+    tl_ctx* c = p->ctx;
+    return plan_free(p) ? run_failure(c) : TL_OK;
   } catch (...) {
     return host_failure(nullptr);
   }
@@ -1997,7 +2030,7 @@ int tl_smear(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigm
     if (rc == TL_OK) rc = tl_plan_run(p);
     if (rc == TL_OK) rc = tl_plan_store(p);
     if (!keep || rc != TL_OK) {
-      plan_free(p);   // waits for the queued work
+      if (plan_free(p) && rc == TL_OK) rc = run_failure(c);   // waits for the queued work
       return rc;
     }
     c->smear_plans.emplace_front(std::move(sig), p);
