@@ -189,10 +189,11 @@ int tl_version(void);
  *                                    own) the
  *                                    one that runs of fewer than four steps use
  *   TL_LOG=1                         print autotuning candidates to stderr
- *   TL_FAULT=alloc|launch|wait       make internal allocations or launches fail, or
- *                                    the waits between a whole-run launch's workgroups
- *                                    run out at once (read at tl_create; exercises error
- *                                    paths)
+ *   TL_FAULT=alloc|launch|exchange|wait
+ *                                    make internal allocations or launches fail, or the
+ *                                    clearing of whole-run launches' memory, or the waits
+ *                                    between their workgroups run out at once (read at
+ *                                    tl_create; exercises error paths)
  *   TL_TUNE_CACHE=<path>             a JSON file of autotuning results: read at tl_create,
  *                                    rewritten after every sweep, so that a later process
  *                                    skips the sweep for batch shapes already tuned (keys name

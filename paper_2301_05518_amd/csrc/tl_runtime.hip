@@ -56,6 +56,7 @@ struct tl_ctx {
   bool log = false;
   bool fault_alloc = false;   // TL_FAULT=alloc: internal allocations report failure
   bool fault_launch = false;  // TL_FAULT=launch: launches report failure without running
+  bool fault_exchange = false;  // TL_FAULT=exchange: memory of whole-run launches cannot be cleared
   bool fault_wait = false;    // TL_FAULT=wait: whole-run launches give up a halo word that is not there at once
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
@@ -805,6 +806,17 @@ bool tiling_applies(const tl_plan* p, const StepConfig& cfg, const char** reason
   return true;
 }
 
+// Device memory that starts as zeros (queued on the context's stream).
+int dev_zeroed(tl_ctx* c, void** m, size_t bytes) {
+  TL_TRY(dev_alloc(c, m, bytes));
+  const hipError_t e = c->fault_exchange ? hipErrorOutOfMemory : hipMemsetAsync(*m, 0, bytes, c->stream);
+  if (e == hipSuccess) return TL_OK;
+  (void)hipGetLastError();
+  (void)hipFree(*m);
+  *m = nullptr;
+  return fail(c, e == hipErrorOutOfMemory ? TL_ERR_NOMEM : TL_ERR_HIP, "clearing %zu bytes: %s", bytes, hipGetErrorString(e));
+}
+
 // Build a whole-run tiling: units table, control block and exchange scratch.  The control block
 // and new scratch start as zeros; afterwards tags only grow, so scratch is never cleared again.
 int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
@@ -841,9 +853,8 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
       c->run_pool.erase(it);
     } else {
       void* m = nullptr;
-      TL_TRY(dev_alloc(c, &m, sizeof(tl::RunCtl)));
+      TL_TRY(dev_zeroed(c, &m, sizeof(tl::RunCtl)));
       p->run.ctl = static_cast<tl::RunCtl*>(m);
-      HIP_TRY(c, hipMemsetAsync(m, 0, sizeof(tl::RunCtl), c->stream));
     }
   }
   if (r.scratch > p->run.bytes) {
@@ -854,10 +865,9 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
     p->run.scratch = nullptr;
     p->run.bytes = 0;
     void* m = nullptr;
-    TL_TRY(dev_alloc(c, &m, r.scratch));
+    TL_TRY(dev_zeroed(c, &m, r.scratch));
     p->run.scratch = static_cast<char*>(m);
     p->run.bytes = r.scratch;
-    HIP_TRY(c, hipMemsetAsync(m, 0, r.scratch, c->stream));
   }
   TL_TRY(upload(c, p->run_units, r.units.data(), r.units.size() * sizeof(tl::RunUnit)));
   t->cfg = cfg;
@@ -1383,6 +1393,7 @@ int tl_create(tl_ctx** out, int device, void* stream) {
     if (fl) {
       c->fault_alloc = strcmp(fl, "alloc") == 0;
       c->fault_launch = strcmp(fl, "launch") == 0;
+      c->fault_exchange = strcmp(fl, "exchange") == 0;
       c->fault_wait = strcmp(fl, "wait") == 0;
     }
     if (device == -1) {
