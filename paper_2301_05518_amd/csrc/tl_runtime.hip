@@ -1022,7 +1022,8 @@ int plan_autotune(tl_plan* p) {
     const Tuned& tu = hit->second;
     if (tiling_applies(p, tu.cfg, &why) && (tu.cfg.variant < 8 || tiling_applies(p, tu.single, &why))) {
       c->stats.tune_hits++;
-      return upload_tuned(p, tu);
+      const int rc = upload_tuned(p, tu);
+      return rc == TL_ERR_NOMEM && tu.cfg.variant == 9 ? upload_tiling(p, tu.single, &p->tile) : rc;
     }
     if (c->log) fprintf(stderr, "[twolink] tune %s: cached tiling %s does not apply (%s), tuning again\n", key.c_str(),
                         cfg_text(tu.cfg).c_str(), why);
@@ -1216,6 +1217,10 @@ int plan_autotune(tl_plan* p) {
       const char* why = nullptr;
       if (!tiling_applies(p, cands9[ci], &why)) continue;
       rc = upload_tiling(p, cands9[ci], &p->tile);
+      if (rc == TL_ERR_NOMEM) {   // no exchange memory: not a candidate
+        rc = TL_OK;
+        continue;
+      }
       if (rc != TL_OK) break;
       float ms = 0.0f;
       bool same = true;
@@ -1285,10 +1290,15 @@ bool default_run(const tl_plan* p, StepConfig* cfg) {
 }
 
 // The tiling of an untuned plan, made ready when the plan is created, so that its first run
-// queues launches only and may be captured by the caller.
+// queues launches only and may be captured by the caller.  Step launches need no exchange memory,
+// so they serve where there is none.
 int prepare_untuned(tl_plan* p) {
   StepConfig run{};
-  return upload_tiling(p, default_run(p, &run) ? run : p->tile.cfg, &p->tile);
+  if (default_run(p, &run)) {
+    const int rc = upload_run(p, run, &p->tile);
+    if (rc != TL_ERR_NOMEM) return rc;
+  }
+  return upload_tiling(p, p->tile.cfg, &p->tile);
 }
 
 int plan_prepare(tl_plan* p) {

@@ -68,3 +68,45 @@ def test_forced_whole_run_is_refused_each_time(ctx, torch, work, monkeypatch):
     assert plan.info()["variant"] == 0
     assert torch.equal(job.psi, want)
     plan.close()
+
+
+@pytest.mark.parametrize("how", ["plan", "graph", "tuned", "smear"])
+def test_step_launches_where_there_is_none(ctx, torch, work, how):
+    import paper_2301_05518_amd as tl
+    job, src, want = work
+    for rep in range(2):
+        job.psi.copy_(src)
+        if how == "smear":
+            ctx.smear([job], 20, 2.0, "f32")
+        else:
+            plan = ctx.plan([job], 20, 2.0, "f32", {"plan": 0, "graph": tl.TL_GRAPH, "tuned": tl.TL_AUTOTUNE}[how])
+            run(plan)
+            log(f"{how}: variant {plan.info()['variant']}")
+            assert plan.info()["variant"] != 9
+            plan.close()
+        ctx.sync()
+        assert torch.equal(job.psi, want), rep
+
+
+def test_cached_whole_run(torch, work, monkeypatch, tmp_path):
+    """A tuning-cache entry that names a whole run: its one-step companion runs."""
+    import json
+
+    import paper_2301_05518_amd as tl
+    job, src, want = work
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("TL_TUNE_CACHE", str(cache))
+    for fault, variant in (("", 9), ("exchange", 0)):
+        monkeypatch.setenv("TL_FAULT", fault)
+        c = tl.Context(0)
+        for _ in range(2):
+            plan = c.plan([job], 20, 2.0, "f32", tl.TL_AUTOTUNE)
+            job.psi.copy_(src)
+            run(plan)
+            c.sync()
+            assert torch.equal(job.psi, want)
+            if fault:
+                assert plan.info()["variant"] == variant and c.stats()["tune_sweeps"] == 0
+            plan.close()
+        c.close()
+        cache.write_text(json.dumps({k: "9,512,32,0,0,0;0,64,1,0,0,0" for k in json.loads(cache.read_text())}))
