@@ -197,8 +197,10 @@ int tl_version(void);
  *   TL_TUNE_CACHE=<path>             a JSON file of autotuning results: read at tl_create,
  *                                    rewritten after every sweep, so that a later process
  *                                    skips the sweep for batch shapes already tuned (keys name
- *                                    the GPU architecture, precision, group width, launch mode
- *                                    and every group's extents and RHS count); an entry whose
+ *                                    the GPU architecture, the set of candidates, precision,
+ *                                    group width, launch mode, the power of two below the step
+ *                                    count (32 at most) and every group's extents and RHS
+ *                                    count); an entry whose
  *                                    tiling the plan cannot run is dropped and tuned again
  */
 

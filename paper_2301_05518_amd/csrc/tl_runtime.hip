@@ -995,9 +995,18 @@ int plan_enqueue(tl_plan* p, hipStream_t s, int parity) {
   return TL_OK;
 }
 
+// What a plan's tuned tiling depends on.  "c2" is the set of candidates: entries of a cache file
+// from before whole-run launches do not name it and are tuned again.  Batched plans name the power
+// of two below n (32 at most; 2 also for 3 steps): fewer than two steps have no two-step and fewer
+// than four no whole-run candidates, and those spread what a run costs once (about 10 us) over n.
 std::string tune_key(const tl_plan* p) {
-  std::string k = p->ctx->arch + "|p" + std::to_string(p->prec) + "|w" + std::to_string(p->width) +
+  std::string k = p->ctx->arch + "|c2|p" + std::to_string(p->prec) + "|w" + std::to_string(p->width) +
                   ((p->flags & TL_PLAIN) ? "|plain" : "|batch") + ((p->flags & TL_ONE_STEP) ? "|one" : "");
+  if (!(p->flags & (TL_PLAIN | TL_ONE_STEP))) {
+    int n = 1;
+    while (n < 32 && 2 * n <= p->n_steps) n *= 2;
+    k += "|n" + std::to_string(n);
+  }
   for (const auto& g : p->groups) {
     const tl_geom& ge = p->jobs[g.job].job.g;
     k += "|" + std::to_string(ge.L[0]) + "x" + std::to_string(ge.L[1]) + "x" + std::to_string(ge.L[2]) + ":" +
