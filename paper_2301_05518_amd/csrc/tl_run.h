@@ -33,8 +33,8 @@
 // the unit's tile count runs the same exchange with several tiles per workgroup and the
 // two-links read from memory each step (run_slow).  Teams take their shares of the units from
 // a common counter.
-// Every wait is bounded; where one runs out the kernel sets *fail, takes NaNs for the words that
-// did not come (so that they spread over the field), and ends.
+// Every wait is bounded; where one runs out the kernel sets *fail, leaves NaNs in the results
+// of the tile concerned (in run_slow: takes them for the words that did not come), and ends.
 //
 // Measured, microseconds per step with everything a run does once spread over its steps, before
 // (the tuned step kernels in a graph) and now: 8^3 FP64 1 RHS 5.2 -> 1.2; 32^3 FP64 3 RHS
@@ -138,7 +138,7 @@ __device__ __forceinline__ void exch_dwords(const v4u (&w)[Exch<P>::NW], uint32_
   for (int k = 0; k < Exch<P>::ND; k++) d[k] = w[k / 3][k % 3];
 }
 
-// What a reader that gives up takes for a word: NaNs in every format (all exponent bits set).
+// What a reader of run_slow that gives up takes for a word: NaNs in every format (all exponent bits set).
 __device__ __forceinline__ v4u exch_nan() { return v4u{~0u, ~0u, ~0u, ~0u}; }
 
 // A site's R vectors in LDS: one record, so that every access of a neighbour is one address
@@ -585,7 +585,7 @@ __device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, 
 // the load's latency run behind arithmetic.  (Requesting them a phase earlier still finds most
 // of them not published yet and asks again: 70 instead of 60 us per step at 64^3 FP32 24 RHS.)
 template <int P, int R, int E>
-__device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile,
+__device__ __forceinline__ bool run_fetch(const RunArgs& a, const RunUnit& g, const RunExch& x, int tile,
                                           unsigned char* lds) {
   using real = typename Fmt<P>::real;
   using X = Exch<P>;
@@ -623,13 +623,10 @@ __device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, co
         bool ok = true;
 #pragma unroll
         for (int q = 0; q < X::NW; q++) ok = ok && hw[k][q].w == tag;
-        if (ok || !has[k]) break;
-        if (dead || ++spin > a.spins) {
-          if (!dead) run_failed(a.fail);
+        if (ok || !has[k] || dead) break;
+        if (++spin > a.spins) {
+          run_failed(a.fail);
           dead = true;
-#pragma unroll
-          for (int q = 0; q < X::NW; q++) hw[k][q] = exch_nan();
-          break;
         }
         asm volatile("" ::: "memory");
         load(k, s, r, hw[k]);
@@ -656,11 +653,12 @@ __device__ __forceinline__ void run_fetch(const RunArgs& a, const RunUnit& g, co
     }
   }
   __builtin_amdgcn_s_setprio(0);
+  return dead;
 }
 
-// One unit, one tile per workgroup: `tile` of this workgroup.
+// One unit, one tile per workgroup: `tile` of this workgroup.  True in a thread that gave up a wait.
 template <int P, int R, bool CUT>
-__device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
+__device__ __forceinline__ bool run_tile_steps(const RunArgs& a, const RunUnit& g, int tile, uint32_t tag0, int par0,
                                                int team, const uint8_t* xcc, bool full, unsigned char* lds,
                                                typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
   RunExch x;
@@ -673,12 +671,25 @@ __device__ __forceinline__ void run_tile_steps(const RunArgs& a, const RunUnit& 
   x.ne = 2 * a.np + (R == 1 ? 2 : 1) * a.halo;
   if (CUT && uniform((int)threadIdx.x) >= a.np * a.subs) {
     const int lanes = (int)blockDim.x - a.np * a.subs, entries = a.subs * a.halo;
-    if (entries <= lanes) run_fetch<P, R, 1>(a, g, x, tile, lds);
-    else if (entries <= 2 * lanes) run_fetch<P, R, 2>(a, g, x, tile, lds);
-    else run_fetch<P, R, kFetch>(a, g, x, tile, lds);
-  } else {
-    run_compute<P, R, CUT>(a, g, x, tile, xcc + g.first, full, lds, alpha, beta);
+    if (entries <= lanes) return run_fetch<P, R, 1>(a, g, x, tile, lds);
+    if (entries <= 2 * lanes) return run_fetch<P, R, 2>(a, g, x, tile, lds);
+    return run_fetch<P, R, kFetch>(a, g, x, tile, lds);
   }
+  run_compute<P, R, CUT>(a, g, x, tile, xcc + g.first, full, lds, alpha, beta);
+  return false;
+}
+
+// The result of a tile whose halo did not come: NaNs at its first site, so that no one takes the
+// field for valid (a launch that goes on from it spreads them).
+template <int P>
+__device__ __forceinline__ void run_poison(const RunArgs& a, const RunUnit& g, int tile) {
+  using real = typename Fmt<P>::real;
+  const RunTile tl = run_tile(g, tile);
+  real v[6];
+  for (int c = 0; c < 6; c++) v[c] = (real)__builtin_nanf("");
+  for (int r = 0; r < g.nr; r++)
+    Fmt<P>::template store_v<real, false>(a.out + g.psi_off + (int64_t)r * g.rhs_stride, g.Vp,
+                                          run_site(g, a.hop, tl.o[0], tl.o[1], tl.o[2]), v);
 }
 
 template <int P, int R, bool CUT>
@@ -771,14 +782,16 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
         if (seq > 1 && (!fast || g.shape != shape)) team_barrier();
         shape = fast ? g.shape : -1;
         const uint32_t pubs = (seq - 1) * (uint32_t)a.n_steps;
+        bool gave_up = false;
         if (fast) {
           if (tile >= 0 && tile < g.t[0] * g.t[1] * g.t[2])
-            run_tile_steps<P, R, CUT>(a, g, tile, epoch + 1u + pubs, (int)(pubs & 1), pl.team, xcc, full, lds, alpha, beta);
+            gave_up = run_tile_steps<P, R, CUT>(a, g, tile, epoch + 1u + pubs, (int)(pubs & 1), pl.team, xcc, full, lds, alpha, beta);
         } else if constexpr (CUT) {
           if ((int)threadIdx.x < a.np * a.subs)
             run_slow<P, R>(a, g, me, size, epoch + 1u + pubs, (int)(pubs & 1), pl.team, alpha, beta);
         }
         __syncthreads();   // LDS is free for the next unit
+        if (CUT && gave_up) run_poison<P>(a, g, tile);
       }
       shape = -1;
       team_barrier();
