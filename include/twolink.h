@@ -189,9 +189,10 @@ int tl_version(void);
  *                                    own) the
  *                                    one that runs of fewer than four steps use
  *   TL_LOG=1                         print autotuning candidates to stderr
- *   TL_FAULT=alloc|launch|exchange|wait
+ *   TL_FAULT=alloc|launch|exchange|team|wait
  *                                    make internal allocations or launches fail, or the
- *                                    clearing of whole-run launches' memory, or the waits
+ *                                    clearing of whole-run launches' memory; make them run
+ *                                    with incomplete teams of workgroups, or the waits
  *                                    between their workgroups run out at once (read at
  *                                    tl_create; exercises error paths)
  *   TL_TUNE_CACHE=<path>             a JSON file of autotuning results: read at tl_create,

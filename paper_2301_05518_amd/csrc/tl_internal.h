@@ -166,6 +166,7 @@ constexpr int kMaxRunGrid = 8192;
 struct RunCtl {
   alignas(128) uint32_t epoch;
   alignas(128) uint32_t next_share;
+  alignas(128) uint32_t full;  // teams that closed with all their members
   alignas(128) uint32_t finished;
   RunTeam team[kMaxRunTeams];
   uint32_t xcc[kMaxRunGrid];   // [team][rank]: the XCD of each workgroup
@@ -176,6 +177,7 @@ struct RunArgs {
   RunCtl* ctl;
   char* scratch;          // exchange words: [team][2][RHS word][team_size * np] of 16 bytes
   uint32_t* fail;         // host-visible: set when a wait ran out
+  int32_t patience;       // looks (0.5 us each) of a team's first member for the others before it closes the team
   int32_t spins;          // polls of a halo word before its wait is given up (kSpinLimit)
   const char* in;
   char* out;

@@ -29,10 +29,17 @@
 //
 // Progress.  Nothing assumes that the whole grid is resident.  A team is made of workgroups
 // that run: each enrols when it starts, the first one closes the team when all expected
-// members have come or after about 2 ms, later ones leave.  A team that is smaller than
-// the unit's tile count runs the same exchange with several tiles per workgroup and the
-// two-links read from memory each step (run_slow).  Teams take their shares of the units from
-// a common counter.
+// members have come or after a wait in proportion to the launch (about what it should take),
+// later ones leave.  An incomplete team leaves too if complete ones can take its work; else it
+// runs the same exchange with several tiles per workgroup and the two-links read from memory
+// each step (run_slow).  Teams take their shares of the
+// units from a common counter.  Microseconds per run with 1 and with 16 CUs held by another
+// stream: with 2 ms of waiting, no leaving, and run_slow one RHS and neighbour at a time; now; and
+// the step kernels.  32^3 FP64 3 RHS, 40 steps: 548 and 1537; 300 and 1030; 2090.  64^3 FP32 6
+// RHS, 20 steps: 607 and 5265; 608 and 2140; 1000.  64^3 FP32 24 RHS, 60 steps: 29900 and 17500;
+// 5790 and 19900; 12000.  96^3 BF16 3 RHS (a team of most CUs), 20 steps: 10030 and 10360; 3710
+// and 3910; 990.  run_slow reads every neighbour from memory, so where every team lacks a member
+// and the lattice is large it is behind the step kernels.
 // Every wait is bounded; where one runs out the kernel sets *fail, leaves NaNs in the results
 // of the tile concerned (in run_slow: takes them for the words that did not come), and ends.
 //
@@ -211,12 +218,16 @@ __device__ __forceinline__ void lds_barrier() {
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 constexpr uint32_t kTeamClosed = 0x40000000u;
-constexpr int kEnrolSpins = 4000;        // about 2 ms of the leader's wait for its team
+constexpr uint32_t kTeamAway = 0x20000000u;   // size of a team that leaves the work to others
+// An incomplete team leaves its shares to the complete ones if those then take at most this many
+// each: about what a share costs an incomplete team more (run_slow).
+constexpr uint32_t kAwayShares = 3;
 
 // Where a workgroup stands: its team and its place there; `expect` workgroups of the grid
 // belong to the team.  Workgroups are dispatched round-robin over the XCDs, so a team of up
 // to a grid's workgroups per XCD sits on one XCD (its exchange then stays in one L2), a
-// larger one on neighbouring XCDs; only speed depends on that.
+// larger one on neighbouring XCDs, in equal parts, so that the workgroups it does not need are
+// spare on each of them; only speed depends on that.
 struct RunPlace {
   int team, rank, expect;
 };
@@ -229,9 +240,9 @@ __device__ __forceinline__ RunPlace run_place(int team_size) {
   }
   int xpt = 2;
   while (xpt < kXcds && xpt * per < team_size) xpt *= 2;
-  const int r = (k % xpt) * per + j;
-  const int expect = min(team_size, xpt * per);
-  return {k / xpt, r < expect ? r : 1 << 20, expect};
+  const int expect = min(team_size, xpt * per), part = (expect + xpt - 1) / xpt;
+  const int r = (k % xpt) * part + j;
+  return {k / xpt, j < part && r < expect ? r : 1 << 20, expect};
 }
 
 // A tile of a unit: origin and extent in cell coordinates.
@@ -276,91 +287,145 @@ __device__ __forceinline__ void run_load_w(bool w12, const char* b, int64_t Vp, 
 // One unit by a team smaller than its tile count: member `me` of `size` takes the tiles me,
 // me + size, ... of every step in turn; vectors live in the scratch words, two-links are read
 // each step.  Every tile of a step is published before any of the next, so no wait is circular.
+// A step costs the latencies of its loads, so a direction's links and the words of all RHS are
+// requested together (RC of them at a time, and FP64 one neighbour's, as registers allow).
 template <int P, int R>
 __device__ void run_slow(const RunArgs& a, const RunUnit& g, int me, int size, uint32_t tag0, int par0, int team,
                          typename Fmt<P>::real alpha, typename Fmt<P>::real beta) {
   using real = typename Fmt<P>::real;
   using X = Exch<P>;
+  constexpr int NW = X::NW, RC = R == 4 ? 2 : P == F64 && R == 3 ? 1 : R;
   const int sub = uniform((int)threadIdx.x / a.np), i = (int)threadIdx.x - sub * a.np;
   const int n_tiles = g.t[0] * g.t[1] * g.t[2], bvol = g.b[0] * g.b[1] * g.b[2];
   const int slots = a.team_size * a.np;
-  const int64_t plane = (int64_t)a.subs * R * X::NW * slots * 16;
+  const int64_t plane = (int64_t)a.subs * R * NW * slots * 16;
   char* const base = a.scratch + team * 2 * plane;
-  auto scratch_plane = [&](int s) {
-    return __builtin_amdgcn_make_buffer_rsrc(base + ((par0 + s) & 1) * plane, 0, (int)plane, 0x00027000);
-  };
   bool dead = false;
+  int rr0 = 0;   // first of the RHS in hand
   for (int s = -1; s < a.n_steps; s++) {   // s = -1 publishes the input
+    const uint32_t tag = tag0 + (uint32_t)s;
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(base + ((par0 + s) & 1) * plane, 0, (int)plane, 0x00027000);
+    const __amdgpu_buffer_rsrc_t ws = __builtin_amdgcn_make_buffer_rsrc(base + ((par0 + s + 1) & 1) * plane, 0, (int)plane, 0x00027000);
+    auto request = [&](int slot, int r, v4u(&w)[NW]) {
+#pragma unroll
+      for (int q = 0; q < NW; q++)
+        w[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, slot * 16, ((rr0 + r) * NW + q) * slots * 16, kDeviceScope);
+    };
+    auto request_all = [&](int slot, v4u(&w)[RC][NW]) {
+#pragma unroll
+      for (int r = 0; r < RC; r++) request(slot, r, w[r]);
+    };
+    auto settle = [&](int slot, v4u(&w)[RC][NW]) {
+      for (int spin = 0;; spin++) {
+        bool late = false, miss[RC];
+#pragma unroll
+        for (int r = 0; r < RC; r++) {
+          miss[r] = false;
+#pragma unroll
+          for (int q = 0; q < NW; q++) miss[r] = miss[r] || w[r][q].w != tag;
+          late = late || miss[r];
+        }
+        if (!late) break;
+        const bool give_up = dead || spin >= a.spins;
+        if (give_up && !dead) run_failed(a.fail);
+        dead = dead || give_up;
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int r = 0; r < RC; r++) {
+          if (!miss[r]) continue;
+          if (!give_up) request(slot, r, w[r]);
+#pragma unroll
+          for (int q = 0; q < NW; q++) w[r][q] = give_up ? exch_nan() : w[r][q];
+        }
+        if (give_up) break;
+      }
+    };
+    auto vector = [&](const v4u(&w)[NW], real(&v)[6]) {
+      uint32_t e[X::ND];
+      exch_dwords<P>(w, e);
+      X::decode(e, v);
+    };
     for (int tile = me; tile < n_tiles; tile += size) {
       const RunTile tl = run_tile(g, tile);
       const int lx = i % g.b[0], lyz = i / g.b[0], ly = lyz % g.b[1], lz = lyz / g.b[1];
       if (i >= bvol || lx >= tl.e[0] || ly >= tl.e[1] || lz >= tl.e[2]) continue;
       const int cx = tl.o[0] + lx, cy = tl.o[1] + ly, cz = tl.o[2] + lz;
-      const int64_t site = run_site(g, a.hop, cx, cy, cz);
+      const int site = run_site(g, a.hop, cx, cy, cz);
       const int own = tile * a.np + i;
-      const uint32_t tag = tag0 + (uint32_t)s;
-      for (int r = 0; r < R; r++) {
-        const int rr = sub * R + r;
-        const int64_t off = g.psi_off + (int64_t)min(rr, g.nr - 1) * g.rhs_stride;
-        const int q0 = rr * X::NW;
-        uint32_t d[X::ND];
+#pragma nounroll
+      for (rr0 = sub * R; rr0 < (sub + 1) * R; rr0 += RC) {
+        auto publish = [&](int r, const uint32_t(&d)[X::ND]) {
+#pragma unroll
+          for (int q = 0; q < NW; q++)
+            exch_store<kDeviceScope>(exch_word<P>(d, q, tag + 1), ws, (own + ((rr0 + r) * NW + q) * slots) * 16);
+        };
         if (s < 0) {
-          X::load(a.in + off, g.Vp, site, d);
-        } else {
-          auto fetch = [&](int slot, real(&v)[6]) {
-            const __amdgpu_buffer_rsrc_t rs = scratch_plane(s);
-            v4u w[X::NW];
-            int spin = 0;
-            while (true) {
-              bool ok = true;
-#pragma unroll
-              for (int q = 0; q < X::NW; q++)
-                w[q] = __builtin_amdgcn_raw_buffer_load_b128(rs, slot * 16, (q0 + q) * slots * 16, kDeviceScope);
-              asm volatile("" ::: "memory");
-#pragma unroll
-              for (int q = 0; q < X::NW; q++) ok = ok && w[q].w == tag;
-              if (ok) break;
-              if (dead || ++spin > a.spins) {
-                if (!dead) run_failed(a.fail);
-                dead = true;
-#pragma unroll
-                for (int q = 0; q < X::NW; q++) w[q] = exch_nan();
-                break;
-              }
-            }
-            uint32_t e[X::ND];
-            exch_dwords<P>(w, e);
-            X::decode(e, v);
-          };
-          real acc[6], v[6], m[18];
-#pragma unroll
-          for (int c = 0; c < 6; c++) acc[c] = (real)0;
-          for (int mu = 0; mu < 3; mu++) {
-            const int dx = mu == 0, dy = mu == 1, dz = mu == 2;
-            const int fx = ring(cx + dx, g.c[0]), fy = ring(cy + dy, g.c[1]), fz = ring(cz + dz, g.c[2]);
-            const int bx = ring(cx - dx, g.c[0]), by = ring(cy - dy, g.c[1]), bz = ring(cz - dz, g.c[2]);
-            const char* W = g.W + mu * g.w_mu_stride;
-            run_load_w<P>(a.w12, W, g.Vp, site, m);
-            fetch(run_slot(g, a.np, fx, fy, fz), v);
-            mv_acc(m, v, acc);
-            run_load_w<P>(a.w12, W, g.Vp, run_site(g, a.hop, bx, by, bz), m);
-            fetch(run_slot(g, a.np, bx, by, bz), v);
-            mdv_acc(m, v, acc);
+          for (int r = 0; r < RC; r++) {
+            uint32_t d[X::ND];
+            X::load(a.in + g.psi_off + (int64_t)min(rr0 + r, g.nr - 1) * g.rhs_stride, g.Vp, site, d);
+            publish(r, d);
           }
-          fetch(own, v);
+          continue;
+        }
+        real acc[RC][6], v[6];
+#pragma unroll
+        for (int r = 0; r < RC; r++)
+#pragma unroll
+          for (int c = 0; c < 6; c++) acc[r][c] = (real)0;
+        auto add = [&](const real(&m)[18], const v4u(&w)[RC][NW], bool forward) {
+#pragma unroll
+          for (int r = 0; r < RC; r++) {
+            vector(w[r], v);
+            if (forward) mv_acc(m, v, acc[r]);
+            else mdv_acc(m, v, acc[r]);
+          }
+        };
+#pragma nounroll
+        for (int mu = 0; mu < 3; mu++) {
+          const int dx = mu == 0, dy = mu == 1, dz = mu == 2;
+          const int bx = ring(cx - dx, g.c[0]), by = ring(cy - dy, g.c[1]), bz = ring(cz - dz, g.c[2]);
+          const int fs = run_slot(g, a.np, ring(cx + dx, g.c[0]), ring(cy + dy, g.c[1]), ring(cz + dz, g.c[2]));
+          const int bs = run_slot(g, a.np, bx, by, bz);
+          const char* W = g.W + mu * g.w_mu_stride;
+          v4u f[RC][NW];
+          real m[18];
+          request_all(fs, f);
+          run_load_w<P>(a.w12, W, g.Vp, site, m);
+          if constexpr (P == F64) {
+            settle(fs, f);
+            add(m, f, true);
+            request_all(bs, f);
+            run_load_w<P>(a.w12, W, g.Vp, run_site(g, a.hop, bx, by, bz), m);
+            settle(bs, f);
+            add(m, f, false);
+          } else {
+            v4u b[RC][NW];
+            real mb[18];
+            request_all(bs, b);
+            run_load_w<P>(a.w12, W, g.Vp, run_site(g, a.hop, bx, by, bz), mb);
+            settle(fs, f);
+            add(m, f, true);
+            settle(bs, b);
+            add(mb, b, false);
+          }
+        }
+        v4u w[RC][NW];
+        request_all(own, w);
+        settle(own, w);
+#pragma unroll
+        for (int r = 0; r < RC; r++) {
+          vector(w[r], v);
           real o[6];
 #pragma unroll
-          for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[c], alpha * v[c]);
-          if (s + 1 == a.n_steps) {
-            if (rr < g.nr) Fmt<P>::template store_v<real, false>(a.out + off, g.Vp, site, o);
-            continue;
+          for (int c = 0; c < 6; c++) o[c] = fma_(beta, acc[r][c], alpha * v[c]);
+          if (s + 1 < a.n_steps) {
+            uint32_t d[X::ND];
+            X::encode(o, d);
+            publish(r, d);
+          } else if (rr0 + r < g.nr) {
+            Fmt<P>::template store_v<real, false>(a.out + g.psi_off + (int64_t)(rr0 + r) * g.rhs_stride, g.Vp, site, o);
           }
-          X::encode(o, d);
         }
-        const __amdgpu_buffer_rsrc_t ws = scratch_plane(s + 1);
-#pragma unroll
-        for (int q = 0; q < X::NW; q++)
-          exch_store<kDeviceScope>(exch_word<P>(d, q, tag + 1), ws, (own + (q0 + q) * slots) * 16);
       }
     }
   }
@@ -710,14 +775,17 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
       }
       e = ctl_add(&tm->enrolled, 1u);
       if (e == 0) {
-        for (int k = 0; k < kEnrolSpins && ctl_load(&tm->enrolled) < (uint32_t)pl.expect; k++) __builtin_amdgcn_s_sleep(2);
+        for (int k = 0; k < a.patience && ctl_load(&tm->enrolled) < (uint32_t)pl.expect; k++) __builtin_amdgcn_s_sleep(2);
         size = __hip_atomic_fetch_or(&tm->enrolled, kTeamClosed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (size == (uint32_t)pl.expect) ctl_add(&a.ctl->full, 1u);
+        else if (ctl_load(&a.ctl->full) * kAwayShares >= (uint32_t)a.n_shares) size = kTeamAway;
         ctl_store(&tm->size, size);
       } else if (e < kTeamClosed) {
         for (int k = 0; k < kSpinLimit && (size = ctl_load(&tm->size)) == 0; k++) __builtin_amdgcn_s_sleep(1);
         if (size == 0) run_failed(a.fail);
       }
     }
+    if (size == kTeamAway) size = 0;
     sh[0] = size;
     sh[1] = size == (uint32_t)pl.expect ? (uint32_t)pl.rank : e;   // a full team's members take their places' tiles
     sh[2] = ctl_load(&a.ctl->epoch);
@@ -813,6 +881,7 @@ __global__ __launch_bounds__(run_max_threads(P)) void smear_run(RunArgs a, typen
   }
   if (threadIdx.x == 0) {
     ctl_store(&a.ctl->next_share, 0);
+    ctl_store(&a.ctl->full, 0);
     ctl_store(&a.ctl->finished, 0);
     ctl_store(&a.ctl->epoch, epoch + (uint32_t)a.n_units * (uint32_t)a.n_steps + 1u);
   }

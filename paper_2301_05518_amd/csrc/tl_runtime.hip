@@ -57,6 +57,7 @@ struct tl_ctx {
   bool fault_alloc = false;   // TL_FAULT=alloc: internal allocations report failure
   bool fault_launch = false;  // TL_FAULT=launch: launches report failure without running
   bool fault_exchange = false;  // TL_FAULT=exchange: memory of whole-run launches cannot be cleared
+  bool fault_team = false;      // TL_FAULT=team: whole-run launches run with the teams that are there at once
   bool fault_wait = false;    // TL_FAULT=wait: whole-run launches give up a halo word that is not there at once
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
@@ -936,6 +937,8 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.w12 = tl::is_w12(p->prec);
     for (int done = 0; done < p->n_steps; done += a.n_steps, a.in = out) {
       a.n_steps = std::min(t.run.steps, p->n_steps - done);
+      // the launch's time at 3 us per unit-step and share, between 100 us and 2 ms
+      a.patience = c->fault_team ? 0 : (int)std::clamp<int64_t>(6 * (int64_t)a.n_steps * ((a.n_units + a.n_shares - 1) / a.n_shares), 200, 4000);
       TL_TRY(launch(c, "smearing run", [&] { return tl::launch_run(tl::vprec(p->prec), t.run.cfg, a, p->alpha, p->beta, s); }));
     }
     return TL_OK;
@@ -1413,6 +1416,7 @@ int tl_create(tl_ctx** out, int device, void* stream) {
       c->fault_alloc = strcmp(fl, "alloc") == 0;
       c->fault_launch = strcmp(fl, "launch") == 0;
       c->fault_exchange = strcmp(fl, "exchange") == 0;
+      c->fault_team = strcmp(fl, "team") == 0;
       c->fault_wait = strcmp(fl, "wait") == 0;
     }
     if (device == -1) {
