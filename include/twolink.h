@@ -19,7 +19,11 @@
  *   crosses this interface.
  * - Asynchrony: device work is queued on the context's stream and the call
  *   returns without waiting, unless stated otherwise.  Errors raised by the
- *   device afterwards surface at tl_sync() or at a later call.
+ *   device afterwards surface at tl_sync() or at a later call.  Where several
+ *   contexts of a process use one device, their whole-run launches (step
+ *   variant 9) that do not fit on the chip together take turns: a context's
+ *   stream waits (through an event) for such launches queued earlier by
+ *   others, except in a graph the caller captures.
  * - Ownership: the caller owns every buffer passed in (gauge field, two-link
  *   field, colour-vector fields, outputs).  The library never frees them and
  *   keeps no pointer to them after the call returns, except that a plan

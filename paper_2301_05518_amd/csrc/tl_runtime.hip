@@ -12,7 +12,9 @@
 #include <fstream>
 #include <list>
 #include <map>
+#include <mutex>
 #include <new>
+#include <optional>
 #include <sstream>
 #include <string>
 #include <utility>
@@ -47,6 +49,13 @@ struct RunMem {
   size_t bytes = 0;   // of scratch
 };
 
+// The contexts on one device, for the order of their whole-run launches (see RunTurn).
+struct RunLane {
+  std::mutex m;
+  std::vector<tl_ctx*> ctxs;
+  uint64_t seq = 0;   // launches recorded
+};
+
 struct tl_ctx {
   int device = -1;
   hipStream_t stream = nullptr;
@@ -74,6 +83,12 @@ struct tl_ctx {
   // workgroups ran out (kFailWords; plans beyond that share the last one)
   uint32_t* run_fail = nullptr;
   std::vector<char> fail_used;
+  // whole-run launches among several contexts (see RunTurn; guarded by the lane's mutex)
+  RunLane* lane = nullptr;
+  hipEvent_t run_event = nullptr;   // recorded after the latest one
+  uint64_t run_seq = 0;             // its number on the device, 0: none
+  uint64_t run_waited = 0;          // numbers up to this one that the context's stream waits for
+  double run_load = 0.0;            // share of the chip those that may still run take
   double* noalloc = nullptr;  // this device's fixed partial-sum area of tl_reduce_noalloc
   std::string noalloc_err;    // why it is missing (lookup failed at tl_create)
   std::map<std::string, Tuned> tune;       // tuned step tilings by workload key
@@ -250,6 +265,68 @@ void mem_put(tl_ctx* c, bool pooled, void* p, size_t bytes) {
   }
   (void)hipFree(p);
 }
+
+// Whole-run launches of several contexts take turns.  A team needs all its workgroups on the chip
+// at once, and launches that are dispatched together get a part of it each: every team then waits,
+// and runs incomplete (four contexts with 48^3 FP32 plans of 40 steps: 1550 us for a run each, 1460 with
+// step launches, 560 in turn; 48^3 BF16 12 RHS 4200, 3010, 1920).  So a context's stream waits for other contexts' launches, the
+// oldest first, until what may run beside its own fits (four 16^3 plans do).  Work of one context
+// is in order anyway, so a context that is alone on its device does nothing here; launches in a
+// graph the caller captured are not ordered.  Waits go to launches queued earlier only.
+RunLane& run_lane(int device) {
+  static std::mutex m;
+  static auto* lanes = new std::map<int, RunLane>();   // as long as the process: contexts may outlive static objects
+  std::lock_guard<std::mutex> lock(m);
+  return (*lanes)[device];
+}
+
+// Takes the turn of a launch that needs `load` of the chip, until it goes out of scope; the launch is
+// queued in between.
+class RunTurn {
+ public:
+  RunTurn(tl_ctx* c, double load) : c_(c), lane_(*c->lane), lock_(lane_.m), load_(load) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (lane_.ctxs.size() < 2 || !c->run_event ||
+        (c->stream && (hipStreamIsCapturing(c->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone))) {
+      lock_.unlock();
+      return;
+    }
+    std::vector<tl_ctx*> others;
+    for (tl_ctx* o : lane_.ctxs)
+      if (o != c && o->run_seq > c->run_waited && o->run_load > 0.0) {
+        others.push_back(o);
+        load += o->run_load;
+      }
+    std::sort(others.begin(), others.end(), [](const tl_ctx* a, const tl_ctx* b) { return a->run_seq < b->run_seq; });
+    for (tl_ctx* o : others) {
+      if (load <= 1.0) break;
+      if (hipStreamWaitEvent(c->stream, o->run_event, 0) != hipSuccess) (void)hipGetLastError();
+      c->run_waited = o->run_seq;
+      load -= o->run_load;
+    }
+  }
+  ~RunTurn() {
+    if (!lock_.owns_lock()) return;
+    if (hipEventRecord(c_->run_event, c_->stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return;
+    }
+    c_->run_seq = ++lane_.seq;
+    c_->run_load = std::max(c_->run_load, load_);
+  }
+  // The context's stream is idle.
+  static void idle(tl_ctx* c) {
+    if (!c->run_event) return;
+    std::lock_guard<std::mutex> lock(c->lane->m);
+    c->run_load = 0.0;
+  }
+
+ private:
+  tl_ctx* c_;
+  RunLane& lane_;
+  std::unique_lock<std::mutex> lock_;
+  double load_;
+};
 
 // Queue one library launch; TL_FAULT=launch makes it fail before anything is queued.
 template <class F>
@@ -837,6 +914,10 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
     std::memset(h, 0, kFailWords * sizeof(uint32_t));
     c->run_fail = static_cast<uint32_t*>(h);
   }
+  if (!c->run_event && hipEventCreateWithFlags(&c->run_event, hipEventDisableTiming) != hipSuccess) {
+    (void)hipGetLastError();
+    c->run_event = nullptr;   // without it the context's launches are not ordered
+  }
   if (!p->fail) {
     const size_t k = std::find(c->fail_used.begin(), c->fail_used.end() - 1, 0) - c->fail_used.begin();
     c->fail_used[k] = 1;
@@ -967,6 +1048,12 @@ int plan_step(tl_plan* p, hipStream_t s, int parity, int g, int k) {
 // neighbours get it through the exchange words), and read before anything is written.
 bool plan_flips(const tl_plan* p) {
   return (p->tile.cfg.variant == 8 ? p->n_steps / 2 + (p->n_steps & 1) : p->n_steps) & 1;
+}
+
+// The share of every CU that a whole-run launch takes (registers by its waves, LDS).
+double run_load(const RunShape& r, int prec) {
+  const double waves = (double)(r.np * r.subs + 64 * r.cfg.fetch) / tl::run_max_threads(tl::vprec(prec));
+  return std::max(waves, (double)r.cfg.lds / (160 * 1024));
 }
 
 // Queue the n steps starting from buffer `parity` on stream s.
@@ -1374,6 +1461,7 @@ bool plan_free(tl_plan* p) {
     DeviceGuard dg(p->ctx->device);
     tl_ctx* c = p->ctx;
     (void)hipStreamSynchronize(c->stream);
+    RunTurn::idle(c);
     failed = fail_taken(p->fail);
     for (auto& g : p->graph)
       if (g) (void)hipGraphExecDestroy(g);
@@ -1459,10 +1547,15 @@ int tl_create(tl_ctx** out, int device, void* stream) {
         (void)hipGetLastError();
       }
     }
-    c->device = device;
     c->stream = static_cast<hipStream_t>(stream);
     c->n_cu = prop.multiProcessorCount;
     c->arch = prop.gcnArchName;
+    c->lane = &run_lane(device);
+    {
+      std::lock_guard<std::mutex> lock(c->lane->m);
+      c->lane->ctxs.push_back(c);
+    }
+    c->device = device;
     *out = c;
     return TL_OK;
   } catch (...) {   // a half-built context is released; *out stays NULL
@@ -1483,6 +1576,10 @@ int tl_destroy(tl_ctx* c) {
       if (c->scratch) (void)hipFree(c->scratch);
       mem_drain(c);
       if (c->run_fail) (void)hipHostFree(c->run_fail);
+      std::lock_guard<std::mutex> lock(c->lane->m);
+      auto& all = c->lane->ctxs;
+      all.erase(std::remove(all.begin(), all.end(), c), all.end());
+      if (c->run_event) (void)hipEventDestroy(c->run_event);
     }
     delete c;
     return TL_OK;
@@ -1521,6 +1618,7 @@ int tl_sync(tl_ctx* c) {
     TL_ON_DEVICE(c);
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     HIP_TRY(c, hipGetLastError());
+    RunTurn::idle(c);
     bool failed = false;
     if (c->run_fail)
       for (size_t k = 0; k < kFailWords; k++) failed = fail_taken(c->run_fail + k) || failed;
@@ -1846,6 +1944,8 @@ int tl_plan_run(tl_plan* p) {
     TL_ON_DEVICE(c);
     if (fail_taken(p->fail)) return run_failure(c);
     TL_TRY(plan_prepare(p));
+    std::optional<RunTurn> turn;
+    if (p->tile.cfg.variant == 9) turn.emplace(c, run_load(p->tile.run, p->prec));
     // a tuned run that is one launch needs no graph
     if ((p->flags & TL_GRAPH) && !(p->tile.cfg.variant == 9 && (p->flags & TL_AUTOTUNE))) {
       TL_TRY(plan_capture(p, p->cur));
