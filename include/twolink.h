@@ -322,7 +322,7 @@ int tl_plan_load(tl_plan *plan);
 /* n_steps smearing steps on the resident buffer (eq. tlSmear applied n_steps times; with a
    two-step tiling, n_steps / 2 launches plus one one-step launch when n_steps is odd; with a
    whole-run tiling one launch, which plans of four or more steps without TL_AUTOTUNE, TL_PLAIN
-   and TL_ONE_STEP use by default where their lattices fit).  A whole-run launch whose wait for
+   and TL_ONE_STEP use by default where their lattices fit and it should be the faster).  A whole-run launch whose wait for
    another workgroup ran out (after several seconds) leaves NaNs in the fields, and TL_ERR_HIP
    reports it once, from the first of these calls that follows its end: tl_plan_run, _store,
    _reduce, _time (nothing is queued then) and _destroy (the plan is released all the same) on that

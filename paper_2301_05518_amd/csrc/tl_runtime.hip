@@ -1356,10 +1356,54 @@ bool tile_override(Tuned* tu) {
   return e && parse_tuned(e, 4, tu);
 }
 
+// Microseconds of a plan's run in one launch, and in n launches of the direct kernel: estimates for
+// default_run, fitted to 4500 measured points (4^3 to 96^3, odd extents, 1 to 96 slices of 1 to 4
+// RHS, every format, 4 to 32 steps).  A whole-run launch costs a few us, each round of units its
+// link loads and then a step for every step: both grow with the waves per SIMD and the RHS per
+// thread, and for teams over several XCDs.  A direct launch costs what its bytes or its arithmetic
+// take, and never less than the chain of a tile's loads and products.
+double run_estimate(const tl_plan* p, const RunShape& r, bool* one_round) {
+  const bool f64 = tl::vprec(p->prec) == tl::F64;
+  const double w = r.cfg.width;
+  double us = 6.0;
+  int rounds = 0;
+  for (size_t i = 0, j; i < r.units.size(); i = j) {
+    const tl::RunUnit& g = r.units[i];
+    for (j = i; j < r.units.size() && r.units[j].shape == g.shape; j++) {}
+    const int tiles = g.t[0] * g.t[1] * g.t[2], at_once = g.span / tiles;
+    const int k = ((int)(j - i) + r.n_shares * at_once - 1) / (r.n_shares * at_once);
+    const int waves = ((g.b[0] * g.b[1] * g.b[2] + 63) / 64 * r.subs + 3) / 4;
+    const bool across = g.span > r.cfg.grid / 8;
+    double step = f64 ? 0.7 + 1.2 * w + 0.5 * waves + (across ? 1.8 : 0.0) : 0.5 + w * (0.5 + 0.1 * waves) + (across ? 0.5 : 0.0);
+    double once = 4.0 + 3.0 * waves + 0.8 * w + (across ? 3.0 : 0.0);
+    if (tiles == 1) {   // nothing to exchange
+      step *= 0.7;
+      once = 4.0 * waves;
+    }
+    us += k * (once + p->n_steps * step);
+    rounds += k;
+  }
+  *one_round = rounds == 1;
+  return us;
+}
+double direct_estimate(const tl_plan* p) {
+  const int vp = tl::vprec(p->prec);
+  const double w = p->width;
+  const double chain = vp == tl::F64 ? 5.0 + 9.0 * w : 4.5 + 2.5 * w;
+  const double tbs = vp == tl::F64 ? 4.0 : 4.6;
+  const double tflops = vp == tl::F64 ? 5.5 - 0.5 * w : vp == tl::F32 ? 15.0 : vp == tl::F16S ? 19.0 : 28.0;
+  const double work = std::max(p->info.bytes_per_step / tbs, p->info.flops_per_step / tflops) * 1e-6;
+  return p->n_steps * std::max(chain, 0.5 * chain + work);
+}
+
 // The tiling of a plan that is neither tuned nor fixed: all steps in one launch where the cells
 // fit teams of one XCD (up to 32 workgroups) or a few, else the direct kernel, one step per
-// launch.  A launch costs about 5 us, the whole-run kernel 1 to 4 us a step plus about 10, so it
-// wins from four steps on (20 steps of 16^3 FP32: 30 instead of 320 us).  Team size: every unit
+// launch.  Where one round of units does all the work one launch was faster at every point measured
+// from four steps on (20 steps of 16^3 FP32 3 RHS: 50 instead of 350 us).  With several rounds of
+// few steps the link loads of each round can cost more than they save (4 steps of 96 slices of
+// 33x33x17 BF16 1 RHS: 368 instead of 202 us), so there the estimates decide: of the 4500 points
+// three then take longer than with the other choice's time, by 17% at most (95, by up to 2.2
+// times, with one launch for all).  Team size: every unit
 // at once if the chip has room, a wave or more of sites per tile; FP64 threads hold one RHS
 // where that fits (its registers are full with one).
 bool default_run(const tl_plan* p, StepConfig* cfg) {
@@ -1383,7 +1427,10 @@ bool default_run(const tl_plan* p, StepConfig* cfg) {
     for (int split : {1, 0})
       if (split == (tl::vprec(p->prec) == tl::F64 && p->width > 1) || (!split && tl::vprec(p->prec) == tl::F64)) {
         *cfg = {9, 512, team, 0, 0, split, 0};
-        if (!make_run(p, *cfg, &r)) return true;
+        if (make_run(p, *cfg, &r)) continue;
+        bool one_round = false;
+        const double us = run_estimate(p, r, &one_round);
+        return one_round || us < direct_estimate(p);
       }
   return false;
 }
@@ -1884,7 +1931,6 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
           rc = fail(c, TL_ERR_HIP, "hipMemsetAsync failed");
     }
     if (rc == TL_OK) rc = describe_tiling(p, p->tile.cfg, &p->tile);
-    if (rc == TL_OK && !(flags & TL_AUTOTUNE)) rc = prepare_untuned(p);   // a tuned one: its first run
     if (rc != TL_OK) return rc;
     // info
     tl_plan_info& in = p->info;
@@ -1903,6 +1949,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     in.bytes_per_step = bytes;
     in.flops_per_step = flops;
     in.resident_bytes = (int64_t)(p->buf_cap[0] + p->buf_cap[1] + p->tables_cap);
+    if (!(flags & TL_AUTOTUNE)) TL_TRY(prepare_untuned(p));   // a tuned one: its first run
     release.p = nullptr;
     *out = p;
     return TL_OK;
