@@ -1365,26 +1365,29 @@ bool tile_override(Tuned* tu) {
 double run_estimate(const tl_plan* p, const RunShape& r, bool* one_round) {
   const bool f64 = tl::vprec(p->prec) == tl::F64;
   const double w = r.cfg.width;
-  double us = 6.0;
-  int rounds = 0;
-  for (size_t i = 0, j; i < r.units.size(); i = j) {
-    const tl::RunUnit& g = r.units[i];
-    for (j = i; j < r.units.size() && r.units[j].shape == g.shape; j++) {}
-    const int tiles = g.t[0] * g.t[1] * g.t[2], at_once = g.span / tiles;
-    const int k = ((int)(j - i) + r.n_shares * at_once - 1) / (r.n_shares * at_once);
-    const int waves = ((g.b[0] * g.b[1] * g.b[2] + 63) / 64 * r.subs + 3) / 4;
-    const bool across = g.span > r.cfg.grid / 8;
-    double step = f64 ? 0.7 + 1.2 * w + 0.5 * waves + (across ? 1.8 : 0.0) : 0.5 + w * (0.5 + 0.1 * waves) + (across ? 0.5 : 0.0);
-    double once = 4.0 + 3.0 * waves + 0.8 * w + (across ? 3.0 : 0.0);
-    if (tiles == 1) {   // nothing to exchange
-      step *= 0.7;
-      once = 4.0 * waves;
+  double longest = 0.0;
+  *one_round = true;
+  for (int share = 0; share < r.n_shares; share++) {   // a team takes every n_shares-th unit
+    double us = 6.0;
+    int rounds = 0;
+    for (size_t u = share; u < r.units.size(); u += r.n_shares) {
+      const tl::RunUnit& g = r.units[u];
+      if (g.first != 0) continue;   // runs beside the one before
+      const int waves = ((g.b[0] * g.b[1] * g.b[2] + 63) / 64 * r.subs + 3) / 4;
+      const bool across = g.span > r.cfg.grid / 8;
+      double step = f64 ? 0.7 + 1.2 * w + 0.5 * waves + (across ? 1.8 : 0.0) : 0.5 + w * (0.5 + 0.1 * waves) + (across ? 0.5 : 0.0);
+      double once = 4.0 + 3.0 * waves + 0.8 * w + (across ? 3.0 : 0.0);
+      if (g.t[0] * g.t[1] * g.t[2] == 1) {   // nothing to exchange
+        step *= 0.7;
+        once = 4.0 * waves;
+      }
+      us += once + p->n_steps * step;
+      rounds++;
     }
-    us += k * (once + p->n_steps * step);
-    rounds += k;
+    longest = std::max(longest, us);
+    *one_round = *one_round && rounds == 1;
   }
-  *one_round = rounds == 1;
-  return us;
+  return longest;
 }
 double direct_estimate(const tl_plan* p) {
   const int vp = tl::vprec(p->prec);

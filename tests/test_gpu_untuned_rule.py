@@ -53,17 +53,28 @@ CASES = [
 
 @pytest.mark.parametrize("L,per,prec,n,flags,variant", CASES)
 def test_rule(torch, ctx, monkeypatch, L, per, prec, n, flags, variant):
-    import paper_2301_05518_amd as tl
     j = job(torch, ctx, L, per, prec)
     src = j.psi.clone()
+    check(ctx, torch, monkeypatch, [j], [src], prec, n, flags, variant)
+
+
+def test_batch_of_one_round(torch, ctx, monkeypatch):
+    """Units of several lattices, each on a team of its own: one round, four steps suffice."""
+    jobs = [job(torch, ctx, L, 2, "f16s") for L in ((32, 24, 20, 1), (14, 9, 16, 1), (4, 6, 4, 2))]
+    check(ctx, torch, monkeypatch, jobs, [j.psi.clone() for j in jobs], "f16s", 4, 0, 9)
+
+
+def check(ctx, torch, monkeypatch, jobs, srcs, prec, n, flags, variant):
+    import paper_2301_05518_amd as tl
     outs = []
     for tile in (None, "0,64,1,0"):
         if tile:
             monkeypatch.setenv("TL_TILE", tile)
-        j.psi.copy_(src)
-        plan = ctx.plan([j], n, 0.1 * n, prec, getattr(tl, flags) if flags else 0)
+        for j, src in zip(jobs, srcs):
+            j.psi.copy_(src)
+        plan = ctx.plan(jobs, n, 0.1 * n, prec, getattr(tl, flags) if flags else 0)
         if not tile:
-            log(f"{L} x {per} {prec} n={n} {flags}: variant {plan.info()['variant']}")
+            log(f"{[j.L for j in jobs]} {prec} n={n} {flags}: variant {plan.info()['variant']}")
             assert plan.info()["variant"] == variant       # ready when created
         plan.load()
         plan.run()
@@ -71,5 +82,5 @@ def test_rule(torch, ctx, monkeypatch, L, per, prec, n, flags, variant):
         ctx.sync()
         assert plan.info()["variant"] == (0 if tile else variant)
         plan.close()
-        outs.append(j.psi.clone())
-    assert torch.equal(outs[0], outs[1])
+        outs.append([j.psi.clone() for j in jobs])
+    assert all(torch.equal(a, b) for a, b in zip(*outs))
