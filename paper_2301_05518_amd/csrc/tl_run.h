@@ -182,10 +182,12 @@ __device__ __forceinline__ void rec_get(const unsigned char* p, int r, double (&
 
 constexpr int kDeviceScope = 16;   // sc1 in a buffer instruction's cache policy
 
-// The word's offset goes into the instruction's vector offset alone.  With part of it in a
-// scalar register the compiler (which then sees no hazard) reuses the data registers in the
-// next instruction, and under load a store has been seen to write the next word's payload
-// under this word's tag, four lanes at a time.
+// The word's offset goes into the instruction's vector offset alone.  A store of 128 bits reads its
+// data registers after it is issued, and what overwrites them needs a wait state, which the
+// compiler inserts only where the scalar offset is not a register.  With part of the offset in one
+// the data registers were reused in the next instruction, and under load a store has been seen to
+// write the next word's payload under this word's tag, four lanes at a time.
+// tests/test_run_stores.py looks for both in the built code.
 template <int Scope>
 __device__ __forceinline__ void exch_store(v4u w, __amdgpu_buffer_rsrc_t rs, int off) {
   __builtin_amdgcn_raw_buffer_store_b128(w, rs, off, 0, Scope);
