@@ -1369,7 +1369,7 @@ double run_estimate(const tl_plan* p, const RunShape& r, bool* one_round) {
   *one_round = true;
   for (int share = 0; share < r.n_shares; share++) {   // a team takes every n_shares-th unit
     double us = 6.0;
-    int rounds = 0;
+    int rounds = 0, shape = -1;
     for (size_t u = share; u < r.units.size(); u += r.n_shares) {
       const tl::RunUnit& g = r.units[u];
       if (g.first != 0) continue;   // runs beside the one before
@@ -1381,6 +1381,8 @@ double run_estimate(const tl_plan* p, const RunShape& r, bool* one_round) {
         step *= 0.7;
         once = 4.0 * waves;
       }
+      if (shape >= 0 && g.shape != shape) once += across ? 8.0 : 3.0;   // a team barrier
+      shape = g.shape;
       us += once + p->n_steps * step;
       rounds++;
     }
@@ -1406,7 +1408,7 @@ double direct_estimate(const tl_plan* p) {
 // few steps the link loads of each round can cost more than they save (4 steps of 96 slices of
 // 33x33x17 BF16 1 RHS: 368 instead of 202 us), so there the estimates decide: of the 4500 points
 // three then take longer than with the other choice's time, by 17% at most (95, by up to 2.2
-// times, with one launch for all).  Team size: every unit
+// times, with one launch for all), and two of 134 random batches of 1 to 24 lattices, by 33%.  Team size: every unit
 // at once if the chip has room, a wave or more of sites per tile; FP64 threads hold one RHS
 // where that fits (its registers are full with one).
 bool default_run(const tl_plan* p, StepConfig* cfg) {
