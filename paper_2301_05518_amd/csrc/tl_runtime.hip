@@ -676,6 +676,9 @@ int64_t plan_lds(const tl_plan* p, const StepConfig& cfg, const std::vector<Step
 // Runs of fewer steps use one launch per step: a whole-run launch reads every two-link twice
 // (once as the forward and once as the backward one of a site) before its first step.
 constexpr int kRunMinSteps = 4;
+// Steps the autotuner times of a whole run at most: what a run costs once is a few steps' time, and
+// 200 launches of all steps of a long run would take minutes.
+constexpr int kTuneSteps = 60;
 
 // Unit-steps of a whole-run launch per team at most; longer runs take several launches.  A member
 // without a tile waits for the others at the end of a team's share, and every wait of the kernel
@@ -993,10 +996,10 @@ int upload_tuned(tl_plan* p, const Tuned& tu) {
 }
 
 // One launch of tiling t over every group (batched) or over one group (plain mode, g >= 0),
-// from buffer `in` to buffer `out`: one step, two for variant 8, all for variant 9 (in launches of
-// at most run.steps steps, the later ones in place, see plan_flips).  k: index of the launch
+// from buffer `in` to buffer `out`: one step, two for variant 8, `steps` for variant 9 (in launches
+// of at most run.steps steps, the later ones in place, see plan_flips).  k: index of the launch
 // in its sequence (odd launches run reversed when the tiling flips).
-int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char* in, char* out, int g, int k) {
+int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char* in, char* out, int g, int k, int steps) {
   tl_ctx* c = p->ctx;
   if (t.cfg.variant == 9) {
     tl::RunArgs a{};
@@ -1016,8 +1019,8 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
     a.halo = t.run.halo;
     a.hop = tl::hop_of(p->prec);
     a.w12 = tl::is_w12(p->prec);
-    for (int done = 0; done < p->n_steps; done += a.n_steps, a.in = out) {
-      a.n_steps = std::min(t.run.steps, p->n_steps - done);
+    for (int done = 0; done < steps; done += a.n_steps, a.in = out) {
+      a.n_steps = std::min(t.run.steps, steps - done);
       // the launch's time at 3 us per unit-step and share, between 100 us and 2 ms
       a.patience = c->fault_team ? 0 : (int)std::clamp<int64_t>(6 * (int64_t)a.n_steps * ((a.n_units + a.n_shares - 1) / a.n_shares), 200, 4000);
       TL_TRY(launch(c, "smearing run", [&] { return tl::launch_run(tl::vprec(p->prec), t.run.cfg, a, p->alpha, p->beta, s); }));
@@ -1037,8 +1040,8 @@ int plan_launch(tl_plan* p, const tl_plan::Tiling& t, hipStream_t s, const char*
   });
 }
 
-int plan_step(tl_plan* p, hipStream_t s, int parity, int g, int k) {
-  return plan_launch(p, p->tile, s, p->buf[parity], p->buf[parity ^ 1], g, k);
+int plan_step(tl_plan* p, hipStream_t s, int parity, int g, int k, int steps = 1) {
+  return plan_launch(p, p->tile, s, p->buf[parity], p->buf[parity ^ 1], g, k, steps);
 }
 
 // Whether a run of the n steps ends in the other resident buffer: every step or two-step launch
@@ -1067,14 +1070,14 @@ int plan_enqueue(tl_plan* p, hipStream_t s, int parity) {
       }
     }
   } else if (p->tile.cfg.variant == 9) {
-    TL_TRY(plan_launch(p, p->tile, s, p->buf[parity], p->buf[plan_flips(p) ? parity ^ 1 : parity], -1, 0));
+    TL_TRY(plan_launch(p, p->tile, s, p->buf[parity], p->buf[plan_flips(p) ? parity ^ 1 : parity], -1, 0, p->n_steps));
   } else if (p->tile.cfg.variant == 8) {
     int q = parity;
     for (int k = 0; k < p->n_steps / 2; k++) {
       TL_TRY(plan_step(p, s, q, -1, k));
       q ^= 1;
     }
-    if (p->n_steps & 1) TL_TRY(plan_launch(p, p->single, s, p->buf[q], p->buf[q ^ 1], -1, 0));
+    if (p->n_steps & 1) TL_TRY(plan_launch(p, p->single, s, p->buf[q], p->buf[q ^ 1], -1, 0, 1));
   } else {
     int q = parity;
     for (int k = 0; k < p->n_steps; k++) {
@@ -1203,12 +1206,13 @@ int plan_autotune(tl_plan* p) {
   }
   // time reps launches of p->tile (after two untimed) for each timed group, then compare the
   // output with ref (have_ref false: keep it as ref instead); ms: per launch
+  const int whole = std::min(p->n_steps, kTuneSteps);
   auto trial = [&](bool have_ref, float* ms, bool* same, int warm = 2, int reps = 10) -> int {
     *ms = 0.0f;
     for (const auto& tw : timed) {
-      for (int w = 0; w < warm; w++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, w));
+      for (int w = 0; w < warm; w++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, w, whole));
       (void)hipEventRecord(e0, c->stream);
-      for (int k = 0; k < reps; k++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, k));
+      for (int k = 0; k < reps; k++) TL_TRY(plan_step(p, c->stream, p->cur, tw.first, k, whole));
       (void)hipEventRecord(e1, c->stream);
       if (hipEventSynchronize(e1) != hipSuccess) return fail(c, TL_ERR_HIP, "autotune timing failed");
       float t = 0.0f;
@@ -1260,8 +1264,8 @@ int plan_autotune(tl_plan* p) {
   if (rc == TL_OK && !cands2.empty()) {
     // reference: two launches of the one-step winner, buffer cur -> cur^1 -> ref
     rc = upload_tiling(p, best_cfg, &p->single);
-    if (rc == TL_OK) rc = plan_launch(p, p->single, c->stream, p->buf[p->cur], p->buf[p->cur ^ 1], -1, 0);
-    if (rc == TL_OK) rc = plan_launch(p, p->single, c->stream, p->buf[p->cur ^ 1], static_cast<char*>(ref), -1, 1);
+    if (rc == TL_OK) rc = plan_launch(p, p->single, c->stream, p->buf[p->cur], p->buf[p->cur ^ 1], -1, 0, 1);
+    if (rc == TL_OK) rc = plan_launch(p, p->single, c->stream, p->buf[p->cur ^ 1], static_cast<char*>(ref), -1, 1, 1);
     float best2 = 1e30f;
     StepConfig best2_cfg{};
     for (size_t ci = 0; ci < cands2.size() && rc == TL_OK; ci++) {
@@ -1286,28 +1290,28 @@ int plan_autotune(tl_plan* p) {
     }
   }
   if (rc == TL_OK && !cands9.empty()) {
-    // whole-run launches (all n steps each), against n launches of the one-step winner from
-    // buffer to buffer.  The winner so far is timed over such a run too: launches that all read
+    // whole-run launches (all n steps each, up to kTuneSteps), against as many launches of the
+    // one-step winner from buffer to buffer.  The winner so far is timed over such a run too: launches that all read
     // one buffer find their input in the caches, those of a run do not.
     rc = upload_tiling(p, best_cfg, &p->single);
     if (rc == TL_OK && tu.cfg.variant == 8) rc = upload_tiling(p, tu.cfg, &p->tile);
     char* pair[2] = {p->buf[p->cur ^ 1], static_cast<char*>(ref)};
     auto sequence = [&](const tl_plan::Tiling& t, int launches) -> int {
       for (int k = 0; k < launches; k++)
-        TL_TRY(plan_launch(p, t, c->stream, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k));
+        TL_TRY(plan_launch(p, t, c->stream, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k, 1));
       return TL_OK;
     };
     for (int rep = 0; rep < 2 && rc == TL_OK; rep++) {
       (void)hipEventRecord(e0, c->stream);
-      rc = tu.cfg.variant == 8 ? sequence(p->tile, p->n_steps / 2) : sequence(p->single, p->n_steps);
+      rc = tu.cfg.variant == 8 ? sequence(p->tile, whole / 2) : sequence(p->single, whole);
       (void)hipEventRecord(e1, c->stream);
       float ms = 0.0f;
       if (rc == TL_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
         rc = fail(c, TL_ERR_HIP, "autotune timing failed");
-      best = ms / (tu.cfg.variant == 8 ? p->n_steps / 2 * 2 : p->n_steps);
+      best = ms / (tu.cfg.variant == 8 ? whole / 2 * 2 : whole);
     }
-    if (rc == TL_OK) rc = sequence(p->single, p->n_steps);
-    if (rc == TL_OK && (p->n_steps & 1) &&
+    if (rc == TL_OK) rc = sequence(p->single, whole);
+    if (rc == TL_OK && (whole & 1) &&
         hipMemcpyAsync(ref, pair[0], p->buf_bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
       rc = fail(c, TL_ERR_HIP, "autotune reference copy failed");
     float best9 = 1e30f;
@@ -1326,9 +1330,9 @@ int plan_autotune(tl_plan* p) {
       rc = trial(true, &ms, &same, 1, 3);
       if (rc != TL_OK) break;
       if (fail_taken(p->fail)) same = false;   // it gave up waiting: not a candidate
-      log(p->tile.cfg, ms / p->n_steps, same);
-      if (same && ms / p->n_steps < best9) {
-        best9 = ms / p->n_steps;
+      log(p->tile.cfg, ms / whole, same);
+      if (same && ms / whole < best9) {
+        best9 = ms / whole;
         best9_cfg = p->tile.cfg;
       }
     }

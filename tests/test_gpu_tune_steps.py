@@ -67,3 +67,19 @@ def test_older_cache_file(torch, monkeypatch, tmp_path):
     assert tuned(c, 20) == (9, (1, 0))
     c.close()
     assert json.loads(cache.read_text())[key].startswith("9,")
+
+
+def test_tuning_time_does_not_grow_with_the_steps(torch):
+    import time
+
+    import paper_2301_05518_amd as tl
+    took = {}
+    for n in (64, 20001):      # 200 launches of 20001 steps would take more than 4 s
+        c = tl.Context(0)
+        c.sync()
+        t0 = time.perf_counter()
+        assert tuned(c, n) == (9, (1, 0))
+        took[n] = time.perf_counter() - t0
+        c.close()
+    log(f"tuning took {took}")
+    assert took[20001] < 3 * took[64] + 0.5
