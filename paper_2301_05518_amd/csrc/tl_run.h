@@ -45,12 +45,13 @@
 //
 // Measured, microseconds per step with everything a run does once spread over its steps, before
 // (the tuned step kernels in a graph) and now: 8^3 FP64 1 RHS 5.2 -> 1.2; 32^3 FP64 3 RHS
-// 8.9 -> 4.0; 48^3 3 RHS FP32 11.1 -> 3.3, F16S 9.3 -> 3.6; 24^3 + 32^3 + 48^3 BF16 21 RHS
-// 24 -> 16.8; 64^3 FP32 24 RHS 104 -> 55.  At 64^3 the vector units issue 91% of the cycles the
-// kernel runs (1.46 M instructions of 4 cycles per SIMD in 6.41 M cycles), so what is left there
-// is the instruction count: 253 per site and RHS, the fetch waves' included, 222 of them FMAs.  A copy that does
-// not wait for its neighbours takes 41.5 instead of 50 us a step there, 3.0 instead of 3.3 at
-// 48^3 FP32, and 2.2 instead of 4.0 at 32^3 FP64, which is the one that the exchange bounds.
+// 8.9 -> 4.0; 48^3 3 RHS FP32 11.1 -> 3.4, F16S 9.3 -> 3.8; 24^3 + 32^3 + 48^3 BF16 21 RHS
+// 24 -> 18.4; 64^3 FP32 24 RHS 104 -> 51 to 55 (about 50 a step and 300 once).  At 64^3 the vector
+// units issue 92% of the cycles the kernel runs (1.45 M instructions of 4 cycles per SIMD in 6.27 M
+// cycles), so what is left there is the instruction count: 251 per site and RHS, the fetch waves'
+// included, 222 of them FMAs.  A copy that does not wait for its neighbours takes 41.5 instead of
+// 50 us a step there, 3.0 instead of 3.3 at 48^3 FP32, and 2.2 instead of 4.0 at 32^3 FP64, which is
+// the one that the exchange bounds.
 #pragma once
 
 #include <type_traits>
@@ -547,7 +548,7 @@ __device__ __forceinline__ void run_compute(const RunArgs& a, const RunUnit& g, 
     }
     // One kind of store per 128-byte cache line (eight slots): a line that holds both written-through
     // and held-back words costs a probe of its owner's L2 for every reader on another XCD (one-link
-    // 45x26x38 FP32 24 RHS: 41 us per step with mixed lines, 18 without).
+    // 45x26x38 FP32 24 RHS: 40.8 us per step with mixed lines, 16.5 without).
     const uint64_t away = __ballot(far && active);
     far = pub && active && ((away >> ((int)__lane_id() & ~7)) & 0xff) != 0;
     pub = pub && active && !far;
