@@ -276,7 +276,9 @@ int tl_pack_links(tl_ctx *ctx, const tl_geom *g, const void *U,
  *   in, out  device complex128 [Lz][Ly][Lx][3]; out must not overlap in
  * `in` is rounded to the storage precision first; the arithmetic is FP64 for
  * TL_F64 and FP32 otherwise; the result is rounded to the storage precision
- * and then widened to complex128.  One launch, no library memory.  With
+ * and then widened to complex128.  One launch, no library memory; for TL_F16S
+ * and TL_BF16 slices of more than 1200000 sites three launches on context
+ * scratch memory (not under stream capture then: TL_ERR_HIP).  With
  * TL_ONELINK in prec (W from tl_pack_links): the one-link Laplacian
  * nabla^2 = H - 6 of Sec. 2 instead.
  */

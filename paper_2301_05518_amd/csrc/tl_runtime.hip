@@ -1762,6 +1762,14 @@ int tl_pack_links(tl_ctx* c, const tl_geom* g, const void* U, const int32_t* sli
   }
 }
 
+// Slices up to this many sites take the Laplacian in one launch on the natural fields, which reads
+// each neighbour's 48 bytes; a larger one no longer finds most of them in the caches, and a field of
+// 16-bit vectors is then packed first.  us, one launch against pack, step and unpack: F16S 104^3
+// (1.1 M sites) 83 / 86, 112^3 122 / 94, 192^3 664 / 454; BF16 104^3 63 / 77, 112^3 97 / 86, 192^3
+// 536 / 419.  FP32 and FP64 fields stay ahead or level in one launch up to 47 M sites (256^3 1663 / 1651 and
+// 2699 / 3446).
+constexpr int64_t kLapNaturalSites = 1200000;
+
 int tl_laplacian(tl_ctx* c, const tl_geom* g, const void* W, const int32_t* w_slices, int n_w_slices, int prec,
                  int t, const void* in, void* out) {
   try {
@@ -1783,7 +1791,36 @@ int tl_laplacian(tl_ctx* c, const tl_geom* g, const void* W, const int32_t* w_sl
     const char* slice = static_cast<const char*>(W) + (int64_t)slot * 3 * Vp * tl::kWBytes[code];
     // Lap = alpha in + beta sum_hops: two-link -3/2, 1/4 (eq. tlLapl1); one-link -6, 1 (H - 6)
     const double la = tl::is_one(code) ? -6.0 : -1.5, lb = tl::is_one(code) ? 1.0 : 0.25;
-    return launch(c, "laplacian", [&] { return tl::launch_laplacian(code, slice, (int)Vp, g->L, in, out, la, lb, c->stream); });
+    const int vp = tl::vprec(code);
+    if ((vp != tl::F16S && vp != tl::BF16) || V3 <= kLapNaturalSites)
+      return launch(c, "laplacian", [&] { return tl::launch_laplacian(code, slice, (int)Vp, g->L, in, out, la, lb, c->stream); });
+    // pack, one step, unpack on context scratch (which a captured launch must not hold)
+    TL_TRY(need_eager(c, "tl_laplacian of a large slice"));
+    const size_t fb = align256((size_t)Vp * tl::kVBytes[vp]);
+    char* s = nullptr;
+    TL_TRY(ctx_scratch(c, 1024 + 2 * fb, &s));
+    const StepConfig cfg{0, 256, 4, 0, 0};
+    struct {
+      StepGroup g;
+      int64_t off0;
+    } tab{};
+    tab.g.W = slice;
+    tab.g.w_mu_stride = Vp * tl::kWBytes[code];
+    tab.g.Lx = g->L[0];
+    tab.g.Ly = g->L[1];
+    tab.g.Lz = g->L[2];
+    tab.g.Vp = (int32_t)Vp;
+    tab.g.nr = 1;
+    tab.g.n_xy_tiles = (int32_t)(((int64_t)g->L[0] * g->L[1] + cfg.block - 1) / cfg.block);
+    tab.g.n_z_tiles = (g->L[2] + cfg.tz - 1) / cfg.tz;
+    TL_TRY(upload(c, s, &tab, sizeof tab));
+    const StepGroup* gdev = reinterpret_cast<const StepGroup*>(s);
+    const int64_t* offdev = reinterpret_cast<const int64_t*>(s + offsetof(decltype(tab), off0));
+    char *A = s + 1024, *B = A + fb;
+    TL_TRY(launch(c, "pack", [&] { return tl::launch_pack(vp, in, A, offdev, 1, V3, Vp, c->stream); }));
+    TL_TRY(launch(c, "laplacian", [&] { return tl::launch_step(code, 1, cfg, gdev, 1, 0, tab.g.n_xy_tiles * tab.g.n_z_tiles, A, B, la, lb,
+                                        0, c->stream); }));
+    return launch(c, "unpack", [&] { return tl::launch_unpack(vp, B, out, offdev, 1, V3, Vp, c->stream); });
   } catch (...) {
     return host_failure(c);
   }
