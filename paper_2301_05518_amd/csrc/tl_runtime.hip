@@ -1108,6 +1108,36 @@ std::string tune_key(const tl_plan* p) {
   return k;
 }
 
+// Captures what enqueue(stream) queues in a graph.
+template <class F>
+int capture_graph(tl_ctx* c, hipGraphExec_t* exec, F&& enqueue) {
+  hipStream_t cs = nullptr;
+  HIP_TRY(c, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+  hipGraph_t graph = nullptr;
+  int rc = TL_OK;
+  if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) {
+    rc = fail(c, TL_ERR_HIP, "hipStreamBeginCapture failed");
+  } else {
+    rc = enqueue(cs);
+    hipError_t e = hipStreamEndCapture(cs, &graph);
+    if (rc == TL_OK && e != hipSuccess) rc = fail(c, TL_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
+  }
+  if (rc == TL_OK) {
+    hipError_t e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+    if (e != hipSuccess) rc = fail(c, TL_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
+  }
+  if (graph) (void)hipGraphDestroy(graph);
+  (void)hipStreamDestroy(cs);
+  return rc;
+}
+
+int plan_capture(tl_plan* p, int parity) {
+  if (p->graph[parity]) return TL_OK;
+  TL_TRY(capture_graph(p->ctx, &p->graph[parity], [&](hipStream_t cs) { return plan_enqueue(p, cs, parity); }));
+  p->ctx->stats.graphs_captured++;
+  return TL_OK;
+}
+
 // Time every candidate tiling on the plan's own data (buffer cur -> cur^1,
 // which leaves the input untouched), require each candidate's output to be
 // bit-identical to the first candidate's, keep the fastest.  Then, for batched
@@ -1291,26 +1321,37 @@ int plan_autotune(tl_plan* p) {
   }
   if (rc == TL_OK && !cands9.empty()) {
     // whole-run launches (all n steps each, up to kTuneSteps), against as many launches of the
-    // one-step winner from buffer to buffer.  The winner so far is timed over such a run too: launches that all read
-    // one buffer find their input in the caches, those of a run do not.
+    // one-step winner from buffer to buffer.  The winner so far is timed over such a run too (launches
+    // that all read one buffer find their input in the caches, those of a run do not), replayed from
+    // a graph if the plan's runs are.
     rc = upload_tiling(p, best_cfg, &p->single);
     if (rc == TL_OK && tu.cfg.variant == 8) rc = upload_tiling(p, tu.cfg, &p->tile);
     char* pair[2] = {p->buf[p->cur ^ 1], static_cast<char*>(ref)};
-    auto sequence = [&](const tl_plan::Tiling& t, int launches) -> int {
+    auto sequence = [&](const tl_plan::Tiling& t, int launches, hipStream_t s) -> int {
       for (int k = 0; k < launches; k++)
-        TL_TRY(plan_launch(p, t, c->stream, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k, 1));
+        TL_TRY(plan_launch(p, t, s, k ? pair[(k - 1) & 1] : p->buf[p->cur], pair[k & 1], -1, k, 1));
       return TL_OK;
     };
-    for (int rep = 0; rep < 2 && rc == TL_OK; rep++) {
+    const tl_plan::Tiling& winner = tu.cfg.variant == 8 ? p->tile : p->single;
+    const int launches = tu.cfg.variant == 8 ? whole / 2 : whole;
+    hipGraphExec_t replay = nullptr;
+    if (rc == TL_OK && (p->flags & TL_GRAPH))
+      rc = capture_graph(c, &replay, [&](hipStream_t s) { return sequence(winner, launches, s); });
+    for (int rep = 0; rep < 2 && rc == TL_OK; rep++) {   // one untimed
+      const int runs = replay ? 1 + 2 * rep : 1;
       (void)hipEventRecord(e0, c->stream);
-      rc = tu.cfg.variant == 8 ? sequence(p->tile, whole / 2) : sequence(p->single, whole);
+      for (int k = 0; k < runs && rc == TL_OK; k++) {
+        if (!replay) rc = sequence(winner, launches, c->stream);
+        else if (hipGraphLaunch(replay, c->stream) != hipSuccess) rc = fail(c, TL_ERR_HIP, "autotune graph launch failed");
+      }
       (void)hipEventRecord(e1, c->stream);
       float ms = 0.0f;
       if (rc == TL_OK && (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms, e0, e1) != hipSuccess))
         rc = fail(c, TL_ERR_HIP, "autotune timing failed");
-      best = ms / (tu.cfg.variant == 8 ? whole / 2 * 2 : whole);
+      best = ms / (runs * (tu.cfg.variant == 8 ? whole / 2 * 2 : whole));
     }
-    if (rc == TL_OK) rc = sequence(p->single, whole);
+    if (replay) (void)hipGraphExecDestroy(replay);
+    if (rc == TL_OK) rc = sequence(p->single, whole, c->stream);
     if (rc == TL_OK && (whole & 1) &&
         hipMemcpyAsync(ref, pair[0], p->buf_bytes, hipMemcpyDeviceToDevice, c->stream) != hipSuccess)
       rc = fail(c, TL_ERR_HIP, "autotune reference copy failed");
@@ -1468,30 +1509,6 @@ int plan_prepare(tl_plan* p) {
   }
   p->ready = true;
   return TL_OK;
-}
-
-int plan_capture(tl_plan* p, int parity) {
-  tl_ctx* c = p->ctx;
-  if (p->graph[parity]) return TL_OK;
-  hipStream_t cs = nullptr;
-  HIP_TRY(c, hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-  hipGraph_t graph = nullptr;
-  int rc = TL_OK;
-  if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-    rc = fail(c, TL_ERR_HIP, "hipStreamBeginCapture failed");
-  } else {
-    rc = plan_enqueue(p, cs, parity);
-    hipError_t e = hipStreamEndCapture(cs, &graph);
-    if (rc == TL_OK && e != hipSuccess) rc = fail(c, TL_ERR_HIP, "hipStreamEndCapture: %s", hipGetErrorString(e));
-  }
-  if (rc == TL_OK) {
-    hipError_t e = hipGraphInstantiate(&p->graph[parity], graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) rc = fail(c, TL_ERR_HIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
-    else c->stats.graphs_captured++;
-  }
-  if (graph) (void)hipGraphDestroy(graph);
-  (void)hipStreamDestroy(cs);
-  return rc;
 }
 
 // The same for a plan's whole-run memory: at most four pairs, 256 MB of scratch in all, are kept.
