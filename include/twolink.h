@@ -30,8 +30,8 @@
  *   (tl_plan_*) keeps the job pointers given to tl_plan_create until
  *   tl_plan_destroy.  Library-internal memory (resident packed fields,
  *   work lists, reduction partials, scratch) belongs to the context or plan;
- *   a context keeps up to 512 MB of the memory of earlier tl_smear calls for
- *   later ones until tl_destroy (or until an allocation fails).
+ *   a context keeps up to 512 MB of its destroyed plans' memory for later
+ *   plans until tl_destroy (or until an allocation fails).
  * - "device" pointers are HIP device memory of the context's device;
  *   "host" pointers are ordinary host memory read during the call.
  * - Geometry: tl_geom.L = {Lx, Ly, Lz, Lt}, every extent in [1, 4096] and
@@ -363,8 +363,9 @@ int tl_plan_get_info(const tl_plan *plan, tl_plan_info *info);
  */
 int tl_stream_time(tl_ctx *ctx, void *buf, int64_t bytes, int n_in, int kinds, int grid, int reps,
                    double *ms);
-/* Wait until the context's stream is idle and release the plan: W and psi may be freed or reused
- * on any stream afterwards.  Graphs that hold the plan's captured calls must not run any more. */
+/* Wait until the device is idle (as hipFree does: the caller may have captured the plan's calls and
+ * replayed them on any stream) and release the plan: W and psi may be freed or reused on any stream
+ * afterwards.  Graphs that hold the plan's captured calls must not run any more. */
 int tl_plan_destroy(tl_plan *plan);
 
 /* -------------------------------------------------------- reductions */

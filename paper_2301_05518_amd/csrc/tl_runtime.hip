@@ -71,7 +71,7 @@ struct tl_ctx {
   bool big_lds = false;       // dynamic-LDS limit raised for the LDS-staged step kernels
   void* scratch = nullptr;
   size_t scratch_bytes = 0;
-  // device memory of tl_smear's plans, kept for the next call (see mem_get)
+  // device memory of plans that are gone, kept for the next ones (see mem_get)
   struct MemBlock {
     void* p;
     size_t bytes;
@@ -191,7 +191,7 @@ void run_free(RunMem& m) {
   m = RunMem{};
 }
 
-// Frees everything the context keeps of earlier tl_smear calls.
+// Frees everything the context keeps of plans that are gone.
 void mem_drain(tl_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   for (auto& b : c->pool) (void)hipFree(b.p);
@@ -219,16 +219,13 @@ int dev_alloc(tl_ctx* c, void** p, size_t bytes) {
   return TL_OK;
 }
 
-// Memory of tl_smear's plans: a block given back (after its last work has finished) serves a later
-// call of the same context, which saves the allocator's round trips.  At most kPoolBlocks blocks and
+// Plan memory: a block given back after its last work has finished (see plan_free) serves a later
+// plan of the same context, which saves the allocator's round trips.  At most kPoolBlocks blocks and
 // kPoolBytes in all are kept (the newest), none over twice the size asked for is handed out, and
-// tl_destroy frees them.  A plan of tl_plan_create takes its memory from the allocator and gives
-// it back there: graphs that the caller captured may run it on streams the context does not know,
-// which only the wait inside hipFree covers.
+// tl_destroy frees them.
 constexpr size_t kPoolBlocks = 12, kPoolBytes = size_t(256) << 20;
 
-int mem_get(tl_ctx* c, bool pooled, void** p, size_t* bytes) {
-  if (!pooled) return dev_alloc(c, p, *bytes);
+int mem_get(tl_ctx* c, void** p, size_t* bytes) {
   *bytes = std::max<size_t>((*bytes + 4095) / 4096 * 4096, 4096);
   size_t best = c->pool.size();
   if (!c->fault_alloc)
@@ -246,10 +243,10 @@ int mem_get(tl_ctx* c, bool pooled, void** p, size_t* bytes) {
   return dev_alloc(c, p, *bytes);
 }
 
-void mem_put(tl_ctx* c, bool pooled, void* p, size_t bytes) {
+void mem_put(tl_ctx* c, bool keep, void* p, size_t bytes) {
   if (!p) return;
-  if (pooled && bytes <= kPoolBytes) {
-    // the blocks kept longest make room: a pool full of sizes that no call asks for any more would
+  if (keep && bytes <= kPoolBytes) {
+    // the blocks kept longest make room: a pool full of sizes that no plan asks for any more would
     // send every later call to the allocator (16^3 FP32, 20 steps: 83 instead of 61 us)
     while (!c->pool.empty() && (c->pool.size() >= kPoolBlocks || c->pool_bytes + bytes > kPoolBytes)) {
       (void)hipFree(c->pool.front().p);
@@ -568,7 +565,7 @@ struct tl_plan {
   size_t buf_cap[2] = {0, 0}, tables_cap = 0;   // bytes of the blocks behind buf and tables
   char* buf[2] = {nullptr, nullptr};
   int cur = 0;
-  bool pooled = false;                          // of a tl_smear call: its memory is kept for the next
+  bool of_call = false;                         // of a tl_smear call: no caller can have captured it
 
   // device tables: the step groups of both tilings (group_cap entries each), whole-run units,
   // per-job pack offsets, reduction fields, partials
@@ -933,7 +930,7 @@ int upload_run(tl_plan* p, const StepConfig& cfg, tl_plan::Tiling* t) {
       if (it == c->run_pool.end() || (it->bytes < r.scratch && k->bytes > it->bytes) ||
           (k->bytes >= r.scratch && k->bytes < it->bytes))
         it = k;
-    if (p->pooled && it != c->run_pool.end() && !c->fault_alloc) {
+    if (it != c->run_pool.end() && !c->fault_alloc) {
       p->run = *it;
       c->run_pool.erase(it);
     } else {
@@ -1512,10 +1509,10 @@ int plan_prepare(tl_plan* p) {
 }
 
 // The same for a plan's whole-run memory: at most four pairs, 256 MB of scratch in all, are kept.
-void run_put(tl_ctx* c, bool pooled, RunMem m) {
+void run_put(tl_ctx* c, bool keep, RunMem m) {
   size_t held = m.bytes;
   for (const auto& k : c->run_pool) held += k.bytes;
-  if (pooled && c->run_pool.size() < 4 && held <= kPoolBytes) {
+  if (keep && c->run_pool.size() < 4 && held <= kPoolBytes) {
     try {
       c->run_pool.push_back(m);
       return;
@@ -1525,22 +1522,25 @@ void run_put(tl_ctx* c, bool pooled, RunMem m) {
   run_free(m);
 }
 
-// Waits for the plan's queued work: afterwards its memory and the jobs' fields may go, on whatever
-// stream they are used next.  Returns whether a whole-run launch of the plan gave up unreported.
+// Waits for the plan's work: afterwards its memory and the jobs' fields may go, on whatever
+// stream they are used next.  A caller may have captured a created plan's calls and replay them on
+// streams the context does not know, so there the whole device is waited for (which hipFree would
+// do as well).  Returns whether a whole-run launch of the plan gave up unreported.
 bool plan_free(tl_plan* p) {
   if (!p) return false;
   bool failed = false;
   if (p->ctx && p->ctx->device >= 0) {
     DeviceGuard dg(p->ctx->device);
     tl_ctx* c = p->ctx;
-    (void)hipStreamSynchronize(c->stream);
+    const bool idle = (p->of_call ? hipStreamSynchronize(c->stream) : hipDeviceSynchronize()) == hipSuccess;
+    if (!idle) (void)hipGetLastError();   // the blocks then go back through hipFree
     RunTurn::idle(c);
     failed = fail_taken(p->fail);
     for (auto& g : p->graph)
       if (g) (void)hipGraphExecDestroy(g);
-    for (int k = 0; k < 2; k++) mem_put(c, p->pooled, p->buf[k], p->buf_cap[k]);
-    mem_put(c, p->pooled, p->tables, p->tables_cap);
-    if (p->run.ctl) run_put(c, p->pooled, p->run);
+    for (int k = 0; k < 2; k++) mem_put(c, idle, p->buf[k], p->buf_cap[k]);
+    mem_put(c, idle, p->tables, p->tables_cap);
+    if (p->run.ctl) run_put(c, idle, p->run);
     if (p->fail) {
       const size_t k = p->fail - c->run_fail;
       if (k + 1 < kFailWords) c->fail_used[k] = 0;
@@ -1847,9 +1847,9 @@ int tl_laplacian(tl_ctx* c, const tl_geom* g, const void* W, const int32_t* w_sl
 
 namespace {
 
-// tl_plan_create; pooled: a plan of tl_smear, which is loaded before it runs.
+// tl_plan_create; of_call: a plan of tl_smear, which is loaded before it runs.
 int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double sigma, int prec, unsigned flags,
-                bool pooled, tl_plan** out) {
+                bool of_call, tl_plan** out) {
   try {
     if (!c) return TL_ERR_ARG;
     if (!out) return fail(c, TL_ERR_ARG, "out is NULL");
@@ -1892,7 +1892,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     p->n_steps = n_steps;
     p->sigma = sigma;
     p->flags = flags;
-    p->pooled = pooled;
+    p->of_call = of_call;
     if (n_steps > 0) step_coeffs(one, n_steps, sigma, &p->alpha, &p->beta);
     const int max_width = (flags & TL_PLAIN) ? 1 : 4;
   
@@ -1941,7 +1941,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     for (int k = 0; k < 2 && rc == TL_OK; k++) {
       void* b = nullptr;
       size_t bytes = p->buf_bytes;
-      rc = mem_get(c, pooled, &b, &bytes);
+      rc = mem_get(c, &b, &bytes);
       if (rc == TL_OK) {
         p->buf[k] = static_cast<char*>(b);
         p->buf_cap[k] = bytes;
@@ -1958,7 +1958,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
     if (rc == TL_OK) {
       void* t = nullptr;
       size_t bytes = gbytes + ubytes + obytes + rbytes + pbytes;
-      rc = mem_get(c, pooled, &t, &bytes);
+      rc = mem_get(c, &t, &bytes);
       if (rc == TL_OK) {
         p->tables = static_cast<char*>(t);
         p->tables_cap = bytes;
@@ -1987,7 +1987,7 @@ int plan_create(tl_ctx* c, const tl_job* jobs, int n_jobs, int n_steps, double s
       }
       rc = upload(c, p->packoff_dev, host.data(), host.size());
     }
-    if (rc == TL_OK && (!pooled || (flags & TL_AUTOTUNE))) {
+    if (rc == TL_OK && (!of_call || (flags & TL_AUTOTUNE))) {
       // zero the resident buffers so tuning runs never see stale bit patterns
       for (int k = 0; k < 2 && rc == TL_OK; k++)
         if (hipMemsetAsync(p->buf[k], 0, p->buf_bytes, c->stream) != hipSuccess)

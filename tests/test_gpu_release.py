@@ -37,3 +37,44 @@ def test_returns_when_done(torch, how, stream):
                 c.smear([job], n, 1.0, "f32")
             assert s.query(), rep
         c.close()
+
+
+def test_destroy_waits_for_replays_elsewhere(torch):
+    """Replays of a captured run on a stream that the context does not know are done when
+    tl_plan_destroy returns, and the next plan's memory is its own."""
+    import paper_2301_05518_amd as tl
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    L, ts, n = (32, 32, 32, 1), [0, 0, 0], 400
+    c = tl.Context(0, side)
+    with torch.cuda.stream(side):
+        g = torch.Generator(device="cuda").manual_seed(78)
+        U = torch.view_as_complex(0.3 * torch.randn(1, 32, 32, 32, 4, 3, 3, 2, dtype=torch.float64, device="cuda", generator=g))
+        src = torch.view_as_complex(torch.randn(3, 32, 32, 32, 3, 2, dtype=torch.float64, device="cuda", generator=g))
+        W = c.build_twolinks(L, U, "f32")
+        jobs = [tl.Job(L, W, ts, src.clone()) for _ in range(2)]
+        want = None
+        for rep in range(4):
+            plan = c.plan([jobs[0]], n, 1.0, "f32")
+            plan.load()
+            side.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                plan.run()
+            # several ms of replays on the other stream, then a new plan in the destroyed one's memory
+            with torch.cuda.stream(other):
+                for _ in range(10):
+                    graph.replay()
+            assert not other.query()
+            plan.close()
+            assert other.query(), rep
+            jobs[1].psi.copy_(src)
+            again = c.plan([jobs[1]], 20, 1.0, "f32")
+            again.load()
+            again.run()
+            again.store()
+            c.sync()
+            want = jobs[1].psi.clone() if want is None else want
+            assert torch.equal(jobs[1].psi, want), rep
+            again.close()
+            del graph
+    c.close()
